@@ -87,6 +87,26 @@ def test_backward_parity_and_determinism(env, N, d):
     assert rel(a, ref) <= TOL
 
 
+@pytest.mark.parametrize("N,d", [(47, 16), (48, 17), (8191, 15), (8192, 16), (8193, 17), (16385, 32), (20001, 4)])
+def test_tile_edges(env, N, d):
+    """Sample counts around a tile and around the point where a backward
+    workgroup takes several tiles (256 x 32 samples), feature counts around
+    the 16-wide operand tile; TOL is the library's relative error bar."""
+    glass, torch = env
+    print(f"mlp tile edges N={N} d={d}", flush=True)
+    X, t, p = case(N, d, 5)
+    Xd, pd, H1, H2, y = run_forward(glass, torch, X, p)
+    wsb = glass.glass_mlp_backward_workspace_size(N, d)
+    ws = torch.full(((wsb + 3) // 4,), float("nan"), dtype=torch.float32, device="cuda:0")
+    g = torch.full((glass.glass_mlp_num_params(d),), float("nan"), dtype=torch.float32, device="cuda:0")
+    assert glass.glass_mlp_backward(N, d, Xd, pd, H1, H2, y, dev(torch, t), g, ws, wsb) == 0
+    torch.cuda.synchronize()
+    h1, h2, yr = mlp.forward(p.astype(np.float64), X.astype(np.float64))
+    for got, ref in ((H1, h1), (H2, h2), (y, yr)):
+        assert rel(got.cpu().numpy(), ref) <= TOL
+    assert rel(g.cpu().numpy(), mlp.grad(p.astype(np.float64), X.astype(np.float64), t.astype(np.float64))) <= TOL
+
+
 def test_backward_rejects_small_workspace(env):
     glass, torch = env
     X, t, p = case(40, 14, 3)
