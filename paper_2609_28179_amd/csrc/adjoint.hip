@@ -11,9 +11,13 @@
 //   thread  (n <= 16) one problem per lane: L in VGPRs (compile-time n),
 //           G and X staged through LDS, dA written through LDS passes as
 //           coalesced stores.
-//   wave    one problem per wavefront, the wave-scope substitutions of
-//           chol.hip; lane i accumulates row i of dA from v_readlane
-//           broadcasts of x_j and dB_j, rows leave through the 8-row LDS chunk.
+//   wave    one problem per wavefront.  Up to order 24 the wave-scope
+//           substitutions of chol.hip; lane i accumulates row i of dA from
+//           v_readlane broadcasts of x_j and dB_j, rows leave through the 8-row
+//           LDS chunk.  From order 25 the blocked routines of chol_blk.hpp:
+//           one right-hand side by the VALU substitutions and an outer product
+//           on the lanes, several by the matrix-core solve and rank-16
+//           products; 16-row block rows of dA leave through LDS.
 //   sub-wave  (n <= 32) 64 / SEG problems per wavefront on SEG-lane segments
 //           (SEG = 16 up to order 16, 32 above), the segment substitutions of
 //           the sub-wave Cholesky kernels; x_j and dB_j reach lane i by
@@ -25,6 +29,7 @@
 #include "device_common.hpp"
 #include "glass_internal.hpp"
 #include "chol_device.hpp"
+#include "chol_blk.hpp"
 
 namespace glass {
 namespace {
@@ -219,6 +224,224 @@ __global__ void __launch_bounds__(512) adjoint_wave(int n, int nrhs, int batch, 
     wave_chunks_desc<NB>(d, buf, dA + p * n * n, vec, n, lane, false, 0.f, 1.f);
 }
 
+// ------------------------------------------------ blocked form, orders 25..64
+// LDS floats of one wavefront: the staged block row of dA and, with several
+// right-hand sides, one exchange block per tile of the transposes.
+constexpr int adjoint_blk_floats(int nblk, bool one) {
+    return one ? 16 * blk_row_stride(nblk) : nblk * 16 * kXS;
+}
+static_assert(adjoint_blk_floats(2, false) >= 16 * blk_row_stride(2) && adjoint_blk_floats(3, false) >= 16 * blk_row_stride(3) &&
+                  adjoint_blk_floats(4, false) >= 16 * blk_row_stride(4),
+              "the staged block row fits the exchange blocks");
+
+// Rows 16 i .. of a row-major n x n matrix from the staged block row at xs, as
+// whole rows (16-byte pieces when vec).
+template <int NBLK, bool FULL>
+GLASS_DEV void block_row_out(float* Mg, int i, int n, const float* xs, int lane, bool vec) {
+    constexpr int RS = blk_row_stride(NBLK);
+    float* dst = Mg + (size_t)16 * i * n;
+    if (FULL) {
+        constexpr int N4 = 4 * NBLK;
+#pragma unroll
+        for (int g = lane; g < 16 * N4; g += 64)
+            reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + (g / N4) * RS + 4 * (g % N4));
+        return;
+    }
+    const int rows = min(16, n - 16 * i);
+    if (vec) {
+        const int n4 = n >> 2;
+        const FastDiv f4 = make_fastdiv((uint32_t)n4);
+        for (int g = lane; g < rows * n4; g += 64) {
+            const int rr = (int)fdiv((uint32_t)g, f4), c4 = g - rr * n4;
+            reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + rr * RS + 4 * c4);
+        }
+    } else {
+        const FastDiv fn = make_fastdiv((uint32_t)n);
+        for (int g = lane; g < rows * n; g += 64) {
+            const int rr = (int)fdiv((uint32_t)g, fn), cc = g - rr * n;
+            dst[g] = xs[rr * RS + cc];
+        }
+    }
+}
+
+// One right-hand side: the substitutions of blk_solve1 on g, then block (i, j)
+// of dA in T layout from row i's entries in R form and column j's in C form.
+// Entry (j, i) is the same two products in the other order, so dA comes out
+// bit-symmetric.  Bound by the write of dA and the whole-line read of L;
+// against the row-per-lane form (adjoint_wave at these orders, whose 2 n
+// substitution steps and n broadcasts per row ran on one chain), at 16,384
+// problems: n = 25 47.6 -> 23.7 us, n = 64 149.5 -> 93.7.
+template <int NBLK, bool FULL>
+__global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const float* __restrict__ L,
+                                                    const float* __restrict__ X, const float* G, float* dB,
+                                                    float* __restrict__ dA) {
+    extern __shared__ float lds[];
+    constexpr int RS = blk_row_stride(NBLK);
+    const int w = wave_index(), lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
+    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
+    if (p >= batch) return;
+    float* xs = lds + (size_t)w * adjoint_blk_floats(NBLK, true);
+    f4_t T[NBLK * (NBLK + 1) / 2];
+    float b[NBLK], x[NBLK], pend[NBLK];
+    blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
+    blk_x_load<NBLK, FULL>(b, G + p * n, n, r);
+    blk_x_load<NBLK, FULL>(x, X + p * n, n, r);
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) pend[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) {
+        float a[16];
+        const float myinv = recip(diag_rows<true>(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
+        blk_fwd_step<NBLK>(T, k, a, myinv, b, pend, q);
+    }
+    blk_bwd1<NBLK>(T, b, xs, q, r);
+    blk_x_store<NBLK, FULL>(b, dB + p * n, n, q, r);
+    float bc[NBLK][4], xc[NBLK][4];
+#pragma unroll
+    for (int j = 0; j < NBLK; ++j) {
+        r_to_c(b[j], bc[j], q);
+        r_to_c(x[j], xc[j], q);
+    }
+    const bool vec = FULL || ((n & 3) == 0 && aligned16(dA));
+#pragma unroll
+    for (int i = 0; i < NBLK; ++i) {
+#pragma unroll
+        for (int j = 0; j < NBLK; ++j) {
+            f4_t v;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = -0.5f * sym_pair(0.f, b[i], xc[j][c], x[i], bc[j][c]);
+            *reinterpret_cast<f4_t*>(xs + r * RS + 16 * j + 4 * q) = v;
+        }
+        wave_sync();
+        block_row_out<NBLK, FULL>(dA + p * n * n, i, n, xs, lane, vec);
+        wave_sync();
+    }
+}
+
+// Columns cb .. cb + 15 of a row-major [n][nr] matrix in T layout per block row
+// (lane (q, r): row 16 k + r, columns cb + 4 q ..; zero past n and nr).
+template <int NBLK, bool FULL>
+GLASS_DEV void cols_load_t(f4_t (&V)[NBLK], const float* Mg, int n, int nr, int cb, int q, int r) {
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool ok = (FULL || 16 * k + r < n) && cb + 4 * q + e < nr;
+            const float v = Mg[ok ? (16 * k + r) * nr + cb + 4 * q + e : 0];
+            V[k][e] = ok ? v : 0.f;
+        }
+}
+
+// Several right-hand sides, 16 columns at a time: the matrix-core solve of the
+// blocked kernels (Y_k = L_kk^{-1} (G_k - sum L_kj Y_j), then its transpose),
+// then the lower blocks D_ij = dB_i X_j^T + X_i dB_j^T as products over the
+// columns.  With dB_i and X_i in T layout (dB through an LDS transpose), they
+// are M and, read as accumulator operands, the transposes.  D_ij comes out with lane
+// (q, r) holding rows 4 q .., column r: written to LDS by element it is block
+// (i, j), as 16-byte pieces block (j, i); the diagonal block's lower entries
+// go to both places, so dA is bit-symmetric.  Past 16 columns D is formed
+// after the solves, from dB read back, so that L is no longer live.
+// Bound by the wavefront's chain of diagonal-block inverses and solves at
+// 3-5 wavefronts per SIMD.  Against the row-per-lane form, 16,384 problems:
+// n = 36, nr = 3 117.7 -> 58.3 us, n = 64, nr = 8 621.6 -> 112.1.
+template <int NBLK, bool FULL>
+__global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, const float* __restrict__ L,
+                                                   const float* __restrict__ X, const float* G, float* dB,
+                                                   float* __restrict__ dA) {
+    extern __shared__ float lds[];
+    constexpr int RS = blk_row_stride(NBLK), NT = NBLK * (NBLK + 1) / 2;
+    const int w = wave_index(), lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
+    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
+    if (p >= batch) return;
+    float* xs = lds + (size_t)w * adjoint_blk_floats(NBLK, false);
+    const float* Xg = X + p * n * nr;
+    const float* Gg = G + p * n * nr;
+    float* Bg = dB + p * n * nr;
+    f4_t Y[NBLK], Xt[NBLK];
+    {
+        f4_t T[NT], linv[NBLK];
+        blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
+        rhs_load<NBLK, FULL>(Y, Gg, n, nr, 0, q, r);
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) {
+            float m[16];
+            const float myinv = recip(diag_rows<true>(T[BI(k, k)], m, xs, q, r)), nmy = -myinv;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) m[j] *= nmy;
+            linv[k] = tri_inverse_l(m, myinv, q, r);
+        }
+#pragma unroll
+        for (int k = 1; k < NBLK; ++k)
+#pragma unroll
+            for (int j = 0; j < k; ++j) T[BI(k, j)] = neg4(T[BI(k, j)]);
+        for (int cb = 0; cb < nr; cb += 16) {
+            if (cb) rhs_load<NBLK, FULL>(Y, Gg, n, nr, cb, q, r);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) {
+                f4_t s = Y[k];
+#pragma unroll
+                for (int j = 0; j < k; ++j) s = mma(T[BI(k, j)], Y[j], s);
+                Y[k] = mma(linv[k], s, zero4());
+            }
+            if (cb == 0) cols_load_t<NBLK, FULL>(Xt, Xg, n, nr, 0, q, r);  // in flight behind the backward pass
+            BwdBlk<NBLK, NBLK - 1>::run(T, linv, Y, xs, q, r);
+            rhs_store<NBLK, FULL>(Y, Bg, n, nr, cb, q, r);
+        }
+    }
+    f4_t D[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) D[t] = zero4();
+    for (int cb = 0; cb < nr; cb += 16) {
+        f4_t Bt[NBLK];
+        if (nr <= 16) {
+            f4_t v[4] = {zero4(), zero4(), zero4(), zero4()};
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) v[k] = Y[k];
+            transpose_blocks<NBLK>(v, xs, q, r);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) Bt[k] = v[k];
+        } else {
+            wave_sync();  // the dB this wavefront has stored
+            cols_load_t<NBLK, FULL>(Bt, Bg, n, nr, cb, q, r);
+            if (cb) cols_load_t<NBLK, FULL>(Xt, Xg, n, nr, cb, q, r);
+        }
+#pragma unroll
+        for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) D[BI(i, j)] = mma(Xt[i], Bt[j], mma(Bt[i], Xt[j], D[BI(i, j)]));
+    }
+    wave_sync();
+    const bool vec = FULL || ((n & 3) == 0 && aligned16(dA));
+#pragma unroll
+    for (int i = 0; i < NBLK; ++i) {
+#pragma unroll
+        for (int j = 0; j < NBLK; ++j) {
+            if (j > i) {
+                const f4_t d = D[BI(j, i)];
+                *reinterpret_cast<f4_t*>(xs + r * RS + 16 * j + 4 * q) =
+                    f4_t{-0.5f * d[0], -0.5f * d[1], -0.5f * d[2], -0.5f * d[3]};
+            } else {
+                const f4_t d = D[BI(i, j)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = -0.5f * d[e];
+                    if (j < i) {
+                        xs[(4 * q + e) * RS + 16 * j + r] = v;
+                    } else if (4 * q + e >= r) {
+                        xs[(4 * q + e) * RS + 16 * j + r] = v;
+                        xs[r * RS + 16 * j + 4 * q + e] = v;
+                    }
+                }
+            }
+        }
+        wave_sync();
+        block_row_out<NBLK, FULL>(dA + p * n * n, i, n, xs, lane, vec);
+        wave_sync();
+    }
+}
+
 template <int SEG, int NB, int J>
 struct SegDa {
     // d[j] += dB_i x_j + x_i dB_j, x_j and dB_j broadcast from lane j of the segment
@@ -293,8 +516,8 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n, r = sh.nrhs;
     dim3 grid((unsigned)g.grid), block(g.threads);
+    auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
     if (g.scope == GLASS_SCOPE_THREAD) {
-        auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
         if (r == 1 && al16(L) && al16(X) && al16(G) && al16(dB) && al16(dA)) {
             switch (n) {
 #define CASE1(N) \
@@ -312,6 +535,23 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
 #undef CASE
         default: return (int)hipErrorInvalidValue;
         }
+    } else if (g.scope == GLASS_SCOPE_WAVE && n >= kBlkMinN) {
+        // whole tiles from order 25, where the blocked solves take over from the
+        // row-per-lane ones (below, 16 x 16 tiles would be mostly padding)
+        const int nblk = blk_nblk(n);
+        const bool full = n == 16 * nblk && al16(L) && al16(dA);
+        const size_t lds = sizeof(float) * (size_t)adjoint_blk_floats(nblk, r == 1) * g.pack;
+#define CASE(NBLK, FULL)                                                                                            \
+    if (nblk == NBLK && full == FULL) {                                                                             \
+        if (r == 1)                                                                                                 \
+            hipLaunchKernelGGL((adjoint_blk1<NBLK, FULL>), grid, block, lds, st, n, batch, L, X, G, dB, dA);         \
+        else                                                                                                        \
+            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL>), grid, block, lds, st, n, r, batch, L, X, G, dB, dA);       \
+        return (int)hipGetLastError();                                                                              \
+    }
+        CASE(2, false) CASE(2, true) CASE(3, false) CASE(3, true) CASE(4, false) CASE(4, true)
+#undef CASE
+        return (int)hipErrorInvalidValue;
     } else if (g.scope == GLASS_SCOPE_WAVE) {
         const int region = (int)wave_region_floats(sh);
         switch (bucket8(n)) {
@@ -319,7 +559,7 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
     case NB:                                                                                                     \
         hipLaunchKernelGGL(adjoint_wave<NB>, grid, block, g.lds_bytes, st, n, r, batch, L, X, G, dB, dA, region); \
         break;
-            CASE(8) CASE(16) CASE(24) CASE(32) CASE(40) CASE(48) CASE(56) CASE(64)
+            CASE(8) CASE(16) CASE(24)
 #undef CASE
         default: return (int)hipErrorInvalidValue;
         }

@@ -127,3 +127,31 @@ def test_adjoint_thread_direct_form_bit_identical(env, n):
     assert normwise(out[0][0], dB_ref).max() <= TOL
     assert normwise(out[0][1], dA_ref).max() <= TOL
     assert np.array_equal(out[0][1], np.swapaxes(out[0][1], 1, 2))
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("n,r", [(25, 1), (31, 2), (32, 1), (32, 16), (33, 17), (39, 5), (48, 1), (48, 15), (49, 33),
+                                 (50, 1), (63, 64), (64, 1), (64, 17)])
+def test_adjoint_blocked_edges(env, n, r, shift):
+    """The blocked wave-scope form at the edges of its tiles (orders) and of
+    its 16-column groups (right-hand sides), on operands on and off 16-byte
+    alignment: the oracle's tolerance, dA bit-symmetric, guards untouched."""
+    from helpers import guarded, guards_intact
+    glass, torch = env
+    batch, pad = 37, 64 + shift
+    print(f"adjoint blocked n={n} nrhs={r} shift={shift}", flush=True)
+    rng = inputs.rng_for(3, "adjoint", n, batch, 500 + r)
+    L = inputs.lower_factor(rng, batch, n)
+    X, W = inputs.uniform(rng, (batch, n, r)), inputs.uniform(rng, (batch, n, r))
+    dB_ref, dA_ref = oracle.posv_adjoint(L, X, W)
+    (_, Lt), (_, Xt), (_, Gt) = (guarded(torch, a, "cuda:0", pad) for a in (L, X, W))
+    dBf, dBt = guarded(torch, np.zeros_like(X), "cuda:0", pad)
+    dAf, dAt = guarded(torch, np.zeros_like(L), "cuda:0", pad)
+    for pack in (1, 8):
+        assert glass.glass_posv_adjoint_batched(n, r, batch, Lt, Xt, Gt, dBt, dAt, ("wave", pack)) == 0
+        torch.cuda.synchronize()
+        dA = dAt.cpu().numpy()
+        assert normwise(dBt.cpu().numpy(), dB_ref).max() <= TOL
+        assert normwise(dA, dA_ref).max() <= TOL
+        assert np.array_equal(dA, np.swapaxes(dA, 1, 2))
+        assert guards_intact(dBf, pad) and guards_intact(dAf, pad)
