@@ -234,36 +234,6 @@ static_assert(adjoint_blk_floats(2, false) >= 16 * blk_row_stride(2) && adjoint_
                   adjoint_blk_floats(4, false) >= 16 * blk_row_stride(4),
               "the staged block row fits the exchange blocks");
 
-// Rows 16 i .. of a row-major n x n matrix from the staged block row at xs, as
-// whole rows (16-byte pieces when vec).
-template <int NBLK, bool FULL>
-GLASS_DEV void block_row_out(float* Mg, int i, int n, const float* xs, int lane, bool vec) {
-    constexpr int RS = blk_row_stride(NBLK);
-    float* dst = Mg + (size_t)16 * i * n;
-    if (FULL) {
-        constexpr int N4 = 4 * NBLK;
-#pragma unroll
-        for (int g = lane; g < 16 * N4; g += 64)
-            reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + (g / N4) * RS + 4 * (g % N4));
-        return;
-    }
-    const int rows = min(16, n - 16 * i);
-    if (vec) {
-        const int n4 = n >> 2;
-        const FastDiv f4 = make_fastdiv((uint32_t)n4);
-        for (int g = lane; g < rows * n4; g += 64) {
-            const int rr = (int)fdiv((uint32_t)g, f4), c4 = g - rr * n4;
-            reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + rr * RS + 4 * c4);
-        }
-    } else {
-        const FastDiv fn = make_fastdiv((uint32_t)n);
-        for (int g = lane; g < rows * n; g += 64) {
-            const int rr = (int)fdiv((uint32_t)g, fn), cc = g - rr * n;
-            dst[g] = xs[rr * RS + cc];
-        }
-    }
-}
-
 // One right-hand side: the substitutions of blk_solve1 on g, then block (i, j)
 // of dA in T layout from row i's entries in R form and column j's in C form.
 // Entry (j, i) is the same two products in the other order, so dA comes out
@@ -304,7 +274,6 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
         r_to_c(b[j], bc[j], q);
         r_to_c(x[j], xc[j], q);
     }
-    const bool vec = FULL || ((n & 3) == 0 && aligned16(dA));
 #pragma unroll
     for (int i = 0; i < NBLK; ++i) {
 #pragma unroll
@@ -315,7 +284,7 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
             *reinterpret_cast<f4_t*>(xs + r * RS + 16 * j + 4 * q) = v;
         }
         wave_sync();
-        block_row_out<NBLK, FULL>(dA + p * n * n, i, n, xs, lane, vec);
+        block_row_store<NBLK, FULL>(dA + p * n * n, i, n, xs, lane);
         wave_sync();
     }
 }
@@ -324,14 +293,16 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
 // (lane (q, r): row 16 k + r, columns cb + 4 q ..; zero past n and nr).
 template <int NBLK, bool FULL>
 GLASS_DEV void cols_load_t(f4_t (&V)[NBLK], const float* Mg, int n, int nr, int cb, int q, int r) {
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(Mg, (uint32_t)(n * nr) * 4u);
+    int off[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) off[e] = cb + 4 * q + e < nr ? (r * nr + cb + 4 * q + e) * 4 : kOob;
 #pragma unroll
     for (int k = 0; k < NBLK; ++k)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const bool ok = (FULL || 16 * k + r < n) && cb + 4 * q + e < nr;
-            const float v = Mg[ok ? (16 * k + r) * nr + cb + 4 * q + e : 0];
-            V[k][e] = ok ? v : 0.f;
-        }
+        for (int e = 0; e < 4; ++e)
+            V[k][e] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rs, off[e] + 16 * k * nr * 4, 0, 0));
 }
 
 // Several right-hand sides, 16 columns at a time: the matrix-core solve of the
@@ -413,7 +384,6 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
             for (int j = 0; j <= i; ++j) D[BI(i, j)] = mma(Xt[i], Bt[j], mma(Bt[i], Xt[j], D[BI(i, j)]));
     }
     wave_sync();
-    const bool vec = FULL || ((n & 3) == 0 && aligned16(dA));
 #pragma unroll
     for (int i = 0; i < NBLK; ++i) {
 #pragma unroll
@@ -437,7 +407,7 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
             }
         }
         wave_sync();
-        block_row_out<NBLK, FULL>(dA + p * n * n, i, n, xs, lane, vec);
+        block_row_store<NBLK, FULL>(dA + p * n * n, i, n, xs, lane);
         wave_sync();
     }
 }

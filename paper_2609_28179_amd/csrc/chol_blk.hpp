@@ -59,64 +59,61 @@ GLASS_DEV f4_t mma(const f4_t& m, const f4_t& x, f4_t c) {
     return c;
 }
 
-// The lower blocks of the problem at Ag in T layout.  FULL: n == 16 NBLK.
-// The strict upper part of a diagonal block is not read (zero).  Otherwise
-// every lane still issues one 16-byte load per piece into registers of its
-// own, all before any is read (loads under a per-lane branch, or a separate
-// element-wise load of a row's last piece, made the compiler wait for each
-// piece in turn): a piece past the problem reads the first one (in range)
-// and is cleared, the piece of the last row that would run past the problem
-// is loaded as its last 16 bytes and moved down, and the entries past
-// column n of the other rows are cleared; loads are 4-byte aligned.
+// A byte offset past the end of every descriptor of these routines: a buffer
+// load there returns 0 and a buffer store there is dropped, so a lane with
+// nothing to move needs no branch.  (Raw-buffer range checking looks at the
+// per-lane offset only, not at the scalar one; multi-dword accesses need
+// 4-byte alignment.)
+constexpr int kOob = 0x40000000;
+
+// The lower blocks of the problem at Ag in T layout.  FULL: n == 16 NBLK;
+// otherwise 16 (NBLK - 1) < n < 16 NBLK, so that only the last block row and
+// column are cut: the blocks above it load at compile-time positions, rows
+// past n load nothing, and the pieces of the last diagonal block past column
+// n hold entries right of the diagonal, which are cleared anyway.  The one
+// piece that would run past the problem (row n - 1, over the last column) is
+// loaded as the problem's last 16 bytes and moved down.  The strict upper
+// part of a diagonal block is cleared.  Every load is issued before any is
+// read.
 template <int NBLK, bool FULL>
 GLASS_DEV void blk_load(f4_t (&T)[NBLK * (NBLK + 1) / 2], const float* Ag, int n, int q, int r) {
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(Ag, (uint32_t)(n * n) * 4u);
+    constexpr int LB = NBLK - 1;
+    const int lane_off = (r * n + 4 * q) * 4;
+    const int R = 16 * LB + r, C = 16 * LB + 4 * q;  // of the last diagonal block
+    const bool tail = !FULL && R == n - 1 && C + 4 > n;
 #pragma unroll
     for (int i = 0; i < NBLK; ++i) {
-        const int R = 16 * i + r;
 #pragma unroll
         for (int j = 0; j <= i; ++j) {
-            const int C = 16 * j + 4 * q;
-            f4_t v = zero4();
-            if (FULL) {
-                v = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (R * n + C) * 4, 0, 0));
-            } else {  // a piece past the problem loads the first one (in range) and is cleared below
-                const int off = !(R < n && C < n) ? 0 : (R == n - 1 && C + 4 > n) ? n * n - 4 : R * n + C;
-                v = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off * 4, 0, 0));
-            }
-            T[BI(i, j)] = v;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < NBLK; ++i) {
-        const int R = 16 * i + r;
-#pragma unroll
-        for (int j = 0; j <= i; ++j) {
-            const int C = 16 * j + 4 * q;
-            f4_t v = T[BI(i, j)];
-            if (!FULL) {
-                if (!(R < n && C < n)) v = zero4();
-                if (16 * j < n && 16 * j + 16 > n) {  // the block column that holds column n - 1
-                    const int over = C + 4 - n;          // entries of the piece past column n
-                    const f4_t d = over == 1   ? f4_t{v[1], v[2], v[3], 0.f}
-                                   : over == 2 ? f4_t{v[2], v[3], 0.f, 0.f}
-                                               : f4_t{v[3], 0.f, 0.f, 0.f};
-                    const f4_t k = f4_t{C < n ? v[0] : 0.f, C + 1 < n ? v[1] : 0.f, C + 2 < n ? v[2] : 0.f,
-                                        C + 3 < n ? v[3] : 0.f};
-                    v = (R == n - 1 && over > 0 && over < 4) ? d : k;
-                }
-                if (i == j && R >= n) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (4 * q + e == r) ? 1.f : 0.f;
+            int off = lane_off, soff = (16 * i * n + 16 * j) * 4;
+            if (!FULL && i == LB) {
+                if (R >= n) off = kOob;
+                if (j == LB) {
+                    off = (R >= n || C > R) ? kOob : tail ? (n * n - 4) * 4 : (R * n + C) * 4;
+                    soff = 0;
                 }
             }
-            if (i == j) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = (4 * q + e <= r) ? v[e] : 0.f;
-            }
-            T[BI(i, j)] = v;
+            T[BI(i, j)] = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, soff, 0));
         }
     }
+    if (!FULL) {
+        f4_t v = T[BI(LB, LB)];
+        const int over = C + 4 - n;  // entries of the piece past column n
+        const f4_t d = over == 1   ? f4_t{v[1], v[2], v[3], 0.f}
+                       : over == 2 ? f4_t{v[2], v[3], 0.f, 0.f}
+                                   : f4_t{v[3], 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float x = tail ? d[e] : v[e];
+            v[e] = R < n ? x : (4 * q + e == r) ? 1.f : 0.f;
+        }
+        T[BI(LB, LB)] = v;
+    }
+#pragma unroll
+    for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) T[BI(i, i)][e] = (4 * q + e <= r) ? T[BI(i, i)][e] : 0.f;
 }
 
 // Diagonal block (T layout) to row-per-lane form: lane (q, r) receives row r
@@ -207,12 +204,63 @@ GLASS_DEV void rows_zero_diag(const float (&a)[16], float (&az)[16], float* xs, 
     wave_sync();
 }
 
+// Rows 16 k .. of a row-major n x n matrix from the staged block row at xs
+// (row stride blk_row_stride): a block row is contiguous in memory, so it
+// leaves as 16-byte pieces whatever the order and alignment (a piece that
+// spans two rows is gathered by element), one per lane and round in NBLK
+// rounds.  The last piece of an odd-sized last block row moves back over its
+// neighbour and writes the same values.  The row of an element comes from
+// (g + 1/2) * (1 / n) in FP32: g < 1024 and n <= 64 keep its error below
+// 2e-5, against a distance of 1 / (2 n) >= 1/128 from the next integer.
+// With element-wise 4-byte stores (an integer division each) and loads and
+// right-hand-side accesses under lane conditions, the cut instances issued
+// nearly twice the instructions of the whole-tile ones (POSV n = 64, several
+// columns: 4511 against 2521 static, now about 2900).  At 16,384 problems: adjoint
+// n = 36, 3 columns 58.3 -> 48.3 us, n = 25 23.7 -> 19.1, POSV n = 36, 3 columns 67 -> 63
+// (there the diagonal blocks' VALU work is the bound), ragged solve of
+// 50,000 systems 153 -> 146.
+template <int NBLK, bool FULL>
+GLASS_DEV void block_row_store(float* Mg, int k, int n, const float* xs, int lane) {
+    constexpr int RS = blk_row_stride(NBLK);
+    float* dst = Mg + (size_t)16 * k * n;
+    if (FULL) {
+        constexpr int N4 = 4 * NBLK;  // 16-byte pieces per row
+#pragma unroll
+        for (int g = lane; g < 16 * N4; g += 64) {
+            const int rr = g / N4, c4 = g % N4;
+            reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + rr * RS + 4 * c4);
+        }
+        return;
+    }
+    const bool last = k == NBLK - 1;
+    const int len = (last ? n - 16 * k : 16) * n;
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(dst, (uint32_t)len * 4u);
+    asm volatile("" : "+v"(lane));  // the piece addresses are formed anew for each block row, not kept in registers between them
+    const float rn = recip((float)n);
+    const bool whole = (n & 3) == 0;
+#pragma unroll
+    for (int u = 0; u < NBLK; ++u) {
+        const int g = 4 * (lane + 64 * u), at = min(g, len - 4);
+        const int rr = (int)(((float)at + 0.5f) * rn), cc = at - rr * n;
+        const float* src = xs + rr * RS + cc;
+        f4_t v;
+        if (whole) {
+            v = *reinterpret_cast<const f4_t*>(src);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = src[cc + e >= n ? e + RS - n : e];
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rs,
+                                               g < len ? at * 4 : kOob, 0, 0);
+    }
+}
+
 // Block row k of L (rows 16 k .. 16 k + 15): the finished blocks left of the
 // diagonal, the diagonal block from its rows and +0 to the right, staged in
 // LDS and stored as whole rows.
 template <int NBLK, bool FULL>
 GLASS_DEV void store_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&a)[16], float* Ag,
-                               int n, float* xs, int q, int r, int lane, bool vec) {
+                               int n, float* xs, int q, int r, int lane) {
     constexpr int kRS = blk_row_stride(NBLK);
 #pragma unroll
     for (int j = 0; j < NBLK; ++j) {
@@ -226,31 +274,7 @@ GLASS_DEV void store_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, co
                 f4_t{a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]};
     }
     wave_sync();
-    float* dst = Ag + (size_t)16 * k * n;
-    if (FULL) {
-        constexpr int N4 = 4 * NBLK;  // 16-byte pieces per row
-#pragma unroll
-        for (int g = lane; g < 16 * N4; g += 64) {
-            const int rr = g / N4, c4 = g % N4;
-            reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + rr * kRS + 4 * c4);
-        }
-    } else {
-        const int rows = min(16, n - 16 * k);
-        if (vec) {
-            const int n4 = n >> 2;
-            const FastDiv f4 = make_fastdiv((uint32_t)n4);
-            for (int g = lane; g < rows * n4; g += 64) {
-                const int rr = (int)fdiv((uint32_t)g, f4), c4 = g - rr * n4;
-                reinterpret_cast<f4_t*>(dst)[g] = *reinterpret_cast<const f4_t*>(xs + rr * kRS + 4 * c4);
-            }
-        } else {
-            const FastDiv fn = make_fastdiv((uint32_t)n);
-            for (int g = lane; g < rows * n; g += 64) {
-                const int rr = (int)fdiv((uint32_t)g, fn), cc = g - rr * n;
-                dst[g] = xs[rr * kRS + cc];
-            }
-        }
-    }
+    block_row_store<NBLK, FULL>(Ag, k, n, xs, lane);
     wave_sync();
 }
 
@@ -270,29 +294,38 @@ GLASS_DEV void transpose_blocks(f4_t (&v)[4], float* xs, int q, int r) {
 
 // Columns cb .. cb + 15 of the row-major [n][nr] right-hand sides, in
 // accumulator layout per block row (lane (q, r), element e: row 16 k + 4 q + e,
-// column cb + r).
+// column cb + r): buffer accesses at a per-lane offset plus a scalar row
+// offset, out of range for columns past nr; the last block row carries its
+// whole offset per lane, so that rows past n fall out of range too.
+template <int NBLK, bool FULL>
+struct RhsOffsets {
+    int lane, nr;
+    GLASS_DEV RhsOffsets(int nr_, int cb, int q, int r)
+        : lane(cb + r < nr_ ? (4 * q * nr_ + cb + r) * 4 : kOob), nr(nr_) {}
+    GLASS_DEV int v(int k, int e) const { return !FULL && k == NBLK - 1 ? lane + (16 * k + e) * nr * 4 : lane; }
+    GLASS_DEV int s(int k, int e) const { return !FULL && k == NBLK - 1 ? 0 : (16 * k + e) * nr * 4; }
+};
+
 template <int NBLK, bool FULL>
 GLASS_DEV void rhs_load(f4_t (&Y)[NBLK], const float* Bg, int n, int nr, int cb, int q, int r) {
-    const int col = cb + r;
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(Bg, (uint32_t)(n * nr) * 4u);
+    const RhsOffsets<NBLK, FULL> o(nr, cb, q, r);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int R = 16 * k + 4 * q + e;
-            Y[k][e] = ((FULL || R < n) && col < nr) ? Bg[R * nr + col] : 0.f;
-        }
+        for (int e = 0; e < 4; ++e)
+            Y[k][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o.v(k, e), o.s(k, e), 0));
 }
 
 template <int NBLK, bool FULL>
 GLASS_DEV void rhs_store(const f4_t (&Y)[NBLK], float* Bg, int n, int nr, int cb, int q, int r) {
-    const int col = cb + r;
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(Bg, (uint32_t)(n * nr) * 4u);
+    const RhsOffsets<NBLK, FULL> o(nr, cb, q, r);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int R = 16 * k + 4 * q + e;
-            if ((FULL || R < n) && col < nr) Bg[R * nr + col] = Y[k][e];
-        }
+        for (int e = 0; e < 4; ++e)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(Y[k][e]), rs, o.v(k, e), o.s(k, e), 0);
 }
 
 template <int NBLK, int K>
@@ -446,22 +479,18 @@ GLASS_DEV float diag_cols(const f4_t& t, float (&col)[16], float* xs, int q, int
 // form (lane (q, r) holds element 16 k + r in every row q).
 template <int NBLK, bool FULL>
 GLASS_DEV void blk_x_load(float (&x)[NBLK], const float* bg, int n, int r) {
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(bg, (uint32_t)n * 4u);
 #pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        const int R = 16 * k + r;
-        x[k] = (FULL || R < n) ? bg[R] : 0.f;
-    }
+    for (int k = 0; k < NBLK; ++k)
+        x[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (16 * k + r) * 4, 0, 0));
 }
 
 template <int NBLK, bool FULL>
 GLASS_DEV void blk_x_store(const float (&x)[NBLK], float* bg, int n, int q, int r) {
-    if (q == 0) {
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(bg, (uint32_t)n * 4u);
 #pragma unroll
-        for (int k = 0; k < NBLK; ++k) {
-            const int R = 16 * k + r;
-            if (FULL || R < n) bg[R] = x[k];
-        }
-    }
+    for (int k = 0; k < NBLK; ++k)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[k]), rs, q == 0 ? (16 * k + r) * 4 : kOob, 0, 0);
 }
 
 // Forward step k: block k of y from its pending sum p[k], the diagonal
@@ -605,11 +634,10 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
 // out: two tiles per side, and the last block), for the solves from rows
 // read without it.  Ag is A (L for the
 // solves), Bg the problem's [n][nr] right-hand sides (nr = 1 for TRSV and op
-// 4); vec: Ag 16-byte aligned with n % 4 == 0.  xs: the wavefront's LDS,
-// kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).  Returns info (0 for the
+// 4).  xs: the wavefront's LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).  Returns info (0 for the
 // solves); a failed factorization leaves B untouched.
 template <int NBLK, int OP, bool FULL>
-GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, bool vec, float* xs, int lane) {
+GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, float* xs, int lane) {
     constexpr int NT = NBLK * (NBLK + 1) / 2;
     constexpr bool FACTOR = OP == 0 || OP == 1 || OP == 4;
     constexpr bool MFMA_SOLVE = OP >= 1 && OP <= 3;
@@ -644,7 +672,7 @@ GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, bool vec
 #pragma unroll
             for (int c = 0; c < 16; ++c) a[c] = c <= r ? a[c] : 0.f;
             if (inf == 0 && f != 0) inf = 16 * k + f;
-            if (early) store_block_row<NBLK, FULL>(T, k, a, Ag, n, xs, q, r, lane, vec);
+            if (early) store_block_row<NBLK, FULL>(T, k, a, Ag, n, xs, q, r, lane);
         } else {
             myinv = recip(d);
         }
@@ -677,7 +705,7 @@ GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, bool vec
         if (FACTOR) {
 #pragma unroll
             for (int i = k + 1; i < NBLK; ++i) T[BI(i, k)] = mma(linv[k], T[BI(i, k)], zero4());
-            if (!early) store_block_row<NBLK, FULL>(T, k, a, Ag, n, xs, q, r, lane, vec);
+            if (!early) store_block_row<NBLK, FULL>(T, k, a, Ag, n, xs, q, r, lane);
 #pragma unroll
             for (int j = k + 1; j < NBLK; ++j) {
                 const f4_t nq = neg4(T[BI(j, k)]);

@@ -346,10 +346,10 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
     float* Ag = A + uniform_i64(offA[e]);
     float* Bg = B + uniform_i64(offB[e]);
     float* buf = chunk[w];
-    if (big) {  // problem offsets are arbitrary: 4-byte stores
-        const int inf = k == 3   ? blk_one<2, 1, false>(Ag, Bg, n, r, 0, false, buf, lane)
-                        : k <= 5 ? blk_one<3, 1, false>(Ag, Bg, n, r, 0, false, buf, lane)
-                                 : blk_one<4, 1, false>(Ag, Bg, n, r, 0, false, buf, lane);
+    if (big) {
+        const int inf = k == 3   ? blk_one<2, 1, false>(Ag, Bg, n, r, 0, buf, lane)
+                        : k <= 5 ? blk_one<3, 1, false>(Ag, Bg, n, r, 0, buf, lane)
+                                 : blk_one<4, 1, false>(Ag, Bg, n, r, 0, buf, lane);
         if (lane == 0) info[e] = inf;
         return;
     }
