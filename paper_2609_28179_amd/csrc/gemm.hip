@@ -5,15 +5,16 @@
 //              through LDS into VGPRs, A is staged whole and each lane turns
 //              its A rows into C rows in place; the epilogue is fused into the
 //              coalesced store.
-//   wave / wg  max(m, n, k) >= 16: FP32 MFMA (v_mfma_f32_16x16x4_f32), the
-//              operand fragments loaded straight from global memory (no LDS):
-//              lane l = 16q + r holds A[row r][k0 + 4q .. k0 + 4q + 3] as one
-//              16-byte load and feeds component c to MFMA step c, so step c
-//              contracts k in {k0 + c, k0 + 4 + c, k0 + 8 + c, k0 + 12 + c};
-//              the matching B fragment is B[k0 + 4q + c][col r].  The wave
-//              scope runs one problem per wavefront; the workgroup scope
-//              splits the 16-wide column tiles of one problem over its waves.
-//   small n    max(m, n, k) < 16 at wave / wg scope: operands staged in LDS,
+//   wave / wg  FP32 MFMA (v_mfma_f32_16x16x4_f32), at workgroup scope from
+//              max(m, n, k) = 16 up, the operand fragments loaded straight from
+//              global memory (no LDS): lane l = 16q + r holds A[row r][k0 + 4q
+//              .. k0 + 4q + 3] as one 16-byte load and feeds component c to
+//              MFMA step c, so step c contracts k in {k0 + c, k0 + 4 + c,
+//              k0 + 8 + c, k0 + 12 + c}; the matching B fragment is
+//              B[k0 + 4q + c][col r].  The wave scope runs one problem per
+//              wavefront; the workgroup scope splits the 16-wide column tiles
+//              of one problem over its waves.
+//   small n    max(m, n, k) < 16 at workgroup scope: operands staged in LDS,
 //              lanes over output elements.
 #include "device_common.hpp"
 #include "glass_internal.hpp"
@@ -73,20 +74,20 @@ __global__ void __launch_bounds__(512) gemm_thread(int batch, float alpha, const
     stage_out_beta(C + p0 * SZ, lds, cnt * SZ, fd, S, beta, tid, nt);
 }
 
-// ------------------------------------------------- small n, wave / wg scope --
+// -------------------------------------------------------- small n, wg scope --
 // TA / TBT: op(A) = A^T (A stored k x m) / op(B) = B^T (B stored n x k).
 // Operands are staged as stored (rows padded to an odd stride).
 template <bool TA, bool TBT>
 GLASS_DEV void gemm_small_problem(int m, int n, int k, float alpha, const float* __restrict__ Ag,
                                   const float* __restrict__ Bg, float beta, float* __restrict__ Cg, float* As,
-                                  int tid, int nt, bool wave) {
+                                  int tid, int nt) {
     const int arows = TA ? k : m, acols = TA ? m : k;
     const int brows = TBT ? n : k, bcols = TBT ? k : n;
     const int sa = acols | 1, sb = bcols | 1;
     float* Bs = As + ((arows * sa + 3) & ~3);
     stage_in<2>(As, Ag, arows * acols, make_fastdiv(acols), sa, tid, nt);
     stage_in<2>(Bs, Bg, brows * bcols, make_fastdiv(bcols), sb, tid, nt);
-    if (wave) wave_sync(); else __syncthreads();
+    __syncthreads();
     const FastDiv fn = make_fastdiv(n);
     for (int e = tid; e < m * n; e += nt) {
         const int i = (int)fdiv((uint32_t)e, fn), j = e - i * n;
@@ -103,18 +104,6 @@ GLASS_DEV void gemm_small_problem(int m, int n, int k, float alpha, const float*
 }
 
 template <bool TA, bool TBT>
-__global__ void __launch_bounds__(512) gemm_small_wave(int m, int n, int k, int batch, float alpha,
-                                                       const float* __restrict__ A, const float* __restrict__ B,
-                                                       float beta, float* __restrict__ C, int region) {
-    extern __shared__ float lds[];
-    const int w = wave_index(), lane = threadIdx.x & 63;
-    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
-    if (p >= batch) return;
-    gemm_small_problem<TA, TBT>(m, n, k, alpha, A + p * m * k, B + p * k * n, beta, C + p * m * n, lds + (size_t)w * region,
-                       lane, 64, true);
-}
-
-template <bool TA, bool TBT>
 __global__ void __launch_bounds__(256) gemm_small_wg(int m, int n, int k, int batch, int pack, float alpha,
                                                      const float* __restrict__ A, const float* __restrict__ B,
                                                      float beta, float* __restrict__ C) {
@@ -123,53 +112,24 @@ __global__ void __launch_bounds__(256) gemm_small_wg(int m, int n, int k, int ba
         const long long p = (long long)blockIdx.x * pack + q;
         if (p >= batch) break;
         gemm_small_problem<TA, TBT>(m, n, k, alpha, A + p * m * k, B + p * k * n, beta, C + p * m * n, lds, threadIdx.x,
-                           blockDim.x, false);
+                           blockDim.x);
         __syncthreads();
     }
 }
 
-// ---------------------------------------------------------------- MFMA path --
+// ------------------------------------------------- MFMA path, workgroup scope --
 // One wave computes the 16x16 column tiles jt = jt0, jt0 + jstep, ... of one
-// problem.  TB = ceil(max(m, n, k) / 16) <= 4 bounds the fragment arrays.
-// Every A and B fragment the wave needs is loaded before the first MFMA, so
-// all of a problem's loads are in flight together.  JJ bounds the number of
-// column tiles one wave owns (TB at wave scope, 1 at workgroup scope where
-// the T(n)/64 waves split the ceil(n/16) <= T(n)/64 column tiles).
+// problem (JJ of them).  TB = ceil(max(m, n, k) / 16) <= 4 bounds the fragment
+// arrays.  Every A and B fragment the wave needs is loaded before the first
+// MFMA, so all of a problem's loads are in flight together; the T(n)/64 waves
+// of a workgroup split the ceil(n/16) <= T(n)/64 column tiles.
 // TA / TBT select transposed operands (A stored k x m, B stored n x k); the
 // transposed A fragment is read element-wise (consecutive lanes take
 // consecutive rows i, so the loads stay coalesced).
-// Wave scope with a staged output (STG: n % 4 == 0, C 16-byte aligned): all
-// column tiles of one 16-row block are accumulated, written to LDS in the
-// MFMA output layout and stored back as whole rows with 16-byte stores (the
-// output layout alone writes 64-byte half lines).
-template <int TB, bool TA, bool TBT>
-GLASS_DEV void mfma_store_block(int m, int n, float alpha, float beta, float* __restrict__ Cg, const float* stg,
-                                int it, int lane) {
-    const int n4 = n >> 2;
-    const int rows = min(16, m - it * 16);
-    for (int g = lane; g < 16 * n4; g += 64) {
-        const int rr = g / n4, c4 = g - rr * n4;
-        if (rr < rows) {
-            const f4_t v = *reinterpret_cast<const f4_t*>(stg + rr * kGemmStageStride + 4 * c4);
-            f4_t* dst = reinterpret_cast<f4_t*>(Cg + (size_t)(it * 16 + rr) * n) + c4;
-            f4_t out;
-            if (beta != 0.f) {
-                const f4_t c0 = *dst;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) out[e] = fmaf(beta, c0[e], alpha * v[e]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) out[e] = alpha * v[e];
-            }
-            *dst = out;
-        }
-    }
-}
-
-template <int TB, bool VEC, int JJ, bool TA = false, bool TBT = false, bool STG = false>
+template <int TB, bool VEC, int JJ, bool TA, bool TBT>
 GLASS_DEV void mfma_problem(int m, int n, int k, float alpha, const float* __restrict__ Ag,
                             const float* __restrict__ Bg, float beta, float* __restrict__ Cg, int lane, int jt0,
-                            int jstep, float* stg = nullptr) {
+                            int jstep) {
     const int q = lane >> 4, r = lane & 15;
     const int MT = (m + 15) >> 4, NT = (n + 15) >> 4, KT = (k + 15) >> 4;
     float af[TB][TB][4];
@@ -206,37 +166,6 @@ GLASS_DEV void mfma_problem(int m, int n, int k, float alpha, const float* __res
                 bf[jj][kb][c] = (kb < KT && kk < k && j < n) ? (TBT ? Bg[j * k + kk] : Bg[kk * n + j]) : 0.f;
             }
     }
-    if (STG) {
-#pragma unroll
-        for (int it = 0; it < TB; ++it) {
-            if (it < MT) {
-                floatx4 acc[JJ];
-#pragma unroll
-                for (int jj = 0; jj < JJ; ++jj) {
-                    acc[jj] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kb = 0; kb < TB; ++kb) {
-                        if (kb < KT) {
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                acc[jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[it][kb][c], bf[jj][kb][c], acc[jj],
-                                                                               0, 0, 0);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int jj = 0; jj < JJ; ++jj)
-                    if (jj < NT) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) stg[(4 * q + e) * kGemmStageStride + jj * 16 + r] = acc[jj][e];
-                    }
-                wave_sync();
-                mfma_store_block<TB, TA, TBT>(m, n, alpha, beta, Cg, stg, it, lane);
-                wave_sync();
-            }
-        }
-        return;
-    }
 #pragma unroll
     for (int jj = 0; jj < JJ; ++jj) {
         const int jt = jt0 + jj * jstep;
@@ -271,91 +200,189 @@ GLASS_DEV void mfma_problem(int m, int n, int k, float alpha, const float* __res
     }
 }
 
-// The A fragments of row block `it` (all TB k-blocks), zero outside m x k.
-template <int TB, bool VEC, bool TA>
-GLASS_DEV void mfma_a_rows(float (&af)[TB][4], int m, int k, const float* __restrict__ Ag, int it, int q, int r) {
-    const int MT = (m + 15) >> 4, KT = (k + 15) >> 4;
-    const int i = it * 16 + r;
+// ------------------------------------------------------ MFMA path, wave scope --
+// Any shape, transposes and alignment, one problem per wavefront.  The column
+// and inner extents are compile-time tile counts (NTB, KTB = ceil(n / 16),
+// ceil(k / 16)), so that only the last tile of each carries a bound; the B
+// fragments stay in VGPRs while A streams in by 16-row block, each block's
+// fragments loaded before the previous block's products.  Every load is a
+// buffer load that no branch guards: a lane outside the operand gets an offset
+// past the descriptor (kOobG), which returns 0.  Each 16-row block of C, contiguous in memory,
+// goes through LDS and leaves as 16-byte pieces at whatever alignment (buffer
+// accesses need 4 bytes), its last 1..3 floats one by one.
+// SYRK: A^T A with both operands the same array (C = J^T J): fragment (it, kb)
+// of A^T is fragment (jj = it, kb) of B, so A is not loaded.
+// Bound by the read of the operands where they are large.  Guarded scalar
+// loads and 4-byte stores in the MFMA output layout took, back to back, J^T J
+// of 64 x 30 at 16,384 problems 66.6 us against 41.3 now (its bytes take 32 at
+// 5.7 TB/s), J^T r 37.9 against 25.9, 33 x 20 x 50 90 against 48, 63 x 61 x 62
+// at 8192 151 against 86; below order 16 the LDS-staged form of the
+// workgroup scope (two LDS reads per FMA) took J^T J of 13 x 7 at 65,536 63.1
+// us against 18.7, 12^3 transposed 68.9 against 19.4.
+constexpr int kOobG = 0x40000000;
+
+GLASS_DEV f4_t gemm_load4(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+    return __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0));
+}
+GLASS_DEV float gemm_load1(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
+}
+
+// Row `row` of a rows x k row-major operand, all KTB pieces k0 = 16 kb + 4 q of the
+// lane, zero past k and past the rows.  The piece of the last row that would
+// run past the operand is loaded as its last 16 bytes and moved down; with
+// fewer than four columns the elements are loaded one by one.
+template <int KTB>
+GLASS_DEV void gemm_row_pieces(f4_t (&f)[KTB], __amdgpu_buffer_rsrc_t rs, int rows, int k, int row, int q) {
+    const int base = row < rows ? (row * k + 4 * q) * 4 : kOobG;
 #pragma unroll
-    for (int kb = 0; kb < TB; ++kb) {
-        const int k0 = kb * 16 + 4 * q;
-        const bool in = it < MT && kb < KT && i < m;
-        if (TA) {
+    for (int kb = 0; kb + 1 < KTB; ++kb) f[kb] = gemm_load4(rs, base, 64 * kb);
+    const int k0 = 16 * (KTB - 1) + 4 * q, left = k - k0;  // elements of the last piece
+    f4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (KTB == 1 && k < 4) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) af[kb][c] = (in && k0 + c < k) ? Ag[(k0 + c) * m + i] : 0.f;
-        } else if (VEC) {
-            floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (in && k0 < k) v = *reinterpret_cast<const floatx4*>(Ag + i * k + k0);
+        for (int c = 0; c < 3; ++c) v[c] = gemm_load1(rs, row < rows && c < left ? base + 4 * c : kOobG, 0);
+    } else {
+        const bool tail = row == rows - 1 && left < 4;
+        const int off = row >= rows || left <= 0 ? kOobG : tail ? (rows * k - 4) * 4 : (row * k + k0) * 4;
+        v = gemm_load4(rs, off, 0);
+        if ((k & 3) != 0) {  // wave-uniform
+            const int sh = tail ? 4 - left : 0;
+            const f4_t d = sh == 0   ? v
+                           : sh == 1 ? f4_t{v[1], v[2], v[3], 0.f}
+                           : sh == 2 ? f4_t{v[2], v[3], 0.f, 0.f}
+                                     : f4_t{v[3], 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) af[kb][c] = v[c];
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) af[kb][c] = (in && k0 + c < k) ? Ag[i * k + k0 + c] : 0.f;
+            for (int c = 0; c < 4; ++c) v[c] = c < left ? d[c] : 0.f;
         }
+    }
+    f[KTB - 1] = v;
+}
+
+// Column `col` of a k x cols row-major operand, elements kk = 16 kb + 4 q + c,
+// zero past k and past the columns.
+template <int KTB>
+GLASS_DEV void gemm_col_elems(f4_t (&f)[KTB], __amdgpu_buffer_rsrc_t rs, int cols, int k, int col, int q) {
+    const int base = col < cols ? (4 * q * cols + col) * 4 : kOobG;
+#pragma unroll
+    for (int kb = 0; kb + 1 < KTB; ++kb)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f[kb][c] = gemm_load1(rs, base, (16 * kb + c) * cols * 4);
+    constexpr int L = KTB - 1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        f[L][c] = gemm_load1(rs, 16 * L + 4 * q + c < k ? base : kOobG, (16 * L + c) * cols * 4);
+}
+
+// The 16-row block at rows 16 it of C from its staged form.
+template <int NTB>
+GLASS_DEV void gemm_store_block(float* __restrict__ Cg, const float* stg, int it, int m, int n, float alpha, float beta,
+                                int lane) {
+    const int len = min(16, m - 16 * it) * n;
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(Cg + (size_t)16 * it * n, (uint32_t)len * 4u);
+    asm volatile("" : "+v"(lane));  // piece addresses formed anew for each block, not held in registers between them
+    // row of element g: (g + 1/2) / n in FP32 is off by less than 7e-5 for
+    // g < 1024, and 1 / (2 n) >= 1/128 away from an integer
+    const float rn = recip((float)n);
+    const bool whole = (n & 3) == 0;
+#pragma unroll
+    for (int u = 0; u < NTB; ++u) {
+        const int g = 4 * (lane + 64 * u), at = min(g, 16 * n - 4 > 0 ? 16 * n - 4 : 0);
+        const int rr = (int)(((float)at + 0.5f) * rn), cc = at - rr * n;
+        f4_t v;
+        if (whole) {
+            v = *reinterpret_cast<const f4_t*>(stg + rr * kGemmStageStride + cc);
+        } else {
+            int row = rr, col = cc;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {  // a piece may span several rows of a narrow C
+                v[e] = stg[row * kGemmStageStride + col];
+                const bool wrap = ++col == n;
+                row += wrap ? 1 : 0;
+                col = wrap ? 0 : col;
+            }
+        }
+        const int off = g + 4 <= len ? g * 4 : kOobG;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] *= alpha;
+        if (beta != 0.f) {
+            const f4_t c0 = gemm_load4(rs, off, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(beta, c0[e], v[e]);
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, v), rs, off,
+                                               0, 0);
+    }
+    if (len & 3) {  // the last floats of an odd-sized block
+        const int g = (len & ~3) + lane;
+        const int at = min(g, len - 1);
+        const int rr = (int)(((float)at + 0.5f) * rn), cc = at - rr * n;
+        const int off = g < len ? g * 4 : kOobG;
+        float v = alpha * stg[rr * kGemmStageStride + cc];
+        if (beta != 0.f) v = fmaf(beta, gemm_load1(rs, off, 0), v);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, off, 0, 0);
     }
 }
 
-// Wave scope with a staged output at TB = 4 (orders 49..64): the B fragments
-// of every column tile stay in VGPRs while A streams in by 16-row block,
-// each block's fragments loaded before the previous block's products.  A
-// block's products then run while the next block's loads are in flight and
-// its stores overlap them; holding one A block at a time (two with the
-// prefetch) instead of all four keeps the wave within 128 VGPRs, i.e. four
-// waves per SIMD, so 4096 problems run in one round of waves.
-template <int TB, bool VEC, bool TA, bool TBT>
-GLASS_DEV void mfma_problem_rows(int m, int n, int k, float alpha, const float* __restrict__ Ag,
-                                 const float* __restrict__ Bg, float beta, float* __restrict__ Cg, int lane,
-                                 float* stg) {
-    const int q = lane >> 4, r = lane & 15;
-    const int MT = (m + 15) >> 4, NT = (n + 15) >> 4, KT = (k + 15) >> 4;
-    float af[2][TB][4];
-    mfma_a_rows<TB, VEC, TA>(af[0], m, k, Ag, 0, q, r);
-    float bf[TB][TB][4];
+template <int NTB, int KTB, bool TA, bool TBT, bool SYRK>
+__global__ void __launch_bounds__(512) gemm_mfma_wave(int m, int n, int k, int batch, float alpha,
+                                                      const float* __restrict__ A, const float* __restrict__ B,
+                                                      float beta, float* __restrict__ C) {
+    static_assert(!SYRK || (TA && !TBT), "A^T A");
+    extern __shared__ float lds[];
+    const int w = wave_index(), lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
+    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
+    if (p >= batch) return;
+    float* stg = lds + (size_t)w * 16 * kGemmStageStride;
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(A + p * m * k, (uint32_t)(m * k) * 4u);
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(B + p * k * n, (uint32_t)(k * n) * 4u);
+    float* Cg = C + p * m * n;
+    const int MT = SYRK ? NTB : (m + 15) >> 4;
+    f4_t af[2][KTB], bf[NTB][KTB];
+    auto a_block = [&](f4_t (&f)[KTB], int it) {
+        if (TA)
+            gemm_col_elems<KTB>(f, ra, m, k, 16 * it + r, q);
+        else
+            gemm_row_pieces<KTB>(f, ra, m, k, 16 * it + r, q);
+    };
+    if (!SYRK) a_block(af[0], 0);
 #pragma unroll
-    for (int jj = 0; jj < TB; ++jj) {
-        const int j = jj * 16 + r;
-#pragma unroll
-        for (int kb = 0; kb < TB; ++kb)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int kk = kb * 16 + 4 * q + c;
-                bf[jj][kb][c] = (kb < KT && kk < k && j < n) ? (TBT ? Bg[j * k + kk] : Bg[kk * n + j]) : 0.f;
-            }
+    for (int jj = 0; jj < NTB; ++jj) {
+        if (TBT)
+            gemm_row_pieces<KTB>(bf[jj], rb, n, k, 16 * jj + r, q);
+        else
+            gemm_col_elems<KTB>(bf[jj], rb, n, k, 16 * jj + r, q);
     }
 #pragma unroll
-    for (int it = 0; it < TB; ++it) {
-        if (it + 1 < TB) mfma_a_rows<TB, VEC, TA>(af[(it + 1) & 1], m, k, Ag, it + 1, q, r);
+    for (int it = 0; it < (SYRK ? NTB : 4); ++it) {
         if (it < MT) {
-            floatx4 acc[TB];
+            if (!SYRK && it + 1 < MT) a_block(af[(it + 1) & 1], it + 1);
+            f4_t acc[NTB];
 #pragma unroll
-            for (int jj = 0; jj < TB; ++jj) {
-                acc[jj] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int jj = 0; jj < NTB; ++jj) acc[jj] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kb = 0; kb < TB; ++kb) {
-                    if (kb < KT) {
+            for (int kb = 0; kb < KTB; ++kb)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            acc[jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[it & 1][kb][c], bf[jj][kb][c], acc[jj],
-                                                                           0, 0, 0);
-                    }
-                }
-            }
+                for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int jj = 0; jj < TB; ++jj)
-                if (jj < NT) {
+                    for (int jj = 0; jj < NTB; ++jj)
+                        acc[jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(SYRK ? bf[SYRK ? it : 0][kb][c] : af[it & 1][kb][c],
+                                                                       bf[jj][kb][c], acc[jj], 0, 0, 0);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) stg[(4 * q + e) * kGemmStageStride + jj * 16 + r] = acc[jj][e];
-                }
+            for (int jj = 0; jj < NTB; ++jj)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) stg[(4 * q + e) * kGemmStageStride + jj * 16 + r] = acc[jj][e];
             wave_sync();
-            mfma_store_block<TB, TA, TBT>(m, n, alpha, beta, Cg, stg, it, lane);
+            gemm_store_block<NTB>(Cg, stg, it, m, n, alpha, beta, lane);
             wave_sync();
         }
     }
 }
 
 // Whole tiles (m = n = k = N = 16 TB, TB = 1..4, no transposes, every operand
-// 16-byte aligned), the schedule of mfma_problem_rows with every bound known at
-// compile time: fragments come from buffer loads at a per-lane offset plus a
+// 16-byte aligned), the schedule of gemm_mfma_wave with every bound known at
+// compile time (at TB = 4 two A blocks and all of B hold the wave within 128
+// VGPRs, i.e. four waves per SIMD, so 4096 problems run in one round of waves): fragments come from buffer loads at a per-lane offset plus a
 // scalar block offset plus an immediate, with no guards and no 64-bit
 // address arithmetic, and the staged rows leave as 16-byte buffer stores.
 //   A block it, k-block kb: lane (q, r) reads row 16 it + r, columns
@@ -441,22 +468,6 @@ __global__ void __launch_bounds__(512) gemm_mfma_wave_full(int batch, float alph
     }
 }
 
-template <int TB, bool VEC, bool TA = false, bool TBT = false, bool STG = false>
-__global__ void __launch_bounds__(512) gemm_mfma_wave(int m, int n, int k, int batch, float alpha,
-                                                      const float* __restrict__ A, const float* __restrict__ B,
-                                                      float beta, float* __restrict__ C) {
-    extern __shared__ float lds[];
-    const int w = wave_index(), lane = threadIdx.x & 63;
-    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
-    if (p >= batch) return;
-    if constexpr (STG && TB == 4)
-        mfma_problem_rows<TB, VEC, TA, TBT>(m, n, k, alpha, A + p * m * k, B + p * k * n, beta, C + p * m * n, lane,
-                                            lds + (size_t)w * 16 * kGemmStageStride);
-    else
-        mfma_problem<TB, VEC, TB, TA, TBT, STG>(m, n, k, alpha, A + p * m * k, B + p * k * n, beta, C + p * m * n,
-                                                lane, 0, 1, lds + (size_t)w * 16 * kGemmStageStride);
-}
-
 template <int TB, bool VEC, bool TA = false, bool TBT = false>
 __global__ void __launch_bounds__(256) gemm_mfma_wg(int m, int n, int k, int batch, int pack, float alpha,
                                                     const float* __restrict__ A, const float* __restrict__ B,
@@ -478,13 +489,9 @@ int launch_gemm_t(const Shape& sh, const Geometry& g, int batch, float alpha, co
                   float beta, float* C, hipStream_t st) {
     const int m = sh.m, n = sh.n, k = sh.k;
     dim3 grid((unsigned)g.grid), block(g.threads);
-    if (!gemm_uses_mfma(sh)) {
-        if (g.scope == GLASS_SCOPE_WAVE)
-            hipLaunchKernelGGL((gemm_small_wave<TA, TBT>), grid, block, g.lds_bytes, st, m, n, k, batch, alpha, A, B,
-                               beta, C, (int)region_floats(sh));
-        else
-            hipLaunchKernelGGL((gemm_small_wg<TA, TBT>), grid, block, g.lds_bytes, st, m, n, k, batch, g.pack,
-                               alpha, A, B, beta, C);
+    if (g.scope == GLASS_SCOPE_WORKGROUP && !gemm_uses_mfma(sh)) {
+        hipLaunchKernelGGL((gemm_small_wg<TA, TBT>), grid, block, g.lds_bytes, st, m, n, k, batch, g.pack, alpha, A, B,
+                           beta, C);
         return (int)hipGetLastError();
     }
     int mx = m > n ? m : n;
@@ -510,28 +517,25 @@ int launch_gemm_t(const Shape& sh, const Geometry& g, int batch, float alpha, co
             }
             return (int)hipGetLastError();
         }
-        // staged full-row stores when C rows are whole 16-byte units
-        const bool stg = (n % 4 == 0) && ((uintptr_t)C % 16 == 0);
-#define X(TB)                                                                                                   \
-    case TB:                                                                                                    \
-        if (vec && stg)                                                                                         \
-            hipLaunchKernelGGL((gemm_mfma_wave<TB, true, TA, TBT, true>), grid, block, g.lds_bytes, st, m, n, k, \
-                               batch, alpha, A, B, beta, C);                                                    \
-        else if (stg)                                                                                           \
-            hipLaunchKernelGGL((gemm_mfma_wave<TB, false, TA, TBT, true>), grid, block, g.lds_bytes, st, m, n,  \
-                               k, batch, alpha, A, B, beta, C);                                                 \
-        else if (vec)                                                                                           \
-            hipLaunchKernelGGL((gemm_mfma_wave<TB, true, TA, TBT>), grid, block, g.lds_bytes, st, m, n, k,      \
-                               batch, alpha, A, B, beta, C);                                                    \
-        else                                                                                                    \
-            hipLaunchKernelGGL((gemm_mfma_wave<TB, false, TA, TBT>), grid, block, g.lds_bytes, st, m, n, k,     \
-                               batch, alpha, A, B, beta, C);                                                    \
-        break;
-        switch (tb) {
-            X(1) X(2) X(3) X(4)
-        default: return (int)hipErrorInvalidValue;
-        }
+        const size_t lds = sizeof(float) * 16 * kGemmStageStride * (size_t)g.pack;
+        // one array as both operands of A^T B with m = n: its fragments serve twice
+        const bool syrk = TA && !TBT && m == n && A == B;
+#define X(NTB, KTB)                                                                                                   \
+    if (nt == NTB && kt == KTB) {                                                                                     \
+        if (syrk)                                                                                                     \
+            hipLaunchKernelGGL((gemm_mfma_wave<NTB, KTB, TA, TBT, TA && !TBT>), grid, block, lds, st, m, n, k, batch, \
+                               alpha, A, B, beta, C);                                                                 \
+        else                                                                                                          \
+            hipLaunchKernelGGL((gemm_mfma_wave<NTB, KTB, TA, TBT, false>), grid, block, lds, st, m, n, k, batch,      \
+                               alpha, A, B, beta, C);                                                                 \
+        return (int)hipGetLastError();                                                                                \
+    }
+#define X_K(NTB) X(NTB, 1) X(NTB, 2) X(NTB, 3) X(NTB, 4)
+        const int nt = (n + 15) / 16, kt = (k + 15) / 16;
+        X_K(1) X_K(2) X_K(3) X_K(4)
+#undef X_K
 #undef X
+        return (int)hipErrorInvalidValue;
     } else {
 #define X(TB)                                                                                                  \
     case TB:                                                                                                   \
