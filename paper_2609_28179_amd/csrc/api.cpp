@@ -122,6 +122,7 @@ glass_status_t glass_gemv_batched(int m, int n, int batch, float alpha, const fl
     if (batch < 0) return GLASS_ERR_INVALID_VALUE;
     if (batch == 0) return GLASS_OK;
     if (!A || !x || !y) return GLASS_ERR_INVALID_VALUE;
+    if (!force && gemv_thin(m, n)) return launched(launch_gemv_thin(m, n, batch, alpha, A, x, beta, y, stream));
     Shape s{GLASS_OP_GEMV, m, n, n, 1, 0};
     Geometry g;
     glass_status_t st = resolve(s, batch, force, &g);

@@ -59,13 +59,6 @@ GLASS_DEV f4_t mma(const f4_t& m, const f4_t& x, f4_t c) {
     return c;
 }
 
-// A byte offset past the end of every descriptor of these routines: a buffer
-// load there returns 0 and a buffer store there is dropped, so a lane with
-// nothing to move needs no branch.  (Raw-buffer range checking looks at the
-// per-lane offset only, not at the scalar one; multi-dword accesses need
-// 4-byte alignment.)
-constexpr int kOob = 0x40000000;
-
 // The lower blocks of the problem at Ag in T layout.  FULL: n == 16 NBLK;
 // otherwise 16 (NBLK - 1) < n < 16 NBLK, so that only the last block row and
 // column are cut: the blocks above it load at compile-time positions, rows

@@ -101,6 +101,68 @@ GLASS_DEV __amdgpu_buffer_rsrc_t buffer_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
 
+// A byte offset past the end of every descriptor: a buffer load there returns
+// 0 and a buffer store there is dropped, so a lane with nothing to move needs
+// no branch.  (Raw-buffer range checking is relied on for the per-lane offset
+// only, not for the scalar one; multi-dword accesses need 4-byte alignment.)
+constexpr int kOob = 0x40000000;
+
+GLASS_DEV f4_t buf_load4(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+    return __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0));
+}
+GLASS_DEV float buf_load1(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
+}
+
+// Operand fragments of the 16 x 16 x 4 matrix instruction, lane (q, r) =
+// (lane / 16, lane % 16), with no branch around any load.
+//
+// Row `row` of a rows x k row-major operand, all KTB pieces k0 = 16 kb + 4 q of the
+// lane, zero past k and past the rows.  The piece of the last row that would
+// run past the operand is loaded as its last 16 bytes and moved down; with
+// fewer than four columns the elements are loaded one by one.
+template <int KTB>
+GLASS_DEV void tile_row_pieces(f4_t (&f)[KTB], __amdgpu_buffer_rsrc_t rs, int rows, int k, int row, int q) {
+    const int base = row < rows ? (row * k + 4 * q) * 4 : kOob;
+#pragma unroll
+    for (int kb = 0; kb + 1 < KTB; ++kb) f[kb] = buf_load4(rs, base, 64 * kb);
+    const int k0 = 16 * (KTB - 1) + 4 * q, left = k - k0;  // elements of the last piece
+    f4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (KTB == 1 && k < 4) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] = buf_load1(rs, row < rows && c < left ? base + 4 * c : kOob, 0);
+    } else {
+        const bool tail = row == rows - 1 && left < 4;
+        const int off = row >= rows || left <= 0 ? kOob : tail ? (rows * k - 4) * 4 : (row * k + k0) * 4;
+        v = buf_load4(rs, off, 0);
+        if ((k & 3) != 0) {  // wave-uniform
+            const int sh = tail ? 4 - left : 0;
+            const f4_t d = sh == 0   ? v
+                           : sh == 1 ? f4_t{v[1], v[2], v[3], 0.f}
+                           : sh == 2 ? f4_t{v[2], v[3], 0.f, 0.f}
+                                     : f4_t{v[3], 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = c < left ? d[c] : 0.f;
+        }
+    }
+    f[KTB - 1] = v;
+}
+
+// Column `col` of a k x cols row-major operand, elements kk = 16 kb + 4 q + c,
+// zero past k and past the columns.
+template <int KTB>
+GLASS_DEV void tile_col_elems(f4_t (&f)[KTB], __amdgpu_buffer_rsrc_t rs, int cols, int k, int col, int q) {
+    const int base = col < cols ? (4 * q * cols + col) * 4 : kOob;
+#pragma unroll
+    for (int kb = 0; kb + 1 < KTB; ++kb)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f[kb][c] = buf_load1(rs, base, (16 * kb + c) * cols * 4);
+    constexpr int L = KTB - 1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        f[L][c] = buf_load1(rs, 16 * L + 4 * q + c < k ? base : kOob, (16 * L + c) * cols * 4);
+}
+
 // Copy src[0 .. len) (contiguous, global) into LDS re-laid as rows of
 // `cols.d` floats at row stride `ldst`: element g lands at
 // dst[(g / cols) * ldst + g % cols].  `nt` cooperating lanes, this one is

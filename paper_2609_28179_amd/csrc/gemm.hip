@@ -207,7 +207,7 @@ GLASS_DEV void mfma_problem(int m, int n, int k, float alpha, const float* __res
 // fragments stay in VGPRs while A streams in by 16-row block, each block's
 // fragments loaded before the previous block's products.  Every load is a
 // buffer load that no branch guards: a lane outside the operand gets an offset
-// past the descriptor (kOobG), which returns 0.  Each 16-row block of C, contiguous in memory,
+// past the descriptor (kOob), which returns 0.  Each 16-row block of C, contiguous in memory,
 // goes through LDS and leaves as 16-byte pieces at whatever alignment (buffer
 // accesses need 4 bytes), its last 1..3 floats one by one.
 // SYRK: A^T A with both operands the same array (C = J^T J): fragment (it, kb)
@@ -219,61 +219,6 @@ GLASS_DEV void mfma_problem(int m, int n, int k, float alpha, const float* __res
 // at 8192 151 against 86; below order 16 the LDS-staged form of the
 // workgroup scope (two LDS reads per FMA) took J^T J of 13 x 7 at 65,536 63.1
 // us against 18.7, 12^3 transposed 68.9 against 19.4.
-constexpr int kOobG = 0x40000000;
-
-GLASS_DEV f4_t gemm_load4(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
-    return __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0));
-}
-GLASS_DEV float gemm_load1(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
-}
-
-// Row `row` of a rows x k row-major operand, all KTB pieces k0 = 16 kb + 4 q of the
-// lane, zero past k and past the rows.  The piece of the last row that would
-// run past the operand is loaded as its last 16 bytes and moved down; with
-// fewer than four columns the elements are loaded one by one.
-template <int KTB>
-GLASS_DEV void gemm_row_pieces(f4_t (&f)[KTB], __amdgpu_buffer_rsrc_t rs, int rows, int k, int row, int q) {
-    const int base = row < rows ? (row * k + 4 * q) * 4 : kOobG;
-#pragma unroll
-    for (int kb = 0; kb + 1 < KTB; ++kb) f[kb] = gemm_load4(rs, base, 64 * kb);
-    const int k0 = 16 * (KTB - 1) + 4 * q, left = k - k0;  // elements of the last piece
-    f4_t v = {0.f, 0.f, 0.f, 0.f};
-    if (KTB == 1 && k < 4) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = gemm_load1(rs, row < rows && c < left ? base + 4 * c : kOobG, 0);
-    } else {
-        const bool tail = row == rows - 1 && left < 4;
-        const int off = row >= rows || left <= 0 ? kOobG : tail ? (rows * k - 4) * 4 : (row * k + k0) * 4;
-        v = gemm_load4(rs, off, 0);
-        if ((k & 3) != 0) {  // wave-uniform
-            const int sh = tail ? 4 - left : 0;
-            const f4_t d = sh == 0   ? v
-                           : sh == 1 ? f4_t{v[1], v[2], v[3], 0.f}
-                           : sh == 2 ? f4_t{v[2], v[3], 0.f, 0.f}
-                                     : f4_t{v[3], 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = c < left ? d[c] : 0.f;
-        }
-    }
-    f[KTB - 1] = v;
-}
-
-// Column `col` of a k x cols row-major operand, elements kk = 16 kb + 4 q + c,
-// zero past k and past the columns.
-template <int KTB>
-GLASS_DEV void gemm_col_elems(f4_t (&f)[KTB], __amdgpu_buffer_rsrc_t rs, int cols, int k, int col, int q) {
-    const int base = col < cols ? (4 * q * cols + col) * 4 : kOobG;
-#pragma unroll
-    for (int kb = 0; kb + 1 < KTB; ++kb)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) f[kb][c] = gemm_load1(rs, base, (16 * kb + c) * cols * 4);
-    constexpr int L = KTB - 1;
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-        f[L][c] = gemm_load1(rs, 16 * L + 4 * q + c < k ? base : kOobG, (16 * L + c) * cols * 4);
-}
-
 // The 16-row block at rows 16 it of C from its staged form.
 template <int NTB>
 GLASS_DEV void gemm_store_block(float* __restrict__ Cg, const float* stg, int it, int m, int n, float alpha, float beta,
@@ -302,11 +247,11 @@ GLASS_DEV void gemm_store_block(float* __restrict__ Cg, const float* stg, int it
                 col = wrap ? 0 : col;
             }
         }
-        const int off = g + 4 <= len ? g * 4 : kOobG;
+        const int off = g + 4 <= len ? g * 4 : kOob;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] *= alpha;
         if (beta != 0.f) {
-            const f4_t c0 = gemm_load4(rs, off, 0);
+            const f4_t c0 = buf_load4(rs, off, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = fmaf(beta, c0[e], v[e]);
         }
@@ -317,9 +262,9 @@ GLASS_DEV void gemm_store_block(float* __restrict__ Cg, const float* stg, int it
         const int g = (len & ~3) + lane;
         const int at = min(g, len - 1);
         const int rr = (int)(((float)at + 0.5f) * rn), cc = at - rr * n;
-        const int off = g < len ? g * 4 : kOobG;
+        const int off = g < len ? g * 4 : kOob;
         float v = alpha * stg[rr * kGemmStageStride + cc];
-        if (beta != 0.f) v = fmaf(beta, gemm_load1(rs, off, 0), v);
+        if (beta != 0.f) v = fmaf(beta, buf_load1(rs, off, 0), v);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, off, 0, 0);
     }
 }
@@ -341,17 +286,17 @@ __global__ void __launch_bounds__(512) gemm_mfma_wave(int m, int n, int k, int b
     f4_t af[2][KTB], bf[NTB][KTB];
     auto a_block = [&](f4_t (&f)[KTB], int it) {
         if (TA)
-            gemm_col_elems<KTB>(f, ra, m, k, 16 * it + r, q);
+            tile_col_elems<KTB>(f, ra, m, k, 16 * it + r, q);
         else
-            gemm_row_pieces<KTB>(f, ra, m, k, 16 * it + r, q);
+            tile_row_pieces<KTB>(f, ra, m, k, 16 * it + r, q);
     };
     if (!SYRK) a_block(af[0], 0);
 #pragma unroll
     for (int jj = 0; jj < NTB; ++jj) {
         if (TBT)
-            gemm_row_pieces<KTB>(bf[jj], rb, n, k, 16 * jj + r, q);
+            tile_row_pieces<KTB>(bf[jj], rb, n, k, 16 * jj + r, q);
         else
-            gemm_col_elems<KTB>(bf[jj], rb, n, k, 16 * jj + r, q);
+            tile_col_elems<KTB>(bf[jj], rb, n, k, 16 * jj + r, q);
     }
 #pragma unroll
     for (int it = 0; it < (SYRK ? NTB : 4); ++it) {

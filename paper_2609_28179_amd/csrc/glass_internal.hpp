@@ -271,6 +271,12 @@ int launch_gemm(const Shape& s, const Geometry& g, int batch, float alpha, const
                 const float* B, float beta, float* C, void* stream);
 int launch_gemv(const Shape& s, const Geometry& g, int batch, float alpha, const float* A,
                 const float* x, float beta, float* y, void* stream);
+// Rectangular GEMV with few wide rows, without a forced placement: four
+// problems per wavefront (the sub-wave scope stops at 16 columns, and one
+// problem per wavefront leaves most of it idle).
+inline bool gemv_thin(int m, int n) { return m <= 16 && n > 16; }
+int launch_gemv_thin(int m, int n, int batch, float alpha, const float* A, const float* x, float beta, float* y,
+                     void* stream);
 int launch_potrf(const Shape& s, const Geometry& g, int batch, float* A, int32_t* info, void* stream);
 int launch_potrs(const Shape& s, const Geometry& g, int batch, const float* L, float* B, void* stream);
 int launch_posv(const Shape& s, const Geometry& g, int batch, float* A, float* B, int32_t* info,

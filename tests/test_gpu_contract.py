@@ -251,3 +251,30 @@ def test_adjoint_in_place(env, scope, n, r, batch):
     assert normwise(Gd.cpu().numpy(), dB_ref).max() <= TOL
     assert normwise(dAd.cpu().numpy(), dA_ref).max() <= TOL
     assert all(guards_intact(b) for b in (Lf, Xf, Gf, dAf))
+
+
+@pytest.mark.parametrize("shift", [0, 1, 2])
+@pytest.mark.parametrize("m,n", [(1, 17), (2, 64), (4, 20), (5, 33), (8, 18), (9, 63), (15, 31), (16, 64)])
+def test_gemv_few_wide_rows(env, m, n, shift):
+    """Rectangular GEMV with m <= 16 < n and no forced placement (four problems
+    per wavefront): batches that leave its last wavefront partly filled, on and
+    off 16-byte alignment, y read and not read, a NaN row staying its own.
+    Every element within the rounding bound of an FP32 dot product in any
+    order, (n + 4) u (|alpha| sum |a_j x_j| + |beta y|): with one row a problem's
+    largest output can itself cancel, so a share of it is no bound."""
+    glass, torch = env
+    pad = 64 + shift
+    for batch in (1, 3, 4, 6, 4099):
+        _say(f"gemv few wide rows m={m} n={n} batch={batch} shift={shift}")
+        rng = _rng(9, m, n, batch)
+        A, x, y0 = (inputs.uniform(rng, s) for s in ((batch, m, n), (batch, n), (batch, m)))
+        A[batch // 2, m // 2, n - 1] = np.nan
+        for beta in (0.0, 0.5):
+            bufs = [guarded(torch, a, "cuda:0", pad) for a in (A, x, y0)]
+            assert glass.glass_gemv_batched(m, n, batch, 1.5, bufs[0][1], bufs[1][1], beta, bufs[2][1]) == 0
+            torch.cuda.synchronize()
+            got, ref = bufs[2][1].cpu().numpy(), oracle.gemv(A, x, y0, alpha=1.5, beta=beta)
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(got).sum() == 1
+            mag = 1.5 * np.einsum("bij,bj->bi", np.abs(A.astype(np.float64)), np.abs(x)) + beta * np.abs(y0)
+            assert (np.nan_to_num(np.abs(got - ref)) <= (n + 4) * 2.0 ** -24 * np.nan_to_num(mag, nan=np.inf)).all()
+            assert all(guards_intact(b[0], pad) for b in bufs)
