@@ -275,7 +275,8 @@ size_t glass_posv_ragged_perm_offset(int count);
  * for nx <= 8 and nu <= 4, thread (one problem per lane, every operand and
  * intermediate in VGPRs; force->pack sets 64 * pack lanes per workgroup).
  * With force NULL: thread scope with one wavefront per workgroup where it
- * runs, else wavefront scope.  The workgroup scope, or a scope outside its
+ * runs, else sub-wave scope from the batch where it is measured faster, else
+ * wavefront scope.  The workgroup scope, or a scope outside its
  * sizes, is GLASS_ERR_INFEASIBLE_PLACEMENT. */
 glass_status_t glass_riccati_gain_batched(int nx, int nu, int batch, const float* A,
                                           const float* B, const float* P, const float* R,

@@ -79,8 +79,6 @@ glass_status_t resolve(const Shape& s, long long batch, const glass_placement_t*
 
 thread_local int t_last_launch_error = 0;
 
-constexpr int kRiccatiDefaultPack = 1;  // problems (wavefronts) per workgroup of the fused LQR gain
-
 inline glass_status_t launched(int err) {
     if (err == 0) return GLASS_OK;
     t_last_launch_error = err;
@@ -288,35 +286,30 @@ glass_status_t glass_riccati_gain_batched(int nx, int nu, int batch, const float
     if (batch < 0) return GLASS_ERR_INVALID_VALUE;
     if (batch == 0) return GLASS_OK;
     if (!A || !B || !P || !R || !K) return GLASS_ERR_INVALID_VALUE;
-    // without a forced placement, thread scope wherever it runs (measured
-    // faster at every batch from 16 to 65,536 at nx, nu = (1, 1), (4, 2),
-    // (6, 3), (8, 1) and (8, 4)), one wavefront per workgroup
-    if (!force && riccati_thread_ok(nx, nu))
-        return launched(launch_riccati_thread(nx, nu, batch, 1, A, B, P, R, K, info, stream));
-    int pack = kRiccatiDefaultPack;
+    int scope, pack;
     if (force) {
-        if (force->scope == GLASS_SCOPE_THREAD) {
-            if (!riccati_thread_ok(nx, nu)) return GLASS_ERR_INFEASIBLE_PLACEMENT;
-            return launched(launch_riccati_thread(nx, nu, batch, force->pack, A, B, P, R, K, info, stream));
-        }
-        if (force->scope == GLASS_SCOPE_SUBWAVE) {
-            if (!riccati_seg_ok(nx, nu)) return GLASS_ERR_INFEASIBLE_PLACEMENT;
-            return launched(launch_riccati_seg(nx, nu, batch, force->pack, A, B, P, R, K, info, stream));
-        }
-        if (force->scope != GLASS_SCOPE_WAVE) return GLASS_ERR_INFEASIBLE_PLACEMENT;
+        scope = force->scope;
         pack = force->pack;
+    } else {
+        riccati_default(nx, nu, batch, &scope, &pack);
     }
-    if (riccati_region_floats(nx, nu) * sizeof(float) * pack > kLdsBudgetBytes) {
-        if (force) return GLASS_ERR_INFEASIBLE_PLACEMENT;
-        pack = 1;
+    if (scope == GLASS_SCOPE_THREAD) {
+        if (!riccati_thread_ok(nx, nu)) return GLASS_ERR_INFEASIBLE_PLACEMENT;
+        return launched(launch_riccati_thread(nx, nu, batch, pack, A, B, P, R, K, info, stream));
     }
+    if (scope == GLASS_SCOPE_SUBWAVE) {
+        if (!riccati_seg_ok(nx, nu)) return GLASS_ERR_INFEASIBLE_PLACEMENT;
+        return launched(launch_riccati_seg(nx, nu, batch, pack, A, B, P, R, K, info, stream));
+    }
+    if (scope != GLASS_SCOPE_WAVE) return GLASS_ERR_INFEASIBLE_PLACEMENT;
     return launched(launch_riccati(nx, nu, batch, pack, A, B, P, R, K, info, stream));
 }
 
 int glass_riccati_feasible(int nx, int nu, int pack) {
     if (!riccati_size_ok(nx, nu)) return GLASS_ERR_UNSUPPORTED;
     if (pack != 1 && pack != 2 && pack != 4 && pack != 8) return GLASS_ERR_INVALID_VALUE;
-    return riccati_region_floats(nx, nu) * sizeof(float) * pack <= kLdsBudgetBytes ? 1 : 0;
+    static_assert(kRiccatiRegionFloats * sizeof(float) * 8 <= kLdsBudgetBytes, "every pack fits the LDS budget");
+    return 1;
 }
 
 int glass_riccati_placement_feasible(int nx, int nu, int scope, int pack) {

@@ -3,23 +3,8 @@
 // Sec. IV-E measures fused against a chain of separate launches).
 //
 // Every intermediate stays on chip.  At wave scope (one wavefront per
-// problem, P problems per workgroup) in one of two forms, riccati_wave and
-// riccati_mfma; at sub-wave scope riccati_seg; at thread scope riccati_thread.
-//
-// riccati_wave (LDS-staged, nx < kRiccatiMfmaMinNx):
-//   1. P (nx x nx) and B (nx x nu) are staged into LDS with coalesced loads,
-//      rows padded with zeros to the 8-wide buckets NX8 / NU8;
-//   2. lane c (c < nu + nx) loads column c of X = [B | A] into VGPRs and
-//      accumulates z = B^T (P x): for each row i of P, y_i = P[i,:] x (P row
-//      read as LDS broadcasts), then z_j += B[i][j] y_i.  Lane c < nu ends
-//      with column c of B^T P B, lane nu + c with column c of T = B^T P A;
-//   3. lanes c < nu add R[:, c] and hold S = R + B^T P B by columns (S is
-//      symmetric, so a column serves as the row the wave Cholesky expects);
-//      the existing DPP wave factorization gives L and 1/L_ii;
-//   4. L goes to LDS; lane nu + c solves L L^T k = t for its own column t of
-//      T (forward and backward substitution with L read as broadcasts) and
-//      stores column c of K (K row-major nu x nx, so a row's stores are
-//      consecutive lanes).
+// problem, P problems per workgroup) riccati_mfma; at sub-wave scope
+// riccati_seg; at thread scope riccati_thread.
 //
 // riccati_thread (thread scope, nx <= 8, nu <= 4): one problem per lane.  A
 // lane loads its own P, B, R and A (every load issued before any is used),
@@ -36,8 +21,8 @@
 // lane i solves L L^T k = t for its own column of K with L's entries as
 // broadcasts.  Every cross-lane move stays inside a 16-lane row.
 //
-// riccati_mfma (nx >= kRiccatiMfmaMinNx): every product on the matrix cores,
-// in the blocked layouts of chol_blk.hpp (nx padded to 16-row blocks; nu <= 16
+// riccati_mfma (every size): every product on the matrix cores, operands read
+// once by branch-free buffer loads (device_common.hpp), in the blocked layouts of chol_blk.hpp (nx padded to 16-row blocks; nu <= 16
 // is one block).  With B_k in accumulator layout (lane (q, r) holds B[16k+4q+c][r])
 // the products chain without data movement:
 //   PB_i = sum_k P_ik B_k                 P_ik loaded row-wise (T layout)
@@ -59,37 +44,6 @@
 
 namespace glass {
 namespace {
-
-// One 16 x 16 block of a row-major [rows][ld] matrix in T layout (lane
-// (q, r): row r0 + r, columns c0 + 4q .. c0 + 4q + 3; zero outside rows x cols).
-GLASS_DEV f4_t load_t_block(__amdgpu_buffer_rsrc_t rs, int ld, int rows, int cols, int r0, int c0, bool vec, int q,
-                            int r) {
-    f4_t v = {0.f, 0.f, 0.f, 0.f};
-    const int R = r0 + r, C = c0 + 4 * q;
-    if (R < rows) {
-        if (vec && C + 4 <= cols) {
-            v = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (R * ld + C) * 4, 0, 0));
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (C + e < cols)
-                    v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (R * ld + C + e) * 4, 0, 0));
-        }
-    }
-    return v;
-}
-
-// The same block in accumulator layout (lane (q, r): rows r0 + 4q .. r0 + 4q + 3,
-// column c0 + r).
-GLASS_DEV f4_t load_acc_block(const float* M, int ld, int rows, int cols, int r0, int c0, int q, int r) {
-    f4_t v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int R = r0 + 4 * q + e, C = c0 + r;
-        v[e] = (R < rows && C < cols) ? M[R * ld + C] : 0.f;
-    }
-    return v;
-}
 
 // L^{-1} of a 16 x 16 lower diagonal block whose rows and columns from NK on
 // are the identity, in T layout: the substitution steps K >= NK add nothing
@@ -118,7 +72,13 @@ GLASS_DEV f4_t tri_inverse_l_first(const float (&m)[16], float myinv, int q, int
 }
 
 // NUB: nu rounded up to 4, 8 or 16.  S is the identity past nu, so its
-// factorization and inverse run NUB pivot steps instead of 16.
+// factorization and inverse run NUB pivot steps instead of 16.  All of P and
+// the first block column of A are in flight before the chain that factors
+// S.  With guarded element-wise loads at the point of use, 16,384 problems took
+// (20, 3) 28.4 us against 22.3 now, (27, 6) 35.6 against 27.6, (41, 9) 104
+// against 62.5, (48, 16) 97.6 against 84.7, and (32, 8) at 65,536 144.5 against
+// 131.9.  What is left is matrix and vector issue: 20 + 8 ceil(nx / 16) products
+// of 16 x 16 x 16 blocks at two tiles of states, a third of them padding.
 template <int NXB, int NUB>
 __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, const float* __restrict__ A,
                                                     const float* __restrict__ B, const float* __restrict__ P,
@@ -128,26 +88,33 @@ __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, c
     const int w = wave_index(), lane = threadIdx.x & 63, q = lane >> 4, r = lane & 15;
     const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
     if (p >= batch) return;
-    float* xs = lds + (size_t)w * kRiccatiMfmaRegionFloats;
+    float* xs = lds + (size_t)w * kRiccatiRegionFloats;
     const float* Ap = A + p * nx * nx;
     const float* Bp = B + p * nx * nu;
     const float* Pp = P + p * nx * nx;
     const float* Rp = R + p * nu * nu;
-    f4_t Bb[NXB];
-#pragma unroll
-    for (int k = 0; k < NXB; ++k) Bb[k] = load_acc_block(Bp, nu, nx, nu, 16 * k, 0, q, r);
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(Ap, (uint32_t)(nx * nx) * 4u);
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(Bp, (uint32_t)(nx * nu) * 4u);
     const __amdgpu_buffer_rsrc_t rp = buffer_rsrc(Pp, (uint32_t)(nx * nx) * 4u);
-    const bool vec = (nx & 3) == 0;
+    const __amdgpu_buffer_rsrc_t rr = buffer_rsrc(Rp, (uint32_t)(nu * nu) * 4u);
+    f4_t Bb[NXB], Pf[NXB][NXB], Rf[1];
+    tile_col_elems<NXB>(Bb, rb, nu, nx, r, q);
+#pragma unroll
+    for (int i = 0; i < NXB; ++i) tile_row_pieces<NXB>(Pf[i], rp, nx, nx, 16 * i + r, q);
+    tile_col_elems<1>(Rf, rr, nu, nu, r, q);
     f4_t PB[NXB];
 #pragma unroll
     for (int i = 0; i < NXB; ++i) {
         f4_t acc = zero4();
 #pragma unroll
-        for (int k = 0; k < NXB; ++k) acc = mma(load_t_block(rp, nx, nx, nx, 16 * i, 16 * k, vec, q, r), Bb[k], acc);
+        for (int k = 0; k < NXB; ++k) acc = mma(Pf[i][k], Bb[k], acc);
         PB[i] = acc;
     }
+    // the first block column of A, in flight behind the factorization of S
+    f4_t Af[2][NXB];
+    tile_col_elems<NXB>(Af[0], ra, nx, nx, r, q);
     // S = R + B^T P B in accumulator layout, identity on the padded diagonal
-    f4_t S = load_acc_block(Rp, nu, nu, nu, 0, 0, q, r);
+    f4_t S = Rf[0];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (4 * q + e == r && r >= nu) S[e] = 1.f;
@@ -185,18 +152,19 @@ __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, c
     f4_t lt[4];
     lt[0] = linv;
     transpose_blocks<1>(lt, xs, q, r);  // lt[0]: L^{-T} in T layout
-    float* Kp = K + p * nu * nx;
+    const __amdgpu_buffer_rsrc_t rk = buffer_rsrc(K + p * nu * nx, (uint32_t)(nu * nx) * 4u);
 #pragma unroll
     for (int j = 0; j < NXB; ++j) {
+        if (j + 1 < NXB) tile_col_elems<NXB>(Af[(j + 1) & 1], ra, nx, nx, 16 * (j + 1) + r, q);
         f4_t t = zero4();
 #pragma unroll
-        for (int i = 0; i < NXB; ++i) t = mma(PB[i], load_acc_block(Ap, nx, nx, nx, 16 * i, 16 * j, q, r), t);
+        for (int i = 0; i < NXB; ++i) t = mma(PB[i], Af[j & 1][i], t);
         const f4_t kj = mma(lt[0], mma(linv, t, zero4()), zero4());  // L^{-T} (L^{-1} T_j)
+        const int col = 16 * j + r;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int row = 4 * q + e, col = 16 * j + r;
-            if (row < nu && col < nx) Kp[row * nx + col] = kj[e];
-        }
+        for (int e = 0; e < 4; ++e)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(kj[e]), rk,
+                                                  4 * q + e < nu && col < nx ? ((4 * q + e) * nx + col) * 4 : kOob, 0, 0);
     }
 }
 
@@ -324,7 +292,7 @@ GLASS_DEV void static_for(F&& f) {
     }
 }
 
-template <int NUB>
+template <int NXB, int NUB>
 __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, const float* __restrict__ A,
                                                    const float* __restrict__ B, const float* __restrict__ P,
                                                    const float* __restrict__ R, float* __restrict__ K,
@@ -340,9 +308,9 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
     const float* Bp = B + pp * nx * nu;
     const float* Rp = R + pp * nu * nu;
     const bool row = i < nx;
-    float prow[16], acol[16], brow[NUB], rrow[NUB];
+    float prow[NXB], acol[NXB], brow[NUB], rrow[NUB];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {  // unconditional loads (entry 0 for the rest), so that all issue at once
+    for (int k = 0; k < NXB; ++k) {  // unconditional loads (entry 0 for the rest), so that all issue at once
         const bool ok = act && row && k < nx;
         const float pv = Pp[ok ? k * nx + i : 0];  // P symmetric: row i read as column i (coalesced)
         const float av = Ap[ok ? k * nx + i : 0];
@@ -365,7 +333,7 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
         pb[j] = 0.f;
         asm volatile("s_nop 1" : "+v"(brow[j]));
     }
-    static_for<0, 16>([&](auto kc) {
+    static_for<0, NXB>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
 #pragma unroll
         for (int j = 0; j < NUB; ++j) fmac_bcast<k>(pb[j], brow[j], prow[k]);
@@ -395,7 +363,7 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
         t[a] = 0.f;
         asm volatile("s_nop 1" : "+v"(pb[a]));
     }
-    static_for<0, 16>([&](auto kc) {
+    static_for<0, NXB>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
 #pragma unroll
         for (int a = 0; a < NUB; ++a) fmac_bcast<k>(t[a], pb[a], acol[k]);
@@ -430,154 +398,29 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
     }
 }
 
-template <int NX8, int NU8>
-__global__ void __launch_bounds__(512) riccati_wave(int nx, int nu, int batch, const float* __restrict__ A,
-                                                    const float* __restrict__ B, const float* __restrict__ P,
-                                                    const float* __restrict__ R, float* __restrict__ K,
-                                                    int32_t* __restrict__ info, int region) {
-    extern __shared__ float lds[];
-    const int w = wave_index(), lane = threadIdx.x & 63;
-    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
-    if (p >= batch) return;
-    float* Ps = lds + (size_t)w * region;  // [NX8][NX8]
-    float* Bs = Ps + NX8 * NX8;            // [NX8][NU8]
-    float* Ls = Bs + NX8 * NU8;            // [NU8][NU8] rows of L, then [NU8] of 1 / L_ii
-    // (every offset is a multiple of 8 floats, so the f4_t accesses are aligned)
-    const float* Pg = P + p * nx * nx;
-    const float* Bg = B + p * nx * nu;
-    const float* Ag = A + p * nx * nx;
-    const float* Rg = R + p * nu * nu;
-
-    for (int e = lane; e < NX8 * NX8; e += 64) {
-        const int i = e / NX8, k = e - i * NX8;
-        Ps[e] = (i < nx && k < nx) ? Pg[i * nx + k] : 0.f;
-    }
-    for (int e = lane; e < NX8 * NU8; e += 64) {
-        const int i = e / NU8, j = e - i * NU8;
-        Bs[e] = (i < nx && j < nu) ? Bg[i * nu + j] : 0.f;
-    }
-    const int c = lane;
-    const bool colB = c < nu, colA = c >= nu && c < nu + nx;
-    float x[NX8];
-#pragma unroll
-    for (int k = 0; k < NX8; ++k)
-        x[k] = k < nx ? (colB ? Bg[k * nu + c] : (colA ? Ag[k * nx + (c - nu)] : 0.f)) : 0.f;
-    wave_sync();
-
-    float z[NU8];
-#pragma unroll
-    for (int j = 0; j < NU8; ++j) z[j] = 0.f;
-    for (int i = 0; i < nx; ++i) {
-        const float* pr = Ps + i * NX8;
-        float y = 0.f;
-#pragma unroll
-        for (int k4 = 0; k4 < NX8 / 4; ++k4) {
-            const f4_t pv = *reinterpret_cast<const f4_t*>(pr + 4 * k4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y = fmaf(pv[e], x[4 * k4 + e], y);
-        }
-        const float* br = Bs + i * NU8;
-#pragma unroll
-        for (int j4 = 0; j4 < NU8 / 4; ++j4) {
-            const f4_t bv = *reinterpret_cast<const f4_t*>(br + 4 * j4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) z[4 * j4 + e] = fmaf(bv[e], y, z[4 * j4 + e]);
-        }
-    }
-
-    // S by columns in lanes < nu, identity rows up to the bucket, zero beyond
-    float a[NU8];
-#pragma unroll
-    for (int j = 0; j < NU8; ++j) {
-        if (colB)
-            a[j] = j < nu ? z[j] + Rg[j * nu + c] : 0.f;
-        else
-            a[j] = (j == c) ? 1.f : 0.f;
-    }
-    float myinv;
-    const int inf = wave_potrf<NU8>(a, lane, myinv);
-    if (inf != 0) {
-        if (info && lane == 0) info[p] = inf;
-        return;
-    }
-    if (lane < NU8) {
-#pragma unroll
-        for (int j4 = 0; j4 < NU8 / 4; ++j4) {
-            f4_t v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = a[4 * j4 + e];
-            *reinterpret_cast<f4_t*>(Ls + lane * NU8 + 4 * j4) = v;
-        }
-        Ls[NU8 * NU8 + lane] = myinv;
-    }
-    wave_sync();
-    if (colA) {
-        float t[NU8];
-#pragma unroll
-        for (int i = 0; i < NU8; ++i) {  // L y = t (padded rows are identity, padded t is 0)
-            float s = z[i];
-#pragma unroll
-            for (int j = 0; j < i; ++j) s = fmaf(-Ls[i * NU8 + j], t[j], s);
-            t[i] = s * Ls[NU8 * NU8 + i];
-        }
-#pragma unroll
-        for (int i = NU8 - 1; i >= 0; --i) {  // L^T k = y
-            float s = t[i];
-#pragma unroll
-            for (int j = i + 1; j < NU8; ++j) s = fmaf(-Ls[j * NU8 + i], t[j], s);
-            t[i] = s * Ls[NU8 * NU8 + i];
-        }
-        float* Kg = K + p * nu * nx + (c - nu);
-#pragma unroll
-        for (int i = 0; i < NU8; ++i)
-            if (i < nu) Kg[i * nx] = t[i];
-    }
-    if (info && lane == 0) info[p] = 0;
-}
-
 }  // namespace
 
-static_assert(kRiccatiMfmaRegionFloats == 16 * kXS, "one exchange block");
-
-size_t riccati_region_floats(int nx, int nu) {
-    if (riccati_uses_mfma(nx)) return kRiccatiMfmaRegionFloats;
-    const int x8 = bucket8_host(nx), u8 = bucket8_host(nu);
-    return (size_t)x8 * x8 + (size_t)x8 * u8 + (size_t)u8 * u8 + u8;
-}
+static_assert(kRiccatiRegionFloats == 16 * kXS, "one exchange block");
 
 int launch_riccati(int nx, int nu, int batch, int pack, const float* A, const float* B, const float* P,
                    const float* R, float* K, int32_t* info, void* stream) {
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
-    const int region = (int)riccati_region_floats(nx, nu);
     dim3 grid((unsigned)((batch + pack - 1) / pack)), block(64 * pack);
-    const size_t lds = sizeof(float) * (size_t)region * pack;
-    if (riccati_uses_mfma(nx)) {
-        const int nub = nu <= 4 ? 4 : nu <= 8 ? 8 : 16;
-        switch ((nx + 15) / 16 * 100 + nub) {
+    const size_t lds = sizeof(float) * (size_t)kRiccatiRegionFloats * pack;
+    const int nub = nu <= 4 ? 4 : nu <= 8 ? 8 : 16;
+    switch ((nx + 15) / 16 * 100 + nub) {
 #define RM(NXB, NUB)                                                                                            \
     case NXB * 100 + NUB:                                                                                       \
         hipLaunchKernelGGL((riccati_mfma<NXB, NUB>), grid, block, lds, st, nx, nu, batch, A, B, P, R, K, info); \
         break;
 #define RM_NX(NXB) RM(NXB, 4) RM(NXB, 8) RM(NXB, 16)
-            RM_NX(1) RM_NX(2) RM_NX(3) RM_NX(4)
+        RM_NX(1) RM_NX(2) RM_NX(3) RM_NX(4)
 #undef RM_NX
 #undef RM
-        default: return (int)hipErrorInvalidValue;
-        }
-        return (int)hipGetLastError();
+    default: return (int)hipErrorInvalidValue;
     }
-    const int x8 = bucket8_host(nx), u8 = bucket8_host(nu);
-#define RK(X8, U8)                                                                                          \
-    if (x8 == X8 && u8 == U8) {                                                                             \
-        hipLaunchKernelGGL((riccati_wave<X8, U8>), grid, block, lds, st, nx, nu, batch, A, B, P, R, K, info, \
-                           region);                                                                         \
-        return (int)hipGetLastError();                                                                      \
-    }
-    RK(8, 8) RK(16, 8) RK(24, 8) RK(32, 8) RK(40, 8) RK(48, 8) RK(56, 8)
-    RK(8, 16) RK(16, 16) RK(24, 16) RK(32, 16) RK(40, 16) RK(48, 16)
-#undef RK
-    return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
 }
 
 int launch_riccati_seg(int nx, int nu, int batch, int pack, const float* A, const float* B, const float* P,
@@ -586,11 +429,16 @@ int launch_riccati_seg(int nx, int nu, int batch, int pack, const float* A, cons
     hipStream_t st = (hipStream_t)stream;
     const int per_wg = 4 * pack;
     dim3 grid((unsigned)((batch + per_wg - 1) / per_wg)), block(64 * pack);
-    if (nu <= 4)
-        hipLaunchKernelGGL((riccati_seg<4>), grid, block, 0, st, nx, nu, batch, A, B, P, R, K, info);
-    else
-        hipLaunchKernelGGL((riccati_seg<8>), grid, block, 0, st, nx, nu, batch, A, B, P, R, K, info);
-    return (int)hipGetLastError();
+    // states rounded up to 8, 12 or 16 (rows of P, B and A loaded and multiplied), inputs to 4 or 8
+    const int nxb = nx <= 8 ? 8 : nx <= 12 ? 12 : 16, nub = nu <= 4 ? 4 : 8;
+#define RS(NXB, NUB)                                                                                       \
+    if (nxb == NXB && nub == NUB) {                                                                        \
+        hipLaunchKernelGGL((riccati_seg<NXB, NUB>), grid, block, 0, st, nx, nu, batch, A, B, P, R, K, info); \
+        return (int)hipGetLastError();                                                                     \
+    }
+    RS(8, 4) RS(8, 8) RS(12, 4) RS(12, 8) RS(16, 4) RS(16, 8)
+#undef RS
+    return (int)hipErrorInvalidValue;
 }
 
 int launch_riccati_thread(int nx, int nu, int batch, int pack, const float* A, const float* B, const float* P,

@@ -286,3 +286,24 @@ def test_graph_replays_of_thread_and_subwave_forms(env, scope, nx, nu):
         assert torch.equal(K, eK) and torch.equal(info, ei), rep
     K_ref, _ = oracle.riccati_gain(*(c[k].cpu().numpy() for k in ("A", "B", "P", "R")))
     assert normwise(eK.cpu().numpy(), K_ref).max() <= TOL
+
+
+@pytest.mark.parametrize("nx,nu,batch", [(9, 4, 4095), (9, 4, 4096), (16, 1, 4099), (5, 5, 8191), (8, 8, 8192),
+                                         (12, 5, 16384), (14, 8, 32768), (16, 8, 2049), (3, 16, 100), (8, 16, 2048),
+                                         (17, 16, 33), (33, 3, 100), (48, 16, 70), (56, 8, 67)])
+def test_fused_default_placement_routes(env, nx, nu, batch):
+    """force = NULL on either side of the batches where the default changes
+    scope or pack, and at the edges of the tiles: the oracle's tolerance on
+    every K of a sample spread over the batch, info 0 throughout."""
+    glass, torch = env
+    print(f"riccati default route nx={nx} nu={nu} batch={batch}", flush=True)
+    c = inputs.make_riccati(batch, nx, nu, seed=9)
+    d = {k: dev(torch, v) for k, v in c.items()}
+    K = torch.full((batch, nu, nx), float("nan"), device="cuda:0")
+    info = torch.full((batch,), -7, dtype=torch.int32, device="cuda:0")
+    assert glass.glass_riccati_gain_batched(nx, nu, batch, d["A"], d["B"], d["P"], d["R"], K, info) == 0
+    torch.cuda.synchronize()
+    pick = np.unique(np.r_[0:8, batch // 2:batch // 2 + 8, batch - 8:batch])
+    ref, _ = oracle.riccati_gain(c["A"][pick], c["B"][pick], c["P"][pick], c["R"][pick])
+    assert normwise(K.cpu().numpy()[pick], ref).max() <= TOL
+    assert not np.isnan(K.cpu().numpy()).any() and (info.cpu().numpy() == 0).all()
