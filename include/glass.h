@@ -157,6 +157,15 @@ glass_status_t glass_posv_batched(int n, int nrhs, int batch, float* A,
                                   float* B, int32_t* info,
                                   const glass_placement_t* force, void* stream);
 
+/* glass_posv_batched out of place: reads A and B, writes L (strict upper +0)
+ * and X, the bits of the in-place call; where info[b] != 0, X[b] = B[b].  L may
+ * be A itself and X may be B itself; otherwise the outputs overlap no
+ * input.  (A differentiable solve keeps its inputs: this saves it their
+ * copies.) */
+glass_status_t glass_posv_to_batched(int n, int nrhs, int batch, const float* A, const float* B,
+                                     float* L, float* X, int32_t* info,
+                                     const glass_placement_t* force, void* stream);
+
 /* Triangular solve, in place  (Sec. III-B).
  * L [batch][n][n] lower triangle read, non-unit diagonal; x [batch][n] holds
  * b on entry and the solution on exit.  trans = 0: L x = b; trans = 1:

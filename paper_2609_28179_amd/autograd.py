@@ -1,7 +1,7 @@
 """torch.autograd.Function for the batched Cholesky solve X = A^{-1} B.
 
-Forward: one fused factor-and-solve launch (glass_posv_batched) on copies of
-A and B; the factor L and the solution X are saved.  Backward: one launch of
+Forward: one fused factor-and-solve launch (glass_posv_to_batched), which
+leaves A and B as they are; the factor L and the solution X are saved.  Backward: one launch of
 the hand-written adjoint kernel (glass_posv_adjoint_batched), which returns
 dB = A^{-1} G and the symmetric dA = -(dB X^T + X dB^T) / 2.
 """
@@ -15,9 +15,7 @@ from . import glass
 class CholeskySolve(torch.autograd.Function):
     @staticmethod
     def forward(ctx, A, B, force=None):
-        L = A.detach().contiguous().clone()
-        X = B.detach().contiguous().clone()
-        _, X, info = glass.posv_(L, X, force=force)
+        L, X, info = glass.posv_to(A.detach().contiguous(), B.detach().contiguous(), force)
         ctx.save_for_backward(L, X)
         ctx.force = force
         ctx.info = info

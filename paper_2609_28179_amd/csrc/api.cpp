@@ -167,7 +167,21 @@ glass_status_t glass_posv_batched(int n, int nrhs, int batch, float* A, float* B
     Geometry g;
     glass_status_t st = resolve(s, batch, force, &g);
     if (st != GLASS_OK) return st;
-    return launched(launch_posv(s, g, batch, A, B, info, stream));
+    return launched(launch_posv(s, g, batch, A, B, A, B, info, stream));
+}
+
+glass_status_t glass_posv_to_batched(int n, int nrhs, int batch, const float* A, const float* B, float* L, float* X,
+                                     int32_t* info, const glass_placement_t* force, void* stream) {
+    if (!valid_force(force)) return GLASS_ERR_INVALID_VALUE;
+    if (!size_ok(n) || !size_ok(nrhs)) return GLASS_ERR_UNSUPPORTED;
+    if (batch < 0) return GLASS_ERR_INVALID_VALUE;
+    if (batch == 0) return GLASS_OK;
+    if (!A || !B || !L || !X) return GLASS_ERR_INVALID_VALUE;
+    Shape s{GLASS_OP_POSV, n, n, n, nrhs, 0};
+    Geometry g;
+    glass_status_t st = resolve(s, batch, force, &g);
+    if (st != GLASS_OK) return st;
+    return launched(launch_posv(s, g, batch, A, B, L, X, info, stream));
 }
 
 glass_status_t glass_trsv_batched(int n, int batch, int trans, const float* L, float* x,

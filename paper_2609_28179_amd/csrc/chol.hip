@@ -49,8 +49,8 @@ __global__ void __launch_bounds__(512) potrf_thread(int batch, float* __restrict
 }
 
 template <int N>
-__global__ void __launch_bounds__(512) posv_thread(int nrhs, int batch, float* __restrict__ A, float* __restrict__ B,
-                                                   int* __restrict__ info) {
+__global__ void __launch_bounds__(512) posv_thread(int nrhs, int batch, const float* Ai, float* A, const float* Bi,
+                                                   float* B, int* __restrict__ info) {
     extern __shared__ float lds[];
     const int nt = blockDim.x, tid = threadIdx.x;
     const long long p0 = (long long)blockIdx.x * nt;
@@ -58,13 +58,13 @@ __global__ void __launch_bounds__(512) posv_thread(int nrhs, int batch, float* _
     float* base = A + p0 * (N * N);
     float a[N * (N + 1) / 2];
     float dinv[N];
-    thread_load_tri<N>(a, base, lds, cnt, tid, nt);
+    thread_load_tri<N>(a, Ai + p0 * (N * N), lds, cnt, tid, nt);
     const bool active = tid < cnt;
     int inf = 0;
     if (active) inf = tri_potrf<N>(a, dinv);
     if (info && active) info[p0 + tid] = inf;
     thread_store_tri<N>(a, base, lds, cnt, tid, nt);
-    thread_solve_rhs<N>(a, dinv, B + p0 * N * nrhs, lds, nrhs, cnt, tid, nt, true, true, active && inf == 0);
+    thread_solve_rhs<N>(a, dinv, Bi + p0 * N * nrhs, B + p0 * N * nrhs, lds, nrhs, cnt, tid, nt, true, true, active && inf == 0);
 }
 
 template <int N>
@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(512) potrs_thread(int nrhs, int batch, const f
     thread_load_tri<N>(a, L + p0 * (N * N), lds, cnt, tid, nt);
 #pragma unroll
     for (int i = 0; i < N; ++i) dinv[i] = recip(a[TI(i, i)]);
-    thread_solve_rhs<N>(a, dinv, B + p0 * N * nrhs, lds, nrhs, cnt, tid, nt, true, true, tid < cnt);
+    thread_solve_rhs<N>(a, dinv, B + p0 * N * nrhs, B + p0 * N * nrhs, lds, nrhs, cnt, tid, nt, true, true, tid < cnt);
 }
 
 template <int N>
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(512) trsv_thread(int trans, int batch, const f
     thread_load_tri<N>(a, L + p0 * (N * N), lds, cnt, tid, nt);
 #pragma unroll
     for (int i = 0; i < N; ++i) dinv[i] = recip(a[TI(i, i)]);
-    thread_solve_rhs<N>(a, dinv, x + p0 * N, lds, 1, cnt, tid, nt, trans == 0, trans != 0, tid < cnt);
+    thread_solve_rhs<N>(a, dinv, x + p0 * N, x + p0 * N, lds, 1, cnt, tid, nt, trans == 0, trans != 0, tid < cnt);
 }
 
 // -------------------------------------------------------------- wave scope --
@@ -119,25 +119,28 @@ __global__ void __launch_bounds__(512) potrf_wave(int n, int batch, float* __res
 // MULTI: several right-hand sides are solved in column groups; the nrhs = 1
 // instance keeps only the single-column path and its register budget.
 template <int NB, bool MULTI>
-__global__ void __launch_bounds__(512) posv_wave(int n, int nrhs, int batch, float* __restrict__ A,
-                                                 float* __restrict__ B, int* __restrict__ info, int region) {
+__global__ void __launch_bounds__(512) posv_wave(int n, int nrhs, int batch, const float* Ai, float* A, const float* Bi,
+                                                 float* B, int* __restrict__ info, int region) {
     extern __shared__ float lds[];
     const int w = wave_index(), lane = threadIdx.x & 63;
     const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
     if (p >= batch) return;
     float* buf = lds + (size_t)w * region;
     float* Ag = A + p * n * n;
+    const float* Bgi = Bi + p * n * nrhs;
     float* Bg = B + p * n * nrhs;
-    const float b0 = MULTI ? 0.f : lane_elem(Bg, n, lane);  // issued with the rows
+    const float b0 = MULTI ? 0.f : lane_elem(Bgi, n, lane);  // issued with the rows
     float a[NB];
-    rows_load_lower<NB, false>(a, Ag, n, lane);
+    rows_load_lower<NB, false>(a, Ai + p * n * n, n, lane);
     float myinv;
     const int inf = wave_potrf<NB>(a, lane, myinv);
     const bool vec = (n & 3) == 0 && aligned16(A);
     if (inf != 0) {
         wave_chunks_desc<NB>(a, buf, Ag, vec, n, lane, false, 0.f, myinv);
+        if (Bi != B)  // out of place: a failed factorization passes B through
+            for (int g = lane; g < n * nrhs; g += 64) Bg[g] = Bgi[g];
     } else if (MULTI) {
-        wave_solve_all<NB>(a, buf, Ag, vec, Bg, n, nrhs, myinv, lane);
+        wave_solve_all<NB>(a, buf, Ag, vec, Bgi, Bg, n, nrhs, myinv, lane);
     } else {
         float acc = b0;
         acc = wave_fwd<NB>(a, acc, myinv, lane);
@@ -162,7 +165,7 @@ __global__ void __launch_bounds__(512) potrs_wave(int n, int nrhs, int batch, co
     rows_load_lower<NB, true>(a, Lg, n, lane);
     const float myinv = diag_inv(dg, n, lane);
     if (MULTI) {
-        wave_solve_all<NB>(a, buf, nullptr, false, Bg, n, nrhs, myinv, lane);
+        wave_solve_all<NB>(a, buf, nullptr, false, Bg, Bg, n, nrhs, myinv, lane);
     } else {
         float acc = b0;
         acc = wave_fwd<NB>(a, acc, myinv, lane);
@@ -279,8 +282,8 @@ __global__ void __launch_bounds__(256) potrf_wg(int n, int batch, int pack, floa
     }
 }
 
-__global__ void __launch_bounds__(256) posv_wg(int n, int nrhs, int batch, int pack, float* __restrict__ A,
-                                               float* __restrict__ B, int* __restrict__ info) {
+__global__ void __launch_bounds__(256) posv_wg(int n, int nrhs, int batch, int pack, const float* Ai, float* A,
+                                               const float* Bi, float* B, int* __restrict__ info) {
     extern __shared__ float lds[];
     const int nt = blockDim.x, tid = threadIdx.x;
     const int s = n | 1, sb = nrhs | 1;
@@ -291,18 +294,16 @@ __global__ void __launch_bounds__(256) posv_wg(int n, int nrhs, int batch, int p
         if (p >= batch) break;
         float* Ag = A + p * n * n;
         float* Bg = B + p * n * nrhs;
-        stage_in<4>(lds, Ag, n * n, fd, s, tid, nt);
-        stage_in<2>(Bm, Bg, n * nrhs, fdb, sb, tid, nt);
+        stage_in<4>(lds, Ai + p * n * n, n * n, fd, s, tid, nt);
+        stage_in<2>(Bm, Bi + p * n * nrhs, n * nrhs, fdb, sb, tid, nt);
         __syncthreads();
         const int inf = wg_potrf(lds, n, s, tid, nt);
         wg_zero_upper(lds, n, s, tid, nt);
         __syncthreads();
         stage_out(Ag, lds, n * n, fd, s, tid, nt);
         if (info && tid == 0) info[p] = inf;
-        if (inf == 0) {
-            wg_solve(lds, s, Bm, sb, n, nrhs, tid, nt, true, true);
-            stage_out(Bg, Bm, n * nrhs, fdb, sb, tid, nt);
-        }
+        if (inf == 0) wg_solve(lds, s, Bm, sb, n, nrhs, tid, nt, true, true);
+        if (inf == 0 || Bi != B) stage_out(Bg, Bm, n * nrhs, fdb, sb, tid, nt);
         __syncthreads();
     }
 }
@@ -349,7 +350,7 @@ __global__ void __launch_bounds__(256) trsv_wg(int n, int trans, int batch, int 
 // ----------------------------------------------------------------- launch --
 #define GLASS_CASES_1_16(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
-#define GLASS_BUCKETS(X) X(8) X(16) X(24) X(32) X(40) X(48) X(56) X(64)
+#define GLASS_BUCKETS(X) X(8) X(16) X(24)  // orders below kBlkMinN; from there on the blocked kernels run
 
 inline int bucket8(int n) { return ((n + 7) / 8) * 8; }
 
@@ -359,8 +360,8 @@ inline int finish() { return (int)hipGetLastError(); }
 }  // namespace
 
 int launch_potrf(const Shape& sh, const Geometry& g, int batch, float* A, int32_t* info, void* stream) {
-    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, A, nullptr, info, stream);
-    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, A, nullptr, info, stream);
+    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, A, A, nullptr, nullptr, info, stream);
+    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, A, A, nullptr, nullptr, info, stream);
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n;
@@ -388,9 +389,10 @@ int launch_potrf(const Shape& sh, const Geometry& g, int batch, float* A, int32_
     return finish();
 }
 
-int launch_posv(const Shape& sh, const Geometry& g, int batch, float* A, float* B, int32_t* info, void* stream) {
-    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, A, B, info, stream);
-    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, A, B, info, stream);
+int launch_posv(const Shape& sh, const Geometry& g, int batch, const float* Ai, const float* Bi, float* A, float* B,
+                int32_t* info, void* stream) {
+    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, Ai, A, Bi, B, info, stream);
+    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, Ai, A, Bi, B, info, stream);
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n, r = sh.nrhs;
@@ -398,7 +400,7 @@ int launch_posv(const Shape& sh, const Geometry& g, int batch, float* A, float* 
     if (g.scope == GLASS_SCOPE_THREAD) {
         switch (n) {
 #define X(N) \
-    case N: hipLaunchKernelGGL(posv_thread<N>, grid, block, g.lds_bytes, st, r, batch, A, B, info); break;
+    case N: hipLaunchKernelGGL(posv_thread<N>, grid, block, g.lds_bytes, st, r, batch, Ai, A, Bi, B, info); break;
             GLASS_CASES_1_16(X)
 #undef X
         default: return (int)hipErrorInvalidValue;
@@ -409,23 +411,23 @@ int launch_posv(const Shape& sh, const Geometry& g, int batch, float* A, float* 
 #define X(NB) \
     case NB:                                                                                                  \
         if (r == 1)                                                                                           \
-            hipLaunchKernelGGL((posv_wave<NB, false>), grid, block, g.lds_bytes, st, n, r, batch, A, B, info, region); \
+            hipLaunchKernelGGL((posv_wave<NB, false>), grid, block, g.lds_bytes, st, n, r, batch, Ai, A, Bi, B, info, region); \
         else                                                                                                  \
-            hipLaunchKernelGGL((posv_wave<NB, true>), grid, block, g.lds_bytes, st, n, r, batch, A, B, info, region);  \
+            hipLaunchKernelGGL((posv_wave<NB, true>), grid, block, g.lds_bytes, st, n, r, batch, Ai, A, Bi, B, info, region);  \
         break;
             GLASS_BUCKETS(X)
 #undef X
         default: return (int)hipErrorInvalidValue;
         }
     } else {
-        hipLaunchKernelGGL(posv_wg, grid, block, g.lds_bytes, st, n, r, batch, g.pack, A, B, info);
+        hipLaunchKernelGGL(posv_wg, grid, block, g.lds_bytes, st, n, r, batch, g.pack, Ai, A, Bi, B, info);
     }
     return finish();
 }
 
 int launch_potrs(const Shape& sh, const Geometry& g, int batch, const float* L, float* B, void* stream) {
-    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, const_cast<float*>(L), B, nullptr, stream);
-    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, const_cast<float*>(L), B, nullptr, stream);
+    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, L, const_cast<float*>(L), B, B, nullptr, stream);
+    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, L, const_cast<float*>(L), B, B, nullptr, stream);
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n, r = sh.nrhs;
@@ -459,8 +461,8 @@ int launch_potrs(const Shape& sh, const Geometry& g, int batch, const float* L, 
 }
 
 int launch_trsv(const Shape& sh, const Geometry& g, int batch, const float* L, float* x, void* stream) {
-    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, const_cast<float*>(L), x, nullptr, stream);
-    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, const_cast<float*>(L), x, nullptr, stream);
+    if (g.scope == GLASS_SCOPE_SUBWAVE) return launch_chol_subwave(sh, g, batch, L, const_cast<float*>(L), x, x, nullptr, stream);
+    if (g.scope == GLASS_SCOPE_WAVE && sh.n >= kBlkMinN) return launch_chol_blk(sh, g, batch, L, const_cast<float*>(L), x, x, nullptr, stream);
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n, tr = sh.trans;

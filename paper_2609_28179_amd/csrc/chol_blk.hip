@@ -11,8 +11,8 @@ namespace {
 // op: 0 POTRF, 1 POSV, 2 POTRS, 3 TRSV (trans: 0 forward, 1 backward), 4 POSV
 // with one right-hand side.
 template <int NBLK, int OP, bool FULL>
-__global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int trans, int batch, float* __restrict__ A,
-                                                float* __restrict__ B, int32_t* __restrict__ info) {
+__global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int trans, int batch, const float* Ai, float* A,
+                                                const float* Bi, float* B, int32_t* __restrict__ info) {
     extern __shared__ float lds[];
     // POTRF on whole 16 x 16 tiles above order 32 (n = 48, 64) is write-bound
     // and runs 1.5-3 % faster at 4 waves per SIMD than at the 5-7 its
@@ -24,7 +24,8 @@ __global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int trans, int 
     if (p >= batch) return;
     const int nr = OP >= 3 ? 1 : nrhs;
     constexpr int region = OP == 4 ? blk_posv1_floats(NBLK) : kBlkRegionFloats;
-    const int inf = blk_one<NBLK, OP, FULL>(A + p * n * n, OP == 0 ? nullptr : B + p * n * nr, n, nrhs, trans,
+    const int inf = blk_one<NBLK, OP, FULL>(Ai + p * n * n, A + p * n * n, OP == 0 ? nullptr : Bi + p * n * nr,
+                                            OP == 0 ? nullptr : B + p * n * nr, n, nrhs, trans,
                                             lds + (size_t)w * region, lane);
     if ((OP <= 1 || OP == 4) && info && lane == 0) info[p] = inf;
 }
@@ -46,14 +47,15 @@ __global__ void __launch_bounds__(512) chol_blk_solve1(int n, int batch, const f
 
 }  // namespace
 
-int launch_chol_blk(const Shape& sh, const Geometry& g, int batch, float* A, float* B, int32_t* info,
-                    void* stream) {
+int launch_chol_blk(const Shape& sh, const Geometry& g, int batch, const float* Ai, float* A, const float* Bi, float* B,
+                    int32_t* info, void* stream) {
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n;
     if (n < kBlkMinN || n > kMaxN) return (int)hipErrorInvalidValue;
     const int nblk = n <= 32 ? 2 : n <= 48 ? 3 : 4;
-    const bool full = n == 16 * nblk && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
+    const bool full =
+        n == 16 * nblk && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Ai)) & 15) == 0;
     const int op = sh.op == GLASS_OP_POTRF ? 0
                    : sh.op == GLASS_OP_POSV ? (sh.nrhs == 1 ? 4 : 1)
                    : sh.op == GLASS_OP_POTRS ? 2
@@ -77,7 +79,7 @@ int launch_chol_blk(const Shape& sh, const Geometry& g, int batch, float* A, flo
 #define BLK(NBLK, OP, FULL)                                                                                    \
     if (nblk == NBLK && op == OP && full == FULL) {                                                            \
         hipLaunchKernelGGL((chol_blk<NBLK, OP, FULL>), grid, block, g.lds_bytes, st, n, sh.nrhs, sh.trans, batch, \
-                           A, B, info);                                                                        \
+                           Ai, A, Bi, B, info);                                                                        \
         return (int)hipGetLastError();                                                                         \
     }
 #define BLK_OPS(NBLK, FULL) \

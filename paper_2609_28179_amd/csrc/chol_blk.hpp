@@ -625,24 +625,26 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
 // after a factorization from the factored rows read back through LDS with
 // their diagonal cleared (the staged block row itself when it is already
 // out: two tiles per side, and the last block), for the solves from rows
-// read without it.  Ag is A (L for the
-// solves), Bg the problem's [n][nr] right-hand sides (nr = 1 for TRSV and op
-// 4).  xs: the wavefront's LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).  Returns info (0 for the
-// solves); a failed factorization leaves B untouched.
+// read without it.  Ai is A (L for the solves), Bi the problem's [n][nr]
+// right-hand sides (nr = 1 for TRSV and op 4); L goes to Ag and the solution to
+// Bg, which are Ai and Bi themselves for a call in place.  xs: the wavefront's
+// LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).  Returns info (0 for
+// the solves); a failed factorization leaves B untouched (out of place: copies it).
 template <int NBLK, int OP, bool FULL>
-GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, float* xs, int lane) {
+GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, int n, int nrhs, int trans, float* xs,
+                      int lane) {
     constexpr int NT = NBLK * (NBLK + 1) / 2;
     constexpr bool FACTOR = OP == 0 || OP == 1 || OP == 4;
     constexpr bool MFMA_SOLVE = OP >= 1 && OP <= 3;
     const int q = lane >> 4, r = lane & 15;
     f4_t T[NT];
-    blk_load<NBLK, FULL>(T, Ag, n, q, r);
+    blk_load<NBLK, FULL>(T, Ai, n, q, r);
     // op 4: the right-hand side, loaded with A, and the forward substitution's
     // pending sums; step k of the substitution runs inside factorization step k
     float x1[NBLK], p1[NBLK], myinv_last = 1.f;
     float* lt = xs + 16 * blk_row_stride(NBLK);  // op 4: L_kk^{-1} of the blocks k < NBLK - 1
     if (OP == 4) {
-        blk_x_load<NBLK, FULL>(x1, Bg, n, r);
+        blk_x_load<NBLK, FULL>(x1, Bi, n, r);
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) p1[k] = 0.f;
     }
@@ -710,14 +712,17 @@ GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, float* x
             if (OP == 4) blk_fwd_step<NBLK>(T, k, m, myinv, x1, p1, q);
         }
     }
-    if (OP == 4) {  // a failed factorization leaves B untouched
+    if (FACTOR && OP != 0 && inf != 0 && Bi != Bg) {  // a failed factorization passes B through
+        for (int g = lane; g < n * nrhs; g += 64) Bg[g] = Bi[g];
+    }
+    if (OP == 4) {
         if (inf == 0) {
             blk_bwd1_posv<NBLK>(T, x1, myinv_last, lt, xs, q, r);
             blk_x_store<NBLK, FULL>(x1, Bg, n, q, r);
         }
         return inf;
     }
-    if (OP == 0 || inf != 0) return inf;  // a failed factorization leaves B untouched
+    if (OP == 0 || inf != 0) return inf;
     // off-diagonal blocks of L, negated: the forward pass subtracts L_kj Y_j
 #pragma unroll
     for (int k = 1; k < NBLK; ++k)
@@ -727,7 +732,7 @@ GLASS_DEV int blk_one(float* Ag, float* Bg, int n, int nrhs, int trans, float* x
     const bool fwd = OP != 3 || trans == 0, bwd = OP != 3 || trans != 0;
     for (int cb = 0; cb < nr; cb += 16) {
         f4_t Y[NBLK];
-        rhs_load<NBLK, FULL>(Y, Bg, n, nr, cb, q, r);
+        rhs_load<NBLK, FULL>(Y, Bi, n, nr, cb, q, r);
         if (fwd) {
 #pragma unroll
             for (int k = 0; k < NBLK; ++k) {

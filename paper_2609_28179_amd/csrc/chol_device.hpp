@@ -145,14 +145,16 @@ GLASS_DEV void thread_store_tri(const float (&a)[N * (N + 1) / 2], float* __rest
     }
 }
 
-// Solve the staged right-hand sides of every lane (all columns) in place.
+// Solve the staged right-hand sides of every lane (all columns), from Bi to Bg
+// (the same array for an in-place solve); a lane that is not active passes its
+// right-hand sides through.
 template <int N>
-GLASS_DEV void thread_solve_rhs(const float (&a)[N * (N + 1) / 2], const float (&dinv)[N], float* __restrict__ Bg,
+GLASS_DEV void thread_solve_rhs(const float (&a)[N * (N + 1) / 2], const float (&dinv)[N], const float* Bi, float* Bg,
                                 float* lds, int nrhs, int cnt, int tid, int nt, bool fwd, bool bwd,
                                 bool active) {
     const int SZ = N * nrhs, S = SZ | 1;
     const FastDiv fd = make_fastdiv(SZ);
-    stage_in<2>(lds, Bg, cnt * SZ, fd, S, tid, nt);
+    stage_in<2>(lds, Bi, cnt * SZ, fd, S, tid, nt);
     __syncthreads();
     if (active) {
         float* b = lds + tid * S;
@@ -466,17 +468,18 @@ GLASS_DEV void wave_bwd_chunk_rg(const float* buf, int r0, int r1, float (&acc)[
     }
 }
 
-// Columns c0 .. c0+RG-1 of the row-major [n][nrhs] block Bg (columns past
-// nrhs are zero padding and are not stored); the backward sweep walks the
-// 8-row chunks of L bottom-up and, when Lg is given, also stores L.
+// Columns c0 .. c0+RG-1 of the row-major [n][nrhs] block Bi into Bg, the same
+// array for an in-place solve (columns past nrhs are zero padding and are not
+// stored); the backward sweep walks the 8-row chunks of L bottom-up and, when
+// Lg is given, also stores L.
 template <int NB, int RG>
-GLASS_DEV void wave_solve_cols(const float (&a)[NB], float* buf, float* Lg, bool vec, float* Bg, int n, int nrhs,
-                               int c0, float myinv, int lane) {
+GLASS_DEV void wave_solve_cols(const float (&a)[NB], float* buf, float* Lg, bool vec, const float* Bi, float* Bg, int n,
+                               int nrhs, int c0, float myinv, int lane) {
     float acc[RG], y[RG];
 #pragma unroll
-    for (int c = 0; c < RG; ++c) {  // unconditional loads (Bg[0] for the rest), so that all issue at once
+    for (int c = 0; c < RG; ++c) {  // unconditional loads (Bi[0] for the rest), so that all issue at once
         const bool ok = lane < n && c0 + c < nrhs;
-        const float v = Bg[ok ? lane * nrhs + c0 + c : 0];
+        const float v = Bi[ok ? lane * nrhs + c0 + c : 0];
         acc[c] = ok ? v : 0.f;
     }
     wave_fwd_rg<NB, RG>(a, acc, y, myinv, lane);
@@ -495,19 +498,19 @@ GLASS_DEV void wave_solve_cols(const float (&a)[NB], float* buf, float* Lg, bool
 
 // All nrhs columns in groups of 8, 4 or 1 (L stored during the first group).
 template <int NB>
-GLASS_DEV void wave_solve_all(const float (&a)[NB], float* buf, float* Lg, bool vec, float* Bg, int n, int nrhs,
-                              float myinv, int lane) {
+GLASS_DEV void wave_solve_all(const float (&a)[NB], float* buf, float* Lg, bool vec, const float* Bi, float* Bg, int n,
+                              int nrhs, float myinv, int lane) {
     for (int c0 = 0; c0 < nrhs;) {
         float* L = c0 == 0 ? Lg : nullptr;
         const int left = nrhs - c0;
         if (left >= 5) {
-            wave_solve_cols<NB, 8>(a, buf, L, vec, Bg, n, nrhs, c0, myinv, lane);
+            wave_solve_cols<NB, 8>(a, buf, L, vec, Bi, Bg, n, nrhs, c0, myinv, lane);
             c0 += 8;
         } else if (left >= 2) {
-            wave_solve_cols<NB, 4>(a, buf, L, vec, Bg, n, nrhs, c0, myinv, lane);
+            wave_solve_cols<NB, 4>(a, buf, L, vec, Bi, Bg, n, nrhs, c0, myinv, lane);
             c0 += 4;
         } else {
-            wave_solve_cols<NB, 1>(a, buf, L, vec, Bg, n, nrhs, c0, myinv, lane);
+            wave_solve_cols<NB, 1>(a, buf, L, vec, Bi, Bg, n, nrhs, c0, myinv, lane);
             c0 += 1;
         }
     }
@@ -703,20 +706,20 @@ GLASS_DEV void seg_bwd(const float* sb, int i, float (&y)[RG], float myinv) {
     SegBwd<SEG, NB, NB - 1, RG, AHEAD>::run(sb, i, lc, y, myinv);
 }
 
-// Columns c0 .. c0+RG-1 of segment-local right-hand sides Bs (row-major
-// [n][r]; columns past r and rows past n are zero padding and are not
-// stored); act: this lane's segment has a problem to solve.  sb: the
+// Columns c0 .. c0+RG-1 of segment-local right-hand sides Bi into Bs, the same
+// array for an in-place solve (row-major [n][r]; columns past r and rows past
+// n are zero padding and are not stored); act: this lane's segment has a problem to solve.  sb: the
 // segment's L in LDS, row stride NB + 4.  a: row i of L for the forward
 // pass with its diagonal entry zero, scaled by 1 / L_ii (the coefficients of
 // SegFwdL).
 template <int SEG, int NB, int RG>
-GLASS_DEV void seg_solve_cols(const float (&a)[NB], const float* sb, float* Bs, int n, int r, int c0, int i,
-                              float myinv, bool act, bool fwd, bool bwd, const float* Bsafe) {
+GLASS_DEV void seg_solve_cols(const float (&a)[NB], const float* sb, const float* Bi, float* Bs, int n, int r, int c0,
+                              int i, float myinv, bool act, bool fwd, bool bwd, const float* Bsafe) {
     float y[RG];
 #pragma unroll
     for (int c = 0; c < RG; ++c) {  // unconditional loads (Bsafe for the rest), so that all issue at once
         const bool ok = act && i < n && c0 + c < r;
-        const float v = *(ok ? Bs + i * r + c0 + c : Bsafe);
+        const float v = *(ok ? Bi + i * r + c0 + c : Bsafe);
         y[c] = ok ? v : 0.f;
     }
     if (fwd) {
@@ -751,23 +754,23 @@ GLASS_DEV void seg_solve_one(const float (&a)[NB], const float* sb, float* Bs, i
 // DPP step runs in all lanes): the batch's nrhs for a uniform batch (the
 // default), the wavefront's largest count for a ragged one.  Bsafe: an
 // address every lane may read, which lanes with nothing to load read instead
-// so that the loads need no branch (default Bs, when every lane's Bs is
+// so that the loads need no branch (default Bi, when every lane's Bi is
 // valid).  a as for seg_solve_cols.
 template <int SEG, int NB>
-GLASS_DEV void seg_solve_all(const float (&a)[NB], const float* sb, float* Bs, int n, int r, int i, float myinv,
-                             bool act, bool fwd, bool bwd, int rloop = -1, const float* Bsafe = nullptr) {
+GLASS_DEV void seg_solve_all(const float (&a)[NB], const float* sb, const float* Bi, float* Bs, int n, int r, int i,
+                             float myinv, bool act, bool fwd, bool bwd, int rloop = -1, const float* Bsafe = nullptr) {
     if (rloop < 0) rloop = r;
-    if (!Bsafe) Bsafe = Bs;
+    if (!Bsafe) Bsafe = Bi;
     for (int c0 = 0; c0 < rloop;) {
         const int left = rloop - c0;
         if (left >= 5) {
-            seg_solve_cols<SEG, NB, 8>(a, sb, Bs, n, r, c0, i, myinv, act, fwd, bwd, Bsafe);
+            seg_solve_cols<SEG, NB, 8>(a, sb, Bi, Bs, n, r, c0, i, myinv, act, fwd, bwd, Bsafe);
             c0 += 8;
         } else if (left >= 2) {
-            seg_solve_cols<SEG, NB, 4>(a, sb, Bs, n, r, c0, i, myinv, act, fwd, bwd, Bsafe);
+            seg_solve_cols<SEG, NB, 4>(a, sb, Bi, Bs, n, r, c0, i, myinv, act, fwd, bwd, Bsafe);
             c0 += 4;
         } else {
-            seg_solve_cols<SEG, NB, 1>(a, sb, Bs, n, r, c0, i, myinv, act, fwd, bwd, Bsafe);
+            seg_solve_cols<SEG, NB, 1>(a, sb, Bi, Bs, n, r, c0, i, myinv, act, fwd, bwd, Bsafe);
             c0 += 1;
         }
     }

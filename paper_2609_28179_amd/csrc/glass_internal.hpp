@@ -279,19 +279,21 @@ int launch_gemv_thin(int m, int n, int batch, float alpha, const float* A, const
                      void* stream);
 int launch_potrf(const Shape& s, const Geometry& g, int batch, float* A, int32_t* info, void* stream);
 int launch_potrs(const Shape& s, const Geometry& g, int batch, const float* L, float* B, void* stream);
-int launch_posv(const Shape& s, const Geometry& g, int batch, float* A, float* B, int32_t* info,
-                void* stream);
+// POSV from A, B into L, X (the same arrays for a call in place).
+int launch_posv(const Shape& s, const Geometry& g, int batch, const float* A, const float* B, float* L, float* X,
+                int32_t* info, void* stream);
 int launch_trsv(const Shape& s, const Geometry& g, int batch, const float* L, float* x, void* stream);
 // Sub-wave scope of POTRF / POSV / POTRS / TRSV (A is L for the solves; B is
 // x for TRSV; info may be NULL), and their blocked wave-scope kernel for
-// orders kBlkMinN .. 64 (same arguments).
-int launch_chol_blk(const Shape& s, const Geometry& g, int batch, float* A, float* B, int32_t* info,
-                    void* stream);
+// orders kBlkMinN .. 64 (same arguments).  Ai and Bi are read, A and B written:
+// the same arrays in every call but an out-of-place POSV.
+int launch_chol_blk(const Shape& s, const Geometry& g, int batch, const float* Ai, float* A, const float* Bi, float* B,
+                    int32_t* info, void* stream);
 // Sub-wave scope of GEMM (Bx = B, Cy = C) and GEMV (Bx = x, Cy = y).
 int launch_blas_subwave(const Shape& s, const Geometry& g, int batch, float alpha, const float* A, const float* Bx,
                         float beta, float* Cy, void* stream);
-int launch_chol_subwave(const Shape& s, const Geometry& g, int batch, float* A, float* B, int32_t* info,
-                        void* stream);
+int launch_chol_subwave(const Shape& s, const Geometry& g, int batch, const float* Ai, float* A, const float* Bi,
+                        float* B, int32_t* info, void* stream);
 int launch_se3(const Shape& s, const Geometry& g, int batch, const float* Ta, const float* Tb,
                float* Tout, void* stream);
 // Placement (scope) of each of the eight ragged size classes (orders 8k+1 ..

@@ -203,7 +203,7 @@ GLASS_DEV void ragged_wave_one(float* __restrict__ Ag, float* __restrict__ Bg, i
     if (inf != 0) {
         wave_chunks_desc<NB>(a, buf, Ag, vec, n, lane, false, 0.f, myinv);
     } else {
-        wave_solve_all<NB>(a, buf, Ag, vec, Bg, n, nrhs, myinv, lane);
+        wave_solve_all<NB>(a, buf, Ag, vec, Bg, Bg, n, nrhs, myinv, lane);
     }
     if (lane == 0) *info = inf;
 }
@@ -271,7 +271,7 @@ GLASS_DEV void ragged_seg(float* A, float* B, const int64_t* offA, const int64_t
     int rmax = 0;
 #pragma unroll
     for (int t = 0; t < 64 / SEG; ++t) rmax = max(rmax, __builtin_amdgcn_readlane(reff, t * SEG));
-    seg_solve_all<SEG, NB>(a, sb, Bg, nn, reff, i, myinv, reff > 0, true, true, rmax);
+    seg_solve_all<SEG, NB>(a, sb, Bg, Bg, nn, reff, i, myinv, reff > 0, true, true, rmax);
 }
 
 // One work item per wavefront: wavefront g of the launch takes item g of the
@@ -347,9 +347,9 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
     float* Bg = B + uniform_i64(offB[e]);
     float* buf = chunk[w];
     if (big) {
-        const int inf = k == 3   ? blk_one<2, 1, false>(Ag, Bg, n, r, 0, buf, lane)
-                        : k <= 5 ? blk_one<3, 1, false>(Ag, Bg, n, r, 0, buf, lane)
-                                 : blk_one<4, 1, false>(Ag, Bg, n, r, 0, buf, lane);
+        const int inf = k == 3   ? blk_one<2, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
+                        : k <= 5 ? blk_one<3, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
+                                 : blk_one<4, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane);
         if (lane == 0) info[e] = inf;
         return;
     }

@@ -25,8 +25,8 @@ namespace {
 
 // op: 0 POTRF, 1 POSV, 2 POTRS, 3 TRSV (trans selects forward 0 / backward 1).
 template <int SEG, int NB, int OP>
-__global__ void __launch_bounds__(512) chol_seg(int n, int nrhs, int trans, int batch, float* __restrict__ A,
-                                                float* __restrict__ B, int32_t* __restrict__ info, int region) {
+__global__ void __launch_bounds__(512) chol_seg(int n, int nrhs, int trans, int batch, const float* Ai, float* A,
+                                                const float* Bi, float* B, int32_t* __restrict__ info, int region) {
     extern __shared__ float lds[];
     constexpr int PPW = 64 / SEG;
     const int w = wave_index(), lane = threadIdx.x & 63;
@@ -37,14 +37,15 @@ __global__ void __launch_bounds__(512) chol_seg(int n, int nrhs, int trans, int 
     const bool act = s < np;
     float* buf = lds + (size_t)w * region;
     float* sb = buf + s * NB * (NB + 4);
-    float* Ab = A + p0 * n * n;
+    const float* Ab = Ai + p0 * n * n;
     const int r = OP == 3 ? 1 : nrhs;
+    const float* Bsi = Bi + (p0 + s) * n * r;
     float* Bs = B + (p0 + s) * n * r;
     // With one right-hand side its entry, and for the solves the diagonal,
     // are loaded with the rows (a lane without a row reads its wave's first
     // problem's entries).
     const bool row = act && i < n, one = OP >= 1 && r == 1;
-    const float b1 = one ? B[row ? (p0 + s) * n + i : p0 * n] : 0.f;
+    const float b1 = one ? Bi[row ? (p0 + s) * n + i : p0 * n] : 0.f;
     const float dg = OP >= 2 ? Ab[row ? s * n * n + i * n + i : 0] : 1.f;
     float a[NB];
     float myinv = 1.f;
@@ -64,7 +65,7 @@ __global__ void __launch_bounds__(512) chol_seg(int n, int nrhs, int trans, int 
         wave_sync();
     }
     if (OP <= 1) {
-        seg_store_L<NB>(Ab, buf, np, n, (n & 3) == 0 && aligned16(A), lane);
+        seg_store_L<NB>(A + p0 * n * n, buf, np, n, (n & 3) == 0 && aligned16(A), lane);
         if (info && act && i == 0) info[p0 + s] = inf;
     }
     if (OP == 0) return;
@@ -82,17 +83,19 @@ __global__ void __launch_bounds__(512) chol_seg(int n, int nrhs, int trans, int 
         wave_sync();
     }
     seg_scale_row<NB>(a, myinv);
-    const bool solve = act && inf == 0;  // a failed factorization leaves B untouched
+    const bool solve = act && inf == 0;  // a failed factorization leaves B untouched (out of place: copies it)
+    if (OP == 1 && Bi != B && row && inf != 0)
+        for (int c = 0; c < r; ++c) Bs[i * r + c] = Bsi[i * r + c];
     if (one)
         seg_solve_one<SEG, NB>(a, sb, Bs, n, i, myinv, solve, fwd, bwd, row ? b1 : 0.f);
     else
-        seg_solve_all<SEG, NB>(a, sb, Bs, n, r, i, myinv, solve, fwd, bwd, -1, B + p0 * n * r);
+        seg_solve_all<SEG, NB>(a, sb, Bsi, Bs, n, r, i, myinv, solve, fwd, bwd, -1, Bi + p0 * n * r);
 }
 
 }  // namespace
 
-int launch_chol_subwave(const Shape& sh, const Geometry& g, int batch, float* A, float* B, int32_t* info,
-                        void* stream) {
+int launch_chol_subwave(const Shape& sh, const Geometry& g, int batch, const float* Ai, float* A, const float* Bi,
+                        float* B, int32_t* info, void* stream) {
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
     hipStream_t st = (hipStream_t)stream;
     const int n = sh.n, nb = subwave_nb(n);
@@ -102,8 +105,8 @@ int launch_chol_subwave(const Shape& sh, const Geometry& g, int batch, float* A,
     const int op = sh.op == GLASS_OP_POTRF ? 0 : sh.op == GLASS_OP_POSV ? 1 : sh.op == GLASS_OP_POTRS ? 2 : 3;
 #define SW(SEG, NB, OP)                                                                                         \
     if (nb == NB && op == OP) {                                                                                 \
-        hipLaunchKernelGGL((chol_seg<SEG, NB, OP>), grid, block, g.lds_bytes, st, n, sh.nrhs, sh.trans, batch, A, \
-                           B, info, region);                                                                    \
+        hipLaunchKernelGGL((chol_seg<SEG, NB, OP>), grid, block, g.lds_bytes, st, n, sh.nrhs, sh.trans, batch, Ai, \
+                           A, Bi, B, info, region);                                                                    \
         return (int)hipGetLastError();                                                                          \
     }
 #define SW_OPS(SEG, NB) SW(SEG, NB, 0) SW(SEG, NB, 1) SW(SEG, NB, 2) SW(SEG, NB, 3)

@@ -65,6 +65,7 @@ _SIGS = {
     "glass_potrf_batched": [_i, _i, _p, _p, _PP, _p],
     "glass_potrs_batched": [_i, _i, _i, _p, _p, _PP, _p],
     "glass_posv_batched": [_i, _i, _i, _p, _p, _p, _PP, _p],
+    "glass_posv_to_batched": [_i, _i, _i, _p, _p, _p, _p, _p, _PP, _p],
     "glass_trsv_batched": [_i, _i, _i, _p, _p, _PP, _p],
     "glass_se3_batched": [_i, _i, _p, _p, _p, _PP, _p],
     "glass_posv_adjoint_batched": [_i, _i, _i, _p, _p, _p, _p, _p, _PP, _p],
@@ -158,6 +159,11 @@ def glass_potrs_batched(n, nrhs, batch, L, B, force=None, stream=None) -> int:
 
 def glass_posv_batched(n, nrhs, batch, A, B, info=None, force=None, stream=None) -> int:
     return _lib.glass_posv_batched(n, nrhs, batch, _ptr(A), _ptr(B), _ptr(info), _force(force), _stream(stream))
+
+
+def glass_posv_to_batched(n, nrhs, batch, A, B, L, X, info=None, force=None, stream=None) -> int:
+    return _lib.glass_posv_to_batched(n, nrhs, batch, _ptr(A), _ptr(B), _ptr(L), _ptr(X), _ptr(info), _force(force),
+                                      _stream(stream))
 
 
 def glass_trsv_batched(n, batch, trans, L, x, force=None, stream=None) -> int:
@@ -354,6 +360,19 @@ def posv_(A, B, info=None, force=None):
     _check(info, "info", (b,), torch.int32)
     _raise(glass_posv_batched(n, B.shape[2], b, A, B, info, force), "posv")
     return A, B, info
+
+
+def posv_to(A, B, force=None):
+    """posv_ out of place: (L, X, info), A and B kept."""
+    b, n, _ = A.shape
+    r = B.shape[2]
+    _check(A, "A", (b, n, n))
+    _check(B, "B", (b, n, r))
+    L = torch.empty_like(A)
+    X = torch.empty_like(B)
+    info = torch.empty((b,), dtype=torch.int32, device=A.device)
+    _raise(glass_posv_to_batched(n, r, b, A, B, L, X, info, force), "posv")
+    return L, X, info
 
 
 def trsv_(L, x, trans=0, force=None):
