@@ -1,7 +1,8 @@
 """torch.autograd.Function for the batched Cholesky solve X = A^{-1} B.
 
 Forward: one fused factor-and-solve launch (glass_posv_to_batched), which
-leaves A and B as they are; the factor L and the solution X are saved.  Backward: one launch of
+leaves A and B as they are; the factor L and the solution X are saved.
+Backward: one launch of
 the hand-written adjoint kernel (glass_posv_adjoint_batched), which returns
 dB = A^{-1} G and the symmetric dA = -(dB X^T + X dB^T) / 2.
 """
@@ -15,7 +16,7 @@ from . import glass
 class CholeskySolve(torch.autograd.Function):
     @staticmethod
     def forward(ctx, A, B, force=None):
-        L, X, info = glass.posv_to(A.detach().contiguous(), B.detach().contiguous(), force)
+        L, X, info = glass.posv_to(A.contiguous(), B.contiguous(), force)
         ctx.save_for_backward(L, X)
         ctx.force = force
         ctx.info = info
