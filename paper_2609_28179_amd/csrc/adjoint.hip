@@ -11,10 +11,10 @@
 //   thread  (n <= 16) one problem per lane: L in VGPRs (compile-time n),
 //           G and X staged through LDS, dA written through LDS passes as
 //           coalesced stores.
-//   wave    one problem per wavefront.  Up to order 24 the wave-scope
+//   wave    one problem per wavefront.  Up to order 16 the wave-scope
 //           substitutions of chol.hip; lane i accumulates row i of dA from
 //           v_readlane broadcasts of x_j and dB_j, rows leave through the 8-row
-//           LDS chunk.  From order 25 the blocked routines of chol_blk.hpp:
+//           LDS chunk.  From order 17 the blocked routines of chol_blk.hpp:
 //           one right-hand side by the VALU substitutions and an outer product
 //           on the lanes, several by the matrix-core solve and rank-16
 //           products; 16-row block rows of dA leave through LDS.
@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(512) adjoint_wave(int n, int nrhs, int batch, 
     wave_chunks_desc<NB>(d, buf, dA + p * n * n, vec, n, lane, false, 0.f, 1.f);
 }
 
-// ------------------------------------------------ blocked form, orders 25..64
+// ------------------------------------------------ blocked form, orders 17..64
 // LDS floats of one wavefront: the staged block row of dA and, with several
 // right-hand sides, one exchange block per tile of the transposes.
 constexpr int adjoint_blk_floats(int nblk, bool one) {
@@ -506,8 +506,8 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
         default: return (int)hipErrorInvalidValue;
         }
     } else if (g.scope == GLASS_SCOPE_WAVE && n >= kBlkMinN) {
-        // whole tiles from order 25, where the blocked solves take over from the
-        // row-per-lane ones (below, 16 x 16 tiles would be mostly padding)
+        // from order 17, two 16 x 16 tiles, where the blocked solves take over
+        // from the row-per-lane ones
         const int nblk = blk_nblk(n);
         const bool full = n == 16 * nblk && al16(L) && al16(dA);
         const size_t lds = sizeof(float) * (size_t)adjoint_blk_floats(nblk, r == 1) * g.pack;
@@ -529,7 +529,7 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
     case NB:                                                                                                     \
         hipLaunchKernelGGL(adjoint_wave<NB>, grid, block, g.lds_bytes, st, n, r, batch, L, X, G, dB, dA, region); \
         break;
-            CASE(8) CASE(16) CASE(24)
+            CASE(8) CASE(16)
 #undef CASE
         default: return (int)hipErrorInvalidValue;
         }

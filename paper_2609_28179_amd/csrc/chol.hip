@@ -350,7 +350,7 @@ __global__ void __launch_bounds__(256) trsv_wg(int n, int trans, int batch, int 
 // ----------------------------------------------------------------- launch --
 #define GLASS_CASES_1_16(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
-#define GLASS_BUCKETS(X) X(8) X(16) X(24)  // orders below kBlkMinN; from there on the blocked kernels run
+#define GLASS_BUCKETS(X) X(8) X(16)  // orders below kBlkMinN; from there on the blocked kernels run
 
 inline int bucket8(int n) { return ((n + 7) / 8) * 8; }
 

@@ -1,5 +1,5 @@
 // chol_blk.hip -- batched wave-scope kernels of POTRF / POSV / POTRS / TRSV
-// for orders 25..64 on the blocked routines of chol_blk.hpp (one problem per
+// for orders 17..64 on the blocked routines of chol_blk.hpp (one problem per
 // wavefront; 2, 3 or 4 tiles of 16 per side): the MFMA kernel for the
 // factorizations and multi-column solves, the VALU substitution for one
 // right-hand side.

@@ -103,11 +103,14 @@ inline int bucket8_host(int n) { return ((n + 7) / 8) * 8; }
 // stores and backward substitution.
 constexpr int kGemmStageStride = 68;  // LDS row stride of the staged 16-row output block of the MFMA GEMM
 
-// Orders from kBlkMinN up of POTRF / POSV / POTRS / TRSV run the blocked MFMA
-// kernel at wave scope (below, the 16 x 16 tiles would be mostly padding);
-// its LDS per wavefront holds one staged 16-row block row of L or four
-// 16 x 16 exchange blocks.
-constexpr int kBlkMinN = 25;
+// Orders from kBlkMinN up (two 16 x 16 tiles or more) of POTRF / POSV / POTRS /
+// TRSV run the blocked kernels at wave scope; at one tile nothing is left to
+// block.  Against the row-per-lane kernels at n = 20, 65,536 problems: TRSV 35.0
+// -> 30.0 us, POTRS 54 -> 33, with 8 right-hand sides 192 -> 59, POSV with 8
+// 265 -> 125, POTRF 102 -> 85 (sub-wave scope 59: three tiles' work for 1.6
+// tiles of matrix).  The blocked MFMA kernel's LDS per wavefront holds one
+// staged 16-row block row of L or four 16 x 16 exchange blocks.
+constexpr int kBlkMinN = 17;
 constexpr int kBlkRegionFloats = 1280;
 constexpr int kBlkXS = 20;  // LDS row stride of a 16 x 16 exchange block
 // LDS row stride of a staged block row of L: 16 nblk floats and four of padding.
