@@ -6,21 +6,23 @@
 // thread scope (class 0 only: a wavefront takes 64 problems, one per lane),
 // sub-wave scope (classes 0 and 1: four problems per wavefront, one per
 // 16-lane row; class 2: two, one per 32-lane half) or wave scope (a
-// wavefront takes one problem; orders above 24 run the blocked MFMA routines
+// wavefront takes one problem; orders above 16 run the blocked MFMA routines
 // of chol_blk.hpp).  Within a class a problem is padded with an identity
 // block up to the class order, so one code path serves all its n.  (Thread
 // scope stops at order 8 here because every path of a solve kernel shares
 // one register allocation.)
 //
 // Launch sequence (all on one stream, no host synchronisation, capturable):
-//   1. ragged_count    per-chunk class histograms (each block a fixed chunk);
-//   2. ragged_scan     one block: class totals, class bases in descending
+//   1. up to kPlanMax problems, ragged_plan: every block counts all classes for
+//      itself and scatters its own chunk.  Past it three kernels:
+//      ragged_count    per-chunk class histograms (each block a fixed chunk);
+//      ragged_scan     one block: class totals, class bases in descending
 //                      class order (largest problems first), per-chunk bases,
 //                      work-item bases;
-//   3. ragged_scatter  stable counting-sort scatter of problem indices into
+//      ragged_scatter  stable counting-sort scatter of problem indices into
 //                      perm[] (ranks from wavefront ballots, so the permutation
 //                      is deterministic: equal classes keep index order);
-//   4. ragged_solve    one wavefront per work item of the class-sorted list
+//   2. ragged_solve    one wavefront per work item of the class-sorted list
 //                      (64 problems of a thread-scope class, four at sub-wave
 //                      scope, or one problem), every class in one launch, so
 //                      the small classes fill the slots that the blocked
@@ -40,11 +42,12 @@ namespace {
 constexpr int kClasses = 8;
 constexpr int kChunk = 1024;        // problems per histogram / scatter block
 constexpr int kScanThreads = 256;
-constexpr int kBigClass = 3;        // classes from here on (orders above 24) run the blocked routines
+constexpr int kBigClass = 2;        // classes from here on (orders above 16) run the blocked routines at wave scope
+constexpr int kPlanMax = 65536;     // problems up to which one launch plans the batch
 // LDS floats per wavefront of the small-class solve: the segments' L blocks
 // (row stride NB + 4) of the sub-wave path, or the wave path's 8-row chunk
 constexpr int kRaggedSegFloats = 2 * 24 * 28;
-static_assert(4 * 16 * 20 <= kRaggedSegFloats && 8 * 24 <= kRaggedSegFloats, "ragged LDS");
+static_assert(4 * 16 * 20 <= kRaggedSegFloats && 8 * 16 <= kRaggedSegFloats, "ragged LDS");
 
 // Work items of class k holding `cnt` problems: 64 problems per item at
 // thread scope, 4 (classes 0, 1) or 2 (class 2) at sub-wave scope, 1 at wave
@@ -150,6 +153,123 @@ __global__ void __launch_bounds__(256) ragged_scatter(int count, const int32_t* 
         __syncthreads();
         if (tid < kClasses) off[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
         __syncthreads();
+    }
+}
+
+// The whole plan in one launch (count <= kPlanMax): block b owns chunk b, 1024
+// problems, and counts every class before its chunk and in all, a lane's counts
+// in the eight bytes of two words (at most 64 problems a lane, read four at a
+// time with all loads of a round in flight).  The batch's orders are read by every block, at most 256 KB from L2; the three launches
+// took 4.8 + 4.8 + 5.1 us at 50,000 problems and the gaps between them, this one 11.5.
+// Chunk order, lane order and ballots keep the permutation the stable one.
+__global__ void __launch_bounds__(kChunk) ragged_plan(int count, const int32_t* __restrict__ nvec,
+                                                      int32_t* __restrict__ perm, int32_t* __restrict__ meta,
+                                                      RaggedScopes scopes) {
+    constexpr int kWaves = kChunk / 64;
+    __shared__ int32_t part[kWaves][2][kClasses];  // per wavefront: counts before the chunk, counts in all
+    __shared__ int32_t sum[2][kClasses];
+    __shared__ int32_t off[kClasses];
+    __shared__ int32_t wcnt[kWaves][kClasses];
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_index();
+    const int mine = blockIdx.x;
+    const __amdgpu_buffer_rsrc_t rn = buffer_rsrc(nvec, (uint32_t)count * 4u);
+    uint32_t all[2] = {0, 0}, bef[2] = {0, 0};  // classes 0..3 and 4..7
+    typedef int i4_t __attribute__((ext_vector_type(4)));
+    constexpr int kRound = kPlanMax / (4 * kChunk);
+    i4_t n[kRound];
+#pragma unroll
+    for (int u = 0; u < kRound; ++u) {  // every whole group of four in flight at once
+        const int g = 4 * (kChunk * u + tid);
+        n[u] = __builtin_bit_cast(i4_t, __builtin_amdgcn_raw_buffer_load_b128(rn, g + 4 <= count ? g * 4 : kOob, 0, 0));
+    }
+    const int e = mine * kChunk + tid;  // this lane's own problem
+    const int n_own = nvec[e < count ? e : 0];
+    const int et = (count & ~3) + tid;  // the last one to three problems
+    const int nt = __builtin_amdgcn_raw_buffer_load_b32(rn, et < count ? et * 4 : kOob, 0, 0);
+#pragma unroll
+    for (int u = 0; u < kRound; ++u) {
+        const int g = 4 * (kChunk * u + tid);
+        if (4 * kChunk * u < count) {  // wave-uniform
+            uint32_t lo = 0, hi = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = class_of(n[u][j]);
+                const uint32_t one = 1u << (8 * (k & 3));
+                lo += k < 4 ? one : 0u;
+                hi += k < 4 ? 0u : one;
+            }
+            if (g + 4 > count) lo = hi = 0;
+            all[0] += lo;
+            all[1] += hi;
+            if (g < mine * kChunk) {  // four neighbours are on one side of the chunk's start
+                bef[0] += lo;
+                bef[1] += hi;
+            }
+        }
+    }
+    if (et < count) {  // never before this block's chunk: chunk starts are multiples of four
+        const int k = class_of(nt);
+        all[k >> 2] += 1u << (8 * (k & 3));
+    }
+    const int k = e < count ? class_of(n_own) : -1;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    int rank = 0;
+#pragma unroll
+    for (int c = 0; c < kClasses; ++c) {
+        const uint64_t m = __ballot(k == c);
+        if (k == c) rank = __popcll(m & lt);
+        if (lane == 0) wcnt[w][c] = __popcll(m);
+    }
+    // bytes to 16-bit fields (even and odd classes of a word; at most 64 x 64
+    // each), summed over the wavefront: f[half][word][parity]
+    constexpr uint32_t kEven = 0x00ff00ffu;
+    uint32_t f[2][2][2];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        f[0][v][0] = bef[v] & kEven;
+        f[0][v][1] = (bef[v] >> 8) & kEven;
+        f[1][v][0] = all[v] & kEven;
+        f[1][v][1] = (all[v] >> 8) & kEven;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            f[u >> 2][(u >> 1) & 1][u & 1] += (uint32_t)__shfl_xor((int)f[u >> 2][(u >> 1) & 1][u & 1], o, 64);
+    if (lane == 0) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < kClasses; ++c)
+                part[w][h][c] = (int)((f[h][c >> 2][c & 1] >> (16 * ((c >> 1) & 1))) & 0xffffu);
+    }
+    __syncthreads();
+    if (tid < 2 * kClasses) {
+        int s = 0;
+        for (int u = 0; u < kWaves; ++u) s += part[u][tid >> 3][tid & 7];
+        sum[tid >> 3][tid & 7] = s;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int base = 0, items = 0;
+        for (int c = kClasses - 1; c >= 0; --c) {
+            const int tot = sum[1][c];
+            off[c] = base + sum[0][c];
+            if (mine == 0) {
+                meta[c] = tot;
+                meta[kClasses + c] = base;
+                meta[2 * kClasses + c] = items;
+            }
+            base += tot;
+            items += items_of(scopes.s[c], c, tot);
+        }
+        if (mine == 0) meta[3 * kClasses] = items;  // total work items
+    }
+    __syncthreads();
+    if (k >= 0) {
+        int at = off[k] + rank;
+        for (int u = 0; u < w; ++u) at += wcnt[u][k];
+        perm[at] = e;
     }
 }
 
@@ -286,9 +406,9 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
                                                     const int64_t* __restrict__ offB, float* A, float* B,
                                                     int32_t* info, const int32_t* __restrict__ perm,
                                                     const int32_t* __restrict__ meta, RaggedScopes scopes) {
-    // per wavefront, the largest of: 8 rows of up to 24 (the row-per-lane wave
+    // per wavefront, the largest of: 8 rows of up to 16 (the row-per-lane wave
     // path), the segments' L blocks (sub-wave) and the blocked routines'
-    // staging (orders above 24)
+    // staging (orders above 16)
     constexpr int kFloats = kBlkRegionFloats > kRaggedSegFloats ? kBlkRegionFloats : kRaggedSegFloats;
     __shared__ float chunk[4][kFloats];
     const int lane = threadIdx.x & 63, w = wave_index();
@@ -301,10 +421,11 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
         const int nit = items_of(scopes.s[c], c, cnt);
         if (cnt > 0 && item >= ib && item < ib + nit) k = c;
     }
-    const bool big = k >= kBigClass;
+    const bool seg_scope = scopes.s[k] == kScopeSubwave;  // classes 0 to 2 only (checked by the caller)
+    const bool big = k >= kBigClass && !seg_scope;
     const int rel = item - meta[2 * kClasses + k];
     const int cbase = meta[kClasses + k];
-    if (!big && scopes.s[k] == kScopeSubwave) {  // classes 0 to 2 only (checked by the caller)
+    if (seg_scope) {
         const int seg = k <= 1 ? 16 : 32;
         const int q = rel * (64 / seg) + lane / seg;
         int e = -1, n = 0, r = 0;
@@ -347,17 +468,16 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
     float* Bg = B + uniform_i64(offB[e]);
     float* buf = chunk[w];
     if (big) {
-        const int inf = k == 3   ? blk_one<2, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
+        const int inf = k <= 3   ? blk_one<2, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
                         : k <= 5 ? blk_one<3, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
                                  : blk_one<4, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane);
         if (lane == 0) info[e] = inf;
         return;
     }
-    switch (k) {
-    case 0: ragged_wave_one<8>(Ag, Bg, n, r, info + e, buf, lane); break;
-    case 1: ragged_wave_one<16>(Ag, Bg, n, r, info + e, buf, lane); break;
-    default: ragged_wave_one<24>(Ag, Bg, n, r, info + e, buf, lane); break;  // class 2
-    }
+    if (k == 0)
+        ragged_wave_one<8>(Ag, Bg, n, r, info + e, buf, lane);
+    else
+        ragged_wave_one<16>(Ag, Bg, n, r, info + e, buf, lane);
 }
 
 }  // namespace
@@ -417,9 +537,13 @@ int launch_posv_ragged(int count, const int32_t* n, const int32_t* nrhs, const i
     int32_t* hist = reinterpret_cast<int32_t*>(workspace);
     int32_t* meta = hist + (size_t)nchunks * kClasses;
     int32_t* perm = meta + 32;
-    hipLaunchKernelGGL(ragged_count, dim3(nchunks), dim3(256), 0, st, count, n, hist);
-    hipLaunchKernelGGL(ragged_scan, dim3(1), dim3(kScanThreads), 0, st, nchunks, hist, meta, scopes);
-    hipLaunchKernelGGL(ragged_scatter, dim3(nchunks), dim3(256), 0, st, count, n, hist, perm);
+    if (count <= kPlanMax) {
+        hipLaunchKernelGGL(ragged_plan, dim3(nchunks), dim3(kChunk), 0, st, count, n, perm, meta, scopes);
+    } else {
+        hipLaunchKernelGGL(ragged_count, dim3(nchunks), dim3(256), 0, st, count, n, hist);
+        hipLaunchKernelGGL(ragged_scan, dim3(1), dim3(kScanThreads), 0, st, nchunks, hist, meta, scopes);
+        hipLaunchKernelGGL(ragged_scatter, dim3(nchunks), dim3(256), 0, st, count, n, hist, perm);
+    }
     // work items never outnumber problems: ceil(count / 4) four-wave blocks cover the list
     hipLaunchKernelGGL(ragged_solve, dim3((count + 3) / 4), dim3(256), 0, st, n, nrhs, offA, offB, A, B, info, perm,
                        meta, scopes);

@@ -107,3 +107,28 @@ def test_ragged_graph_replays_match_eager():
         torch.cuda.synchronize()
         assert torch.equal(rg.A, A_e) and torch.equal(rg.B, B_e), rep
         assert torch.equal(rg.info, info_e) and torch.equal(rg.perm(), perm_e), rep
+
+
+@pytest.mark.parametrize("count", [1023, 1024, 1025, 4099, 65535, 65536, 65537, 70001])
+def test_plan_edges(count):
+    """The permutation on either side of a chunk, of a group of four, and of the
+    batch size where the plan changes from one launch to three, bit-exact;
+    info 0 throughout and the problems of the last chunk solved."""
+    import torch
+    from paper_2609_28179_amd import glass
+    print(f"ragged plan count={count}", flush=True)
+    rng = np.random.default_rng(count)
+    n = rng.integers(1, 20, count).astype(np.int32)
+    n[rng.integers(0, count, 9)] = 64
+    sa = n.astype(np.int64) ** 2
+    offA, offB = np.cumsum(sa) - sa, np.cumsum(n, dtype=np.int64) - n
+    A, B = np.zeros(int(sa.sum()), np.float32), rng.uniform(-1, 1, int(n.sum())).astype(np.float32)
+    d = np.repeat(offA, n) + np.concatenate([np.arange(m, dtype=np.int64) * (m + 1) for m in n])
+    A[d] = 4.0  # A = 4 I: x = b / 4 exactly
+    case = {"n": n, "nrhs": np.ones(count, np.int32), "offA": offA, "offB": offB, "A": A, "B": B.copy()}
+    rg = glass.Ragged(case)
+    rg.solve()
+    torch.cuda.synchronize()
+    assert np.array_equal(rg.perm().cpu().numpy(), oracle.ragged_order(n))
+    assert (rg.info.cpu().numpy() == 0).all()
+    assert np.max(np.abs(rg.B.cpu().numpy() - B / 4)) <= 2.0 ** -22
