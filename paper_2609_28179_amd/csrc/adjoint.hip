@@ -264,9 +264,9 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
         const float myinv = recip(diag_rows<true>(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
 #pragma unroll
         for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
-        blk_fwd_step<NBLK>(T, k, a, myinv, b, pend, q);
+        blk_fwd_step<NBLK>(T, k, a, myinv, b, pend, q, blk_live<NBLK, FULL>(n, k));
     }
-    blk_bwd1<NBLK>(T, b, xs, q, r);
+    blk_bwd1<NBLK, FULL>(T, b, xs, n, q, r);
     blk_x_store<NBLK, FULL>(b, dB + p * n, n, q, r);
     float bc[NBLK][4], xc[NBLK][4];
 #pragma unroll
@@ -341,7 +341,7 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
             const float myinv = recip(diag_rows<true>(T[BI(k, k)], m, xs, q, r)), nmy = -myinv;
 #pragma unroll
             for (int j = 0; j < 16; ++j) m[j] *= nmy;
-            linv[k] = tri_inverse_l(m, myinv, q, r);
+            linv[k] = tri_inverse_l(m, myinv, q, r, blk_live<NBLK, FULL>(n, k));
         }
 #pragma unroll
         for (int k = 1; k < NBLK; ++k)

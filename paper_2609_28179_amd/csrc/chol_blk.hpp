@@ -143,18 +143,52 @@ GLASS_DEV void fmac_self_bcast(float& acc, float m) {
                  : "v"(m), "n"(K));
 }
 
-template <int K>
+template <int K, int END>
 struct InvStep {
     static GLASS_DEV void run(float (&u)[4], const float (&m)[16]) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) fmac_self_bcast<K>(u[c], m[K]);
-        InvStep<K + 1>::run(u, m);
+        InvStep<K + 1, END>::run(u, m);
     }
 };
-template <>
-struct InvStep<16> {
+template <int END>
+struct InvStep<END, END> {
     static GLASS_DEV void run(float (&)[4], const float (&)[16]) {}
 };
+
+// Rows of diagonal block k that belong to the problem, rows past them being
+// the identity: pivot steps on those would find unit pivots and zero
+// coefficients, so the last block of an order that is no multiple of 16 runs
+// its first 4, 8, 12 or 16 steps.  With the staged rows of blk_one serving the
+// inverse (16 registers fewer: POSV n = 33..47 with several columns at seven
+// wavefronts per SIMD): POSV n = 22 x 65,536 107 -> 91 us, n = 36, 3 columns x
+// 16,384 63 -> 60, ragged solve of 50,000 systems 144 -> 133.
+template <int NBLK, bool FULL>
+GLASS_DEV int blk_live(int n, int k) {
+    return FULL || k + 1 < NBLK ? 16 : n - 16 * (NBLK - 1);
+}
+
+// Cholesky steps of a diagonal block in row form whose rows from `live` (1 ..
+// 16, wave-uniform) on are the identity.
+template <int NB>
+GLASS_DEV void diag_factor_n(float (&a)[16], int& f, float& myinv, int r) {
+    float as[NB];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) as[c] = a[c];
+    SegStep<16, NB, 0>::run(as, f, myinv);
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[c] = c < NB ? (c <= r ? as[c] : 0.f) : (c == r ? 1.f : 0.f);
+}
+GLASS_DEV void diag_factor(float (&a)[16], int& f, float& myinv, int r, int live) {
+    if (live > 12)
+        diag_factor_n<16>(a, f, myinv, r);
+    else if (live > 8)
+        diag_factor_n<12>(a, f, myinv, r);
+    else if (live > 4)
+        diag_factor_n<8>(a, f, myinv, r);
+    else
+        diag_factor_n<4>(a, f, myinv, r);
+}
 
 // X = L^{-1} of a 16 x 16 lower diagonal block, in T layout: lane (q, r)
 // returns row r, columns 4 q .. 4 q + 3.  Forward substitution against the
@@ -162,31 +196,30 @@ struct InvStep<16> {
 // K and above the diagonal) and myinv = 1 / L_rr reads
 // X_r = e_r / L_rr + sum_{K<r} m_K X_K, so the rows are finished in order
 // K = 0..15 and each step is one v_fmac per column with lane K's row
-// broadcast.
-GLASS_DEV f4_t tri_inverse_l(const float (&m)[16], float myinv, int q, int r) {
+// broadcast.  Rows from `live` on are the identity.
+GLASS_DEV f4_t tri_inverse_l(const float (&m)[16], float myinv, int q, int r, int live = 16) {
     float u[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) u[c] = (4 * q + c == r) ? myinv : 0.f;
     asm volatile("s_nop 1" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]));
-    InvStep<0>::run(u, m);
+    InvStep<0, 4>::run(u, m);
+    if (live > 4) {
+        InvStep<4, 8>::run(u, m);
+        if (live > 8) {
+            InvStep<8, 12>::run(u, m);
+            if (live > 12) InvStep<12, 16>::run(u, m);
+        }
+    }
     return f4_t{u[0], u[1], u[2], u[3]};
 }
 
-// Row r of a factored diagonal block with its diagonal entry cleared, read
-// back through LDS at xs (row stride S).  STAGED: the rows are already there
-// (the staged block row); otherwise the lanes of row 0 write them first.
-// Leaves the cleared rows in LDS.
-template <int S, bool STAGED>
-GLASS_DEV void rows_zero_diag(const float (&a)[16], float (&az)[16], float* xs, int q, int r) {
-    if (!STAGED) {
-        if (q == 0) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                *reinterpret_cast<f4_t*>(xs + r * S + 4 * u) = f4_t{a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]};
-        }
-        wave_sync();
-    }
-    xs[r * S + r] = 0.f;
+// Row r of a factored diagonal block that is in LDS at xs (row stride S), with
+// its diagonal entry cleared; the entry itself is put back if KEEP.
+template <int S, bool KEEP>
+GLASS_DEV void staged_rows_zero_diag(float (&az)[16], float* xs, int r) {
+    float* d = xs + r * S + r;
+    const float keep = KEEP ? *d : 0.f;
+    *d = 0.f;
     wave_sync();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -195,6 +228,23 @@ GLASS_DEV void rows_zero_diag(const float (&a)[16], float (&az)[16], float* xs, 
         for (int e = 0; e < 4; ++e) az[4 * u + e] = v[e];
     }
     wave_sync();
+    if (KEEP) {
+        *d = keep;
+        wave_sync();
+    }
+}
+
+// The same for a block whose rows are in registers (every 16-lane row a copy):
+// the lanes of row 0 write them to LDS first.
+template <int S>
+GLASS_DEV void rows_zero_diag(const float (&a)[16], float (&az)[16], float* xs, int q, int r) {
+    if (q == 0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            *reinterpret_cast<f4_t*>(xs + r * S + 4 * u) = f4_t{a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]};
+    }
+    wave_sync();
+    staged_rows_zero_diag<S, false>(az, xs, r);
 }
 
 // Rows 16 k .. of a row-major n x n matrix from the staged block row at xs
@@ -248,12 +298,12 @@ GLASS_DEV void block_row_store(float* Mg, int k, int n, const float* xs, int lan
     }
 }
 
-// Block row k of L (rows 16 k .. 16 k + 15): the finished blocks left of the
-// diagonal, the diagonal block from its rows and +0 to the right, staged in
-// LDS and stored as whole rows.
-template <int NBLK, bool FULL>
-GLASS_DEV void store_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&a)[16], float* Ag,
-                               int n, float* xs, int q, int r, int lane) {
+// Block row k of L (rows 16 k .. 16 k + 15) staged in LDS for block_row_store:
+// the finished blocks left of the diagonal, the diagonal block from its rows
+// and +0 to the right.
+template <int NBLK>
+GLASS_DEV void stage_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&a)[16], float* xs, int q,
+                               int r) {
     constexpr int kRS = blk_row_stride(NBLK);
 #pragma unroll
     for (int j = 0; j < NBLK; ++j) {
@@ -266,8 +316,6 @@ GLASS_DEV void store_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, co
             *reinterpret_cast<f4_t*>(xs + r * kRS + 16 * k + 4 * u) =
                 f4_t{a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]};
     }
-    wave_sync();
-    block_row_store<NBLK, FULL>(Ag, k, n, xs, lane);
     wave_sync();
 }
 
@@ -374,21 +422,40 @@ GLASS_DEV void fmac_self_bcast_w(float& acc, float m) {
                  : "v"(m), "n"(K));
 }
 
-template <int K, int DIR>
+template <int K, int END>  // steps K, K + 1 .. END - 1, or K, K - 1 .. END + 1
 struct DiagSub {
     static GLASS_DEV void run(float& s, const float (&m)[16]) {
         fmac_self_bcast_w<K>(s, m[K]);
-        DiagSub<K + DIR, DIR>::run(s, m);
+        DiagSub<K + (K < END ? 1 : -1), END>::run(s, m);
     }
 };
-template <>
-struct DiagSub<16, 1> {
+template <int END>
+struct DiagSub<END, END> {
     static GLASS_DEV void run(float&, const float (&)[16]) {}
 };
-template <>
-struct DiagSub<-1, -1> {
-    static GLASS_DEV void run(float&, const float (&)[16]) {}
-};
+
+// Forward (unknowns 0 .. 15) and backward (15 .. 0) substitution; rows from
+// `live` on are the identity, whose steps add nothing.
+GLASS_DEV void diag_fwd(float& s, const float (&m)[16], int live) {
+    DiagSub<0, 4>::run(s, m);
+    if (live > 4) {
+        DiagSub<4, 8>::run(s, m);
+        if (live > 8) {
+            DiagSub<8, 12>::run(s, m);
+            if (live > 12) DiagSub<12, 16>::run(s, m);
+        }
+    }
+}
+GLASS_DEV void diag_bwd(float& s, const float (&m)[16], int live) {
+    if (live > 4) {
+        if (live > 8) {
+            if (live > 12) DiagSub<15, 11>::run(s, m);
+            DiagSub<11, 7>::run(s, m);
+        }
+        DiagSub<7, 3>::run(s, m);
+    }
+    DiagSub<3, -1>::run(s, m);
+}
 
 // v summed over the four 16-lane rows (lanes r, r + 16, r + 32, r + 48), in
 // every lane: each v_permlane*_swap exchanges half of v with half of a copy,
@@ -493,10 +560,10 @@ GLASS_DEV void blk_x_store(const float (&x)[NBLK], float* bg, int n, int q, int 
 // rows q).
 template <int NBLK>
 GLASS_DEV void blk_fwd_step(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&m)[16], float myinv,
-                            float (&x)[NBLK], float (&p)[NBLK], int q) {
+                            float (&x)[NBLK], float (&p)[NBLK], int q, int live) {
     float s = k > 0 ? x[k] - sum_rows4(p[k]) : x[k];
     s *= myinv;
-    DiagSub<0, 1>::run(s, m);
+    diag_fwd(s, m, live);
     x[k] = s;
     if (k + 1 < NBLK) {
         float xc[4];
@@ -510,8 +577,8 @@ GLASS_DEV void blk_fwd_step(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const
 
 // L^T x = y, bottom block first (left-looking over the columns: z[j] collects
 // sum_i L_ij^T x_i split over the lanes of a row).
-template <int NBLK>
-GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float* xs, int q, int r) {
+template <int NBLK, bool FULL>
+GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float* xs, int n, int q, int r) {
     float z[NBLK][4];
 #pragma unroll
     for (int k = 0; k < NBLK; ++k)
@@ -529,7 +596,7 @@ GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK]
 #pragma unroll
         for (int j = 0; j < 16; ++j) col[j] *= nmy;  // -L_jr / L_rr
         s *= myinv;
-        DiagSub<15, -1>::run(s, col);
+        diag_bwd(s, col, blk_live<NBLK, FULL>(n, k));
         x[k] = s;
 #pragma unroll
         for (int j = 0; j < k; ++j)
@@ -550,9 +617,9 @@ GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK]
 //       x_k = L_kk^{-T} s is four FMAs on s in C form (the form the sum of
 //       the pending products L_ik^T x_i already has) and one sum over the
 //       four rows q -- no substitution chain.
-template <int NBLK>
+template <int NBLK, bool FULL>
 GLASS_DEV void blk_bwd1_posv(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float myinv_last,
-                             const float* lt, float* xs, int q, int r) {
+                             const float* lt, float* xs, int n, int q, int r) {
     constexpr int K = NBLK - 1;
     constexpr int RS = blk_row_stride(NBLK);
     float z[NBLK][4];
@@ -567,7 +634,7 @@ GLASS_DEV void blk_bwd1_posv(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[
 #pragma unroll
         for (int j = 0; j < 16; ++j) mt[j] = colr[j * RS] * nmy;
         float s = x[K] * myinv_last;
-        DiagSub<15, -1>::run(s, mt);
+        diag_bwd(s, mt, blk_live<NBLK, FULL>(n, K));
         x[K] = s;
 #pragma unroll
         for (int j = 0; j < K; ++j)
@@ -607,10 +674,10 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
             const float myinv = recip(diag_rows<true>(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
 #pragma unroll
             for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
-            blk_fwd_step<NBLK>(T, k, a, myinv, x, p, q);
+            blk_fwd_step<NBLK>(T, k, a, myinv, x, p, q, blk_live<NBLK, FULL>(n, k));
         }
     }
-    if (BWD) blk_bwd1<NBLK>(T, x, xs, q, r);
+    if (BWD) blk_bwd1<NBLK, FULL>(T, x, xs, n, q, r);
     blk_x_store<NBLK, FULL>(x, bg, n, q, r);
 }
 
@@ -622,10 +689,8 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
 // of blk_bwd1_posv after it on the inverses the panels used; no inverse of
 // the last diagonal block and no block transposes).  Every op forms the
 // diagonal blocks' inverses with tri_inverse_l on lane-local coefficients:
-// after a factorization from the factored rows read back through LDS with
-// their diagonal cleared (the staged block row itself when it is already
-// out: two tiles per side, and the last block), for the solves from rows
-// read without it.  Ai is A (L for the solves), Bi the problem's [n][nr]
+// after a factorization from the rows of the staged block row with their
+// diagonal cleared, for the solves from rows read without it.  Ai is A (L for the solves), Bi the problem's [n][nr]
 // right-hand sides (nr = 1 for TRSV and op 4); L goes to Ag and the solution to
 // Bg, which are Ai and Bi themselves for a call in place.  xs: the wavefront's
 // LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).  Returns info (0 for
@@ -652,38 +717,42 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
     int inf = 0;
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
-        // Block row k is final once its diagonal block is factored.  On three
-        // or four tiles per side it is staged and stored while the matrix
-        // cores run the panel products (3 % on POTRF / POSV n = 64 x 4096,
-        // whose waves are bound by this chain); on two tiles, memory-bound
+        // Block row k is final once its diagonal block is factored, and is
+        // staged in LDS at once (its rows then serve the inverse, and no longer
+        // need registers).  On three or four tiles per side it is stored while
+        // the matrix cores run the panel products (3 % on POTRF / POSV n = 64 x
+        // 4096, whose waves are bound by this chain); on two tiles, memory-bound
         // at large batches, and for the last block it goes out first.
         const bool early = NBLK < 3 || k + 1 == NBLK;
+        const int live = blk_live<NBLK, FULL>(n, k);
+        constexpr int RS = blk_row_stride(NBLK);
         float a[16];
         const float d = diag_rows<!FACTOR>(T[BI(k, k)], a, xs, q, r);
         float myinv = 1.f;
         if (FACTOR) {
             int f = 0;
-            SegStep<16, 16, 0>::run(a, f, myinv);
-#pragma unroll
-            for (int c = 0; c < 16; ++c) a[c] = c <= r ? a[c] : 0.f;
+            diag_factor(a, f, myinv, r, live);
             if (inf == 0 && f != 0) inf = 16 * k + f;
-            if (early) store_block_row<NBLK, FULL>(T, k, a, Ag, n, xs, q, r, lane);
+            stage_block_row<NBLK>(T, k, a, xs, q, r);
+            if (early) {
+                block_row_store<NBLK, FULL>(Ag, k, n, xs, lane);
+                wave_sync();
+            }
         } else {
             myinv = recip(d);
         }
         // The coefficients -L_rj / L_rr of the block's substitutions (its
         // inverse; op 4's forward step): the rows with their diagonal entry
-        // cleared, read back through LDS after a factorization (from the
-        // staged block row when it is already out), as they come for the
-        // solves.
+        // cleared, from the staged block row after a factorization, as they
+        // come for the solves.
         const bool need_inv = MFMA_SOLVE || k + 1 < NBLK;
         float m[16];
         if (need_inv || OP == 4) {
             if (FACTOR) {
                 if (early)
-                    rows_zero_diag<blk_row_stride(NBLK), true>(a, m, xs + 16 * k, q, r);
+                    staged_rows_zero_diag<RS, false>(m, xs + 16 * k, r);
                 else
-                    rows_zero_diag<kXS, false>(a, m, xs, q, r);
+                    staged_rows_zero_diag<RS, true>(m, xs + 16 * k, r);
             } else {
 #pragma unroll
                 for (int j = 0; j < 16; ++j) m[j] = a[j];
@@ -693,14 +762,17 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
             for (int j = 0; j < 16; ++j) m[j] *= nmy;
         }
         if (need_inv) {
-            linv[k] = tri_inverse_l(m, myinv, q, r);
+            linv[k] = tri_inverse_l(m, myinv, q, r, live);
             if (OP == 4) *reinterpret_cast<f4_t*>(lt + k * 16 * kXS + r * kXS + 4 * q) = linv[k];
         }
         if (OP == 4 && k + 1 == NBLK) myinv_last = myinv;
         if (FACTOR) {
 #pragma unroll
             for (int i = k + 1; i < NBLK; ++i) T[BI(i, k)] = mma(linv[k], T[BI(i, k)], zero4());
-            if (!early) store_block_row<NBLK, FULL>(T, k, a, Ag, n, xs, q, r, lane);
+            if (!early) {
+                block_row_store<NBLK, FULL>(Ag, k, n, xs, lane);
+                wave_sync();
+            }
 #pragma unroll
             for (int j = k + 1; j < NBLK; ++j) {
                 const f4_t nq = neg4(T[BI(j, k)]);
@@ -709,7 +781,7 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
             }
             // op 4: forward step k (needs this step's panel L_ik), on VALU
             // while the matrix cores run the trailing products
-            if (OP == 4) blk_fwd_step<NBLK>(T, k, m, myinv, x1, p1, q);
+            if (OP == 4) blk_fwd_step<NBLK>(T, k, m, myinv, x1, p1, q, live);
         }
     }
     if (FACTOR && OP != 0 && inf != 0 && Bi != Bg) {  // a failed factorization passes B through
@@ -717,7 +789,7 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
     }
     if (OP == 4) {
         if (inf == 0) {
-            blk_bwd1_posv<NBLK>(T, x1, myinv_last, lt, xs, q, r);
+            blk_bwd1_posv<NBLK, FULL>(T, x1, myinv_last, lt, xs, n, q, r);
             blk_x_store<NBLK, FULL>(x1, Bg, n, q, r);
         }
         return inf;

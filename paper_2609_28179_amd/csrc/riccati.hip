@@ -45,32 +45,6 @@
 namespace glass {
 namespace {
 
-// L^{-1} of a 16 x 16 lower diagonal block whose rows and columns from NK on
-// are the identity, in T layout: the substitution steps K >= NK add nothing
-// (their coefficients are zero), so only the first NK run.
-template <int K, int NK>
-struct InvStepN {
-    static GLASS_DEV void run(float (&u)[4], const float (&m)[16]) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) fmac_self_bcast<K>(u[c], m[K]);
-        InvStepN<K + 1, NK>::run(u, m);
-    }
-};
-template <int NK>
-struct InvStepN<NK, NK> {
-    static GLASS_DEV void run(float (&)[4], const float (&)[16]) {}
-};
-
-template <int NK>
-GLASS_DEV f4_t tri_inverse_l_first(const float (&m)[16], float myinv, int q, int r) {
-    float u[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) u[c] = (4 * q + c == r) ? myinv : 0.f;
-    asm volatile("s_nop 1" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]));
-    InvStepN<0, NK>::run(u, m);
-    return f4_t{u[0], u[1], u[2], u[3]};
-}
-
 // NUB: nu rounded up to 4, 8 or 16.  S is the identity past nu, so its
 // factorization and inverse run NUB pivot steps instead of 16.  All of P and
 // the first block column of A are in flight before the chain that factors
@@ -145,10 +119,10 @@ __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, c
     if (info && lane == 0) info[p] = f;
     if (f != 0) return;  // K is not written for an indefinite S
     float m[16];  // the rows again, diagonal entry cleared, scaled by -1 / L_rr
-    rows_zero_diag<kXS, false>(a, m, xs, q, r);
+    rows_zero_diag<kXS>(a, m, xs, q, r);
 #pragma unroll
     for (int j = 0; j < 16; ++j) m[j] *= -myinv;
-    const f4_t linv = tri_inverse_l_first<NUB>(m, myinv, q, r);  // L^{-1} in T layout
+    const f4_t linv = tri_inverse_l(m, myinv, q, r, NUB);  // L^{-1} in T layout
     f4_t lt[4];
     lt[0] = linv;
     transpose_blocks<1>(lt, xs, q, r);  // lt[0]: L^{-T} in T layout
