@@ -215,7 +215,7 @@ GLASS_DEV void mfma_problem(int m, int n, int k, float alpha, const float* __res
 // Bound by the read of the operands where they are large.  Guarded scalar
 // loads and 4-byte stores in the MFMA output layout took, back to back, J^T J
 // of 64 x 30 at 16,384 problems 66.6 us against 41.3 now (its bytes take 32 at
-// 5.7 TB/s), J^T r 37.9 against 25.9, 33 x 20 x 50 90 against 48, 63 x 61 x 62
+// 5.7 TB/s), 33 x 20 x 50 90 against 48, 63 x 61 x 62
 // at 8192 151 against 86; below order 16 the LDS-staged form of the
 // workgroup scope (two LDS reads per FMA) took J^T J of 13 x 7 at 65,536 63.1
 // us against 18.7, 12^3 transposed 68.9 against 19.4.
@@ -322,6 +322,58 @@ __global__ void __launch_bounds__(512) gemm_mfma_wave(int m, int n, int k, int b
             wave_sync();
         }
     }
+}
+
+// y = alpha A^T x + beta y (op(A) = A^T, one column, m >= 4), one problem per
+// wavefront: A is k x m, LPR lanes take a row of it in 16-byte pieces (64 / LPR
+// rows per load instruction, LPR instructions cover k <= 64, all issued before
+// any is read), a lane's four partial sums run over its rows and the lanes of
+// a column meet by exchanges at the end.  The last piece of a row moves back over its
+// neighbour, so that no piece leaves its row; the columns both hold come out
+// alike.  Bound by the read of A; as a one-column product of the matrix cores, with
+// 4-byte loads in operand layout, 64 x 30 at 16,384 problems took 25.9 us
+// against 21.0 (its bytes take 22 at the rate of a copy).
+template <int LPR>
+__global__ void __launch_bounds__(512) gemm_tvec(int m, int k, int batch, float alpha, const float* __restrict__ A,
+                                                 const float* __restrict__ x, float beta, float* __restrict__ y) {
+    constexpr int RPI = 64 / LPR;
+    const int w = wave_index(), lane = threadIdx.x & 63, row0 = lane / LPR, c = lane % LPR;
+    const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
+    if (p >= batch) return;
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(A + p * m * k, (uint32_t)(m * k) * 4u);
+    const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(x + p * k, (uint32_t)k * 4u);
+    const __amdgpu_buffer_rsrc_t ry = buffer_rsrc(y + p * m, (uint32_t)m * 4u);
+    const bool col = 4 * c < m;
+    const int s = min(4 * c, m - 4);
+    const float xv = buf_load1(rx, lane < k ? lane * 4 : kOob, 0);
+    f4_t a[LPR];
+#pragma unroll
+    for (int j = 0; j < LPR; ++j) {
+        const int row = j * RPI + row0;
+        a[j] = buf_load4(ra, col && row < k ? (row * m + s) * 4 : kOob, 0);
+    }
+    f4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < LPR; ++j) {
+        const float xr =
+            __int_as_float(__builtin_amdgcn_ds_bpermute((j * RPI + row0) * 4, __float_as_int(xv)));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(a[j][e], xr, acc[e]);
+    }
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+    const int off = row0 == 0 && col ? s * 4 : kOob;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= alpha;
+    if (beta != 0.f) {
+        const f4_t y0 = buf_load4(ry, off, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(beta, y0[e], acc[e]);
+    }
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, acc), ry, off,
+                                           0, 0);
 }
 
 // Whole tiles (m = n = k = N = 16 TB, TB = 1..4, no transposes, every operand
@@ -460,6 +512,15 @@ int launch_gemm_t(const Shape& sh, const Geometry& g, int batch, float alpha, co
                 hipLaunchKernelGGL(gemm_mfma_wave_full<4>, grid, block, g.lds_bytes, st, batch, alpha, A, B, beta, C);
                 break;
             }
+            return (int)hipGetLastError();
+        }
+        if (TA && n == 1 && m >= 4) {  // a vector: no matrix tile to fill
+            if (m <= 16)
+                hipLaunchKernelGGL(gemm_tvec<4>, grid, block, 0, st, m, k, batch, alpha, A, B, beta, C);
+            else if (m <= 32)
+                hipLaunchKernelGGL(gemm_tvec<8>, grid, block, 0, st, m, k, batch, alpha, A, B, beta, C);
+            else
+                hipLaunchKernelGGL(gemm_tvec<16>, grid, block, 0, st, m, k, batch, alpha, A, B, beta, C);
             return (int)hipGetLastError();
         }
         const size_t lds = sizeof(float) * 16 * kGemmStageStride * (size_t)g.pack;

@@ -12,7 +12,7 @@ from helpers import TOL, guarded, guards_intact, normwise
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1), (1, 3, 2), (3, 1, 5), (2, 16, 3), (7, 7, 13), (15, 16, 17), (16, 5, 4), (17, 33, 15), (30, 1, 64),
-          (30, 30, 64), (31, 2, 49), (33, 48, 32), (48, 63, 1), (49, 18, 61), (64, 64, 64), (64, 13, 3), (63, 61, 62)]
+          (4, 1, 1), (5, 1, 64), (16, 1, 33), (17, 1, 9), (32, 1, 64), (33, 1, 40), (63, 1, 17), (64, 1, 64), (30, 30, 64), (31, 2, 49), (33, 48, 32), (48, 63, 1), (49, 18, 61), (64, 64, 64), (64, 13, 3), (63, 61, 62)]
 
 
 @pytest.fixture(scope="module")
