@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
         float a[16];
-        const float myinv = recip(diag_rows<true>(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
+        const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
 #pragma unroll
         for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
         blk_fwd_step<NBLK>(T, k, a, myinv, b, pend, q, blk_live<NBLK, FULL>(n, k));
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
             float m[16];
-            const float myinv = recip(diag_rows<true>(T[BI(k, k)], m, xs, q, r)), nmy = -myinv;
+            const float myinv = recip(diag_rows(T[BI(k, k)], m, xs, q, r)), nmy = -myinv;
 #pragma unroll
             for (int j = 0; j < 16; ++j) m[j] *= nmy;
             linv[k] = tri_inverse_l(m, myinv, q, r, blk_live<NBLK, FULL>(n, k));

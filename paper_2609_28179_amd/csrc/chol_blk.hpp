@@ -27,10 +27,10 @@
 //   update    A_ij^T -= L_jk L_ik^T                 M = -L_jk
 //   forward   Y_k = L_kk^{-1} (B_k - sum_j L_kj Y_j)  M = L_kk^{-1}, -L_kj
 // The backward substitution needs L_ik^T and L_kk^{-T} as M; those come from
-// a transpose through LDS.  A diagonal block goes through LDS into
-// row-per-lane form (each 16-lane row of the wavefront receives all 16 rows),
-// is factored with the 16-lane DPP column steps, and is inverted by forward
-// substitution against the identity, which yields L_kk^{-1} in T layout.
+// a transpose through LDS.  A diagonal block is factored in T layout by panels
+// of four columns, and is inverted, from its rows read back from LDS (each
+// 16-lane row of the wavefront receives all 16), by forward substitution
+// against the identity, which yields L_kk^{-1} in T layout.
 //
 // Rows past n are identity rows (unit pivots that leave the real rows alone;
 // L = I there for the solves) and columns past n are zero.
@@ -109,25 +109,20 @@ GLASS_DEV void blk_load(f4_t (&T)[NBLK * (NBLK + 1) / 2], const float* Ag, int n
         for (int e = 0; e < 4; ++e) T[BI(i, i)][e] = (4 * q + e <= r) ? T[BI(i, i)][e] : 0.f;
 }
 
-// Diagonal block (T layout) to row-per-lane form: lane (q, r) receives row r
-// (every 16-lane row of the wavefront a full copy).  Returns the lane's
-// diagonal entry; ZD: the rows come with that entry cleared.
-template <bool ZD = false>
+// Diagonal block (T layout) to row-per-lane form with its diagonal entries
+// cleared: lane (q, r) receives row r (every 16-lane row of the wavefront a
+// full copy).  Returns the lane's diagonal entry.
 GLASS_DEV float diag_rows(const f4_t& t, float (&a)[16], float* xs, int q, int r) {
     *reinterpret_cast<f4_t*>(xs + r * kXS + 4 * q) = t;
     wave_sync();
-    float d = 0.f;
-    if (ZD) {
-        d = xs[r * kXS + r];
-        xs[r * kXS + r] = 0.f;
-    }
+    const float d = xs[r * kXS + r];
+    xs[r * kXS + r] = 0.f;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const f4_t v = *reinterpret_cast<const f4_t*>(xs + r * kXS + 4 * u);
 #pragma unroll
         for (int e = 0; e < 4; ++e) a[4 * u + e] = v[e];
     }
-    if (!ZD) d = xs[r * kXS + r];
     wave_sync();
     return d;
 }
@@ -160,34 +155,105 @@ struct InvStep<END, END> {
 // the identity: pivot steps on those would find unit pivots and zero
 // coefficients, so the last block of an order that is no multiple of 16 runs
 // its first 4, 8, 12 or 16 steps.  With the staged rows of blk_one serving the
-// inverse (16 registers fewer: POSV n = 33..47 with several columns at seven
-// wavefronts per SIMD): POSV n = 22 x 65,536 107 -> 91 us, n = 36, 3 columns x
+// inverse (16 registers fewer): POSV n = 22 x 65,536 107 -> 91 us, n = 36, 3 columns x
 // 16,384 63 -> 60, ragged solve of 50,000 systems 144 -> 133.
 template <int NBLK, bool FULL>
 GLASS_DEV int blk_live(int n, int k) {
     return FULL || k + 1 < NBLK ? 16 : n - 16 * (NBLK - 1);
 }
 
-// Cholesky steps of a diagonal block in row form whose rows from `live` (1 ..
-// 16, wave-uniform) on are the identity.
-template <int NB>
-GLASS_DEV void diag_factor_n(float (&a)[16], int& f, float& myinv, int r) {
-    float as[NB];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) as[c] = a[c];
-    SegStep<16, NB, 0>::run(as, f, myinv);
-#pragma unroll
-    for (int c = 0; c < 16; ++c) a[c] = c < NB ? (c <= r ? as[c] : 0.f) : (c == r ? 1.f : 0.f);
+// Panel S (columns 4 S .. 4 S + 3) of a diagonal block in T layout, held by the
+// 16 lanes of row S: each column is scaled by 1 / sqrt of its pivot and taken
+// off the later columns of the panel.  inv: 1 / sqrt of the first pivot; it and
+// the block's registers were written by instructions of the compiler's own, so
+// that nothing the asm writes can still be an operand of a product in flight.
+// The DPP row mask keeps the other rows' registers; rows above the panel's
+// diagonal hold values that are cleared after the last panel.  This is the
+// serial chain of the factorization, so the wait states (one before a
+// transcendental result or a lane read of a VALU result, two before a DPP read
+// or a use of a scalar written by the VALU) are filled with the other columns'
+// updates where there are any.
+template <int S>
+GLASS_DEV void panel_cols(f4_t& t, float inv, float& myinv) {
+    constexpr int J = 4 * S;
+    constexpr unsigned long long m = seg_mask<16>() << J;
+    float d;
+    asm volatile(
+        "s_nop 0\n\t"
+        "v_mul_f32_dpp %0, %0, %5 quad_perm:[0,1,2,3] row_mask:%11 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %4, %4, %5, %7\n\ts_nop 0\n\t"
+        "v_fmac_f32_dpp %1, %0, -%0 row_newbcast:%13 row_mask:%11 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %0, -%0 row_newbcast:%14 row_mask:%11 bank_mask:0xf\n\t"
+        "v_readlane_b32 %6, %1, %16\n\t"
+        "v_fmac_f32_dpp %3, %0, -%0 row_newbcast:%15 row_mask:%11 bank_mask:0xf\n\t"
+        "s_nop 0\n\tv_rsq_f32_e32 %5, %6\n\ts_nop 0\n\t"
+        "v_mul_f32_dpp %1, %1, %5 quad_perm:[0,1,2,3] row_mask:%11 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %4, %4, %5, %8\n\ts_nop 0\n\t"
+        "v_fmac_f32_dpp %2, %1, -%1 row_newbcast:%14 row_mask:%11 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %1, -%1 row_newbcast:%15 row_mask:%11 bank_mask:0xf\n\t"
+        "v_readlane_b32 %6, %2, %17\n\t"
+        "s_nop 1\n\tv_rsq_f32_e32 %5, %6\n\ts_nop 0\n\t"
+        "v_mul_f32_dpp %2, %2, %5 quad_perm:[0,1,2,3] row_mask:%11 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %4, %4, %5, %9\n\ts_nop 0\n\t"
+        "v_fmac_f32_dpp %3, %2, -%2 row_newbcast:%15 row_mask:%11 bank_mask:0xf\n\t"
+        "s_nop 0\n\tv_readlane_b32 %6, %3, %18\n\t"
+        "s_nop 1\n\tv_rsq_f32_e32 %5, %6\n\ts_nop 0\n\t"
+        "v_mul_f32_dpp %3, %3, %5 quad_perm:[0,1,2,3] row_mask:%11 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %4, %4, %5, %10"
+        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(myinv), "+v"(inv), "=&s"(d)
+        : "s"(m), "s"(m << 1), "s"(m << 2), "s"(m << 3), "n"(1 << S), "n"(0), "n"(J + 1), "n"(J + 2), "n"(J + 3),
+          "n"(16 * S + J + 1), "n"(16 * S + J + 2), "n"(16 * S + J + 3));
 }
-GLASS_DEV void diag_factor(float (&a)[16], int& f, float& myinv, int r, int live) {
-    if (live > 12)
-        diag_factor_n<16>(a, f, myinv, r);
-    else if (live > 8)
-        diag_factor_n<12>(a, f, myinv, r);
-    else if (live > 4)
-        diag_factor_n<8>(a, f, myinv, r);
-    else
-        diag_factor_n<4>(a, f, myinv, r);
+
+// Panel S of the block as an MFMA operand of depth 4: lane (q, r) receives
+// register q of lane (S, r), which is P[r][q] as the first operand and
+// P^T[q][r] as the second.  Two wait states between a VALU write and the swap
+// or MFMA that reads it.
+template <int S>
+GLASS_DEV float panel_operand(const f4_t& t) {
+    float u0 = t[0], u1 = t[1], u2 = t[2], u3 = t[3];
+    asm volatile(
+        "s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3\n\ts_nop 1\n\t"
+        ".if %4\n\tv_permlane32_swap_b32 %1, %3\n\t.else\n\tv_permlane32_swap_b32 %0, %2\n\t.endif\n\ts_nop 1"
+        : "+v"(u0), "+v"(u1), "+v"(u2), "+v"(u3)
+        : "n"(S & 1));
+    return S == 0 ? u0 : S == 1 ? u1 : u2;
+}
+
+// Panels S .. of a diagonal block: four columns, then their product P P^T off
+// the columns to the right, one v_mfma_f32_16x16x4_f32.  The finished columns
+// are kept by a select and not by zero rows of P, so that a failed pivot's NaN
+// leaves the columns left of it as they are.
+template <int S>
+GLASS_DEV void panel_steps(f4_t& t, float& myinv, int q, int live) {
+    panel_cols<S>(t, rsq(readlane(t[0], 20 * S)), myinv);
+    if constexpr (S < 3) {
+        if (live > 4 * (S + 1)) {
+            const float p = panel_operand<S>(t);
+            const f4_t d = __builtin_amdgcn_mfma_f32_16x16x4f32(-p, p, t, 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) t[c] = q > S ? d[c] : t[c];
+            panel_steps<S + 1>(t, myinv, q, live);
+        }
+    }
+}
+
+// Cholesky of a diagonal block in T layout, in place (strict upper part
+// cleared); rows from `live` (1 .. 16, wave-uniform) on are the identity.  In
+// row-per-lane form, all four 16-lane rows with a copy, the 120 updates of the
+// trailing columns were the largest part of the factorization's VALU work
+// (without them POSV n = 22 x 65,536 took 76 of 96 us, n = 30 x 16,384 31 of
+// 37); by panels of four columns they are 24, and three matrix-core products.
+// Row form against panels: POTRF n = 20 x 65,536 74 -> 65.5 us, POSV n = 22 x
+// 65,536 96 -> 88, n = 30 x 16,384 38.5 -> 36, n = 36 with 3 columns x 16,384
+// 59.7 -> 57, n = 48 x 256 (the chain alone) 7.6 -> 7.0, ragged solve of
+// 50,000 systems with its plan 155 -> 143; POTRF n = 32 x 65,536, at its
+// bytes, 94 -> 95.
+GLASS_DEV void diag_factor(f4_t& t, int& f, float& myinv, int q, int r, int live) {
+    panel_steps<0>(t, myinv, q, live);
+    f = first_nonfinite<16>(myinv);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t[c] = 4 * q + c <= r ? t[c] : 0.f;
 }
 
 // X = L^{-1} of a 16 x 16 lower diagonal block, in T layout: lane (q, r)
@@ -299,23 +365,13 @@ GLASS_DEV void block_row_store(float* Mg, int k, int n, const float* xs, int lan
 }
 
 // Block row k of L (rows 16 k .. 16 k + 15) staged in LDS for block_row_store:
-// the finished blocks left of the diagonal, the diagonal block from its rows
-// and +0 to the right.
+// the finished blocks up to the diagonal and +0 to the right.
 template <int NBLK>
-GLASS_DEV void stage_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&a)[16], float* xs, int q,
-                               int r) {
+GLASS_DEV void stage_block_row(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, float* xs, int q, int r) {
     constexpr int kRS = blk_row_stride(NBLK);
 #pragma unroll
-    for (int j = 0; j < NBLK; ++j) {
-        if (j < k) *reinterpret_cast<f4_t*>(xs + r * kRS + 16 * j + 4 * q) = T[BI(k, j)];
-        if (j > k) *reinterpret_cast<f4_t*>(xs + r * kRS + 16 * j + 4 * q) = zero4();
-    }
-    if (q == 0) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            *reinterpret_cast<f4_t*>(xs + r * kRS + 16 * k + 4 * u) =
-                f4_t{a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]};
-    }
+    for (int j = 0; j < NBLK; ++j)
+        *reinterpret_cast<f4_t*>(xs + r * kRS + 16 * j + 4 * q) = j <= k ? T[BI(k, j)] : zero4();
     wave_sync();
 }
 
@@ -671,7 +727,7 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
             float a[16];
-            const float myinv = recip(diag_rows<true>(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
+            const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
 #pragma unroll
             for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
             blk_fwd_step<NBLK>(T, k, a, myinv, x, p, q, blk_live<NBLK, FULL>(n, k));
@@ -726,36 +782,30 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
         const bool early = NBLK < 3 || k + 1 == NBLK;
         const int live = blk_live<NBLK, FULL>(n, k);
         constexpr int RS = blk_row_stride(NBLK);
-        float a[16];
-        const float d = diag_rows<!FACTOR>(T[BI(k, k)], a, xs, q, r);
-        float myinv = 1.f;
+        float m[16], myinv = 1.f;
         if (FACTOR) {
             int f = 0;
-            diag_factor(a, f, myinv, r, live);
+            diag_factor(T[BI(k, k)], f, myinv, q, r, live);
             if (inf == 0 && f != 0) inf = 16 * k + f;
-            stage_block_row<NBLK>(T, k, a, xs, q, r);
+            stage_block_row<NBLK>(T, k, xs, q, r);
             if (early) {
                 block_row_store<NBLK, FULL>(Ag, k, n, xs, lane);
                 wave_sync();
             }
         } else {
-            myinv = recip(d);
+            myinv = recip(diag_rows(T[BI(k, k)], m, xs, q, r));
         }
         // The coefficients -L_rj / L_rr of the block's substitutions (its
         // inverse; op 4's forward step): the rows with their diagonal entry
         // cleared, from the staged block row after a factorization, as they
         // come for the solves.
         const bool need_inv = MFMA_SOLVE || k + 1 < NBLK;
-        float m[16];
         if (need_inv || OP == 4) {
             if (FACTOR) {
                 if (early)
                     staged_rows_zero_diag<RS, false>(m, xs + 16 * k, r);
                 else
                     staged_rows_zero_diag<RS, true>(m, xs + 16 * k, r);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) m[j] = a[j];
             }
             const float nmy = -myinv;
 #pragma unroll

@@ -199,3 +199,37 @@ def test_nonfinite_pivots(env, op, scope):
         if not (guards_intact(Af) and guards_intact(Bf)):
             fails.append(f"{label}: guard band written")
     assert not fails, "\n".join(fails)
+
+
+@pytest.mark.parametrize("op", ["potrf", "posv"])
+def test_blocked_orders(env, op):
+    """Every order of the blocked wave kernels (the diagonal blocks' panels of
+    four columns end at each remainder): factors against the oracle, and in a
+    problem whose last pivot fails the columns left of it stay the factor's."""
+    glass, torch = env
+    fails = []
+    batch = 5
+    for n in range(17, 65):
+        rng = np.random.default_rng(3000 + n)
+        A = inputs.spd(rng, batch, n)
+        B = inputs.uniform(rng, (batch, n, 2))
+        A[3, n - 1, n - 1] = -100.0
+        G = A[3].astype(np.float64)
+        L = np.linalg.cholesky(G[:-1, :-1])
+        left = np.vstack([L, np.linalg.solve(L, G[:-1, -1])[None]])
+        L_ref, info_ref = oracle.potrf(A)
+        Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+        info = torch.full((batch,), -7, dtype=torch.int32, device="cuda:0")
+        if op == "potrf":
+            st = glass.glass_potrf_batched(n, batch, Ad, info, ("wave", 1))
+        else:
+            st = glass.glass_posv_batched(n, 2, batch, Ad, Bd, info, ("wave", 1))
+        torch.cuda.synchronize()
+        assert st == 0
+        ok = np.array([0, 1, 2, 4])
+        got = np.tril(Ad.cpu().numpy())
+        err = normwise(got[ok], L_ref[ok]).max()
+        err_left = normwise(got[3:4, :, :-1], left[None]).max()
+        if not np.array_equal(info.cpu().numpy(), info_ref) or not err <= TOL or not err_left <= TOL:
+            fails.append(f"{op} n={n}: info {info.cpu().numpy()}, err {err:.3e}, left of the failed pivot {err_left:.3e}")
+    assert not fails, "\n".join(fails)
