@@ -187,7 +187,7 @@ def emit(args):
         raise SystemExit(f"{args.sweep} was measured on sources {meta and meta.get('src')}, the tree has "
                          f"{source_hash()}: re-sweep (or --allow-stale)")
     ch = choose(recs)
-    nk, bk = timing.SWEEP_N, timing.TABLE_B
+    nk, bk = timing.TABLE_N, timing.TABLE_B
     lines = []
     missing = 0
     for op in OP_ORDER:
@@ -372,7 +372,7 @@ def main(argv=None):
     s.add_argument("--ns", default="", help="comma-separated orders to sweep (default: all)")
     s.add_argument("--max-batch", type=int, default=0)
     s.add_argument("--cells", choices=("table", "heldout"), default="table",
-                   help="table: the 250 cells of the dispatch table; heldout: n in {5,9,20,48} x "
+                   help="table: the 408 cells of the dispatch table; heldout: n in {5,9,20,48} x "
                         "batch in {256,65536}, the cost model's evaluation set")
     e = sub.add_parser("emit")
     e.add_argument("--sweep", default=DEFAULT_SWEEP)
