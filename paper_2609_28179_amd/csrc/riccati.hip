@@ -19,11 +19,17 @@
 // four DPP exchanges; S is factored with the segment Cholesky (lane a holds
 // row a of L); column i of T = PB^T A takes PB's rows as broadcasts, and
 // lane i solves L L^T k = t for its own column of K with L's entries as
-// broadcasts.  Every cross-lane move stays inside a 16-lane row.
+// broadcasts.  Every cross-lane move stays inside a 16-lane row.  The operands
+// come by buffer loads at one per-lane offset per operand and a scalar row
+// offset, and S's rows are picked from the sums by one select per entry; with
+// 64-bit addresses and selects per element (12 x 4: 322 VALU instructions per
+// wavefront, 180 now) 65,536 problems took (12, 4) 20.7 us against 17.2 (its
+// bytes take 18.4 at the rate of a copy), (16, 4) 31.5 against 29.9, (16, 8) 50.6 against
+// 39.8 (38.3), (14, 7) 42.7 against 41.2 (29.3).
 //
 // riccati_mfma (every size): every product on the matrix cores, operands read
-// once by branch-free buffer loads (device_common.hpp), in the blocked layouts of chol_blk.hpp (nx padded to 16-row blocks; nu <= 16
-// is one block).  With B_k in accumulator layout (lane (q, r) holds B[16k+4q+c][r])
+// once by branch-free buffer loads (device_common.hpp), in the blocked layouts
+// of chol_blk.hpp (nx padded to 16-row blocks; nu <= 16 is one block).  With B_k in accumulator layout (lane (q, r) holds B[16k+4q+c][r])
 // the products chain without data movement:
 //   PB_i = sum_k P_ik B_k                 P_ik loaded row-wise (T layout)
 //   S    = R + sum_i B_i^T PB_i           B_i's registers are the T layout of B_i^T
@@ -276,29 +282,45 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
     if (p0 >= batch) return;
     const long long ps = p0 + s;
     const bool act = ps < batch;
-    const long long pp = act ? ps : p0;  // a row past the batch reads its wave's first problem
-    const float* Pp = P + pp * nx * nx;
-    const float* Ap = A + pp * nx * nx;
-    const float* Bp = B + pp * nx * nu;
-    const float* Rp = R + pp * nu * nu;
     const bool row = i < nx;
+    // The wavefront's problems are adjacent, so one descriptor per operand
+    // covers them; a lane past its matrix or the batch gets an offset out of
+    // its range and reads 0.  nx > NXB - 4 from 12 states up, so that only the
+    // last rows of P and A need a test there.
+    const int np = (int)min(4ll, batch - p0);
+    const __amdgpu_buffer_rsrc_t rp = buffer_rsrc(P + p0 * nx * nx, (uint32_t)(np * nx * nx) * 4u);
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(A + p0 * nx * nx, (uint32_t)(np * nx * nx) * 4u);
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(B + p0 * nx * nu, (uint32_t)(np * nx * nu) * 4u);
+    const __amdgpu_buffer_rsrc_t rr = buffer_rsrc(R + p0 * nu * nu, (uint32_t)(np * nu * nu) * 4u);
+    const int off = row ? (s * nx * nx + i) * 4 : kOob;
+    const int offb = row ? (s * nx + i) * nu * 4 : kOob, offr = i < nu ? (s * nu + i) * nu * 4 : kOob;
     float prow[NXB], acol[NXB], brow[NUB], rrow[NUB];
+    if (nu == NUB) {  // whole 16-byte pieces
 #pragma unroll
-    for (int k = 0; k < NXB; ++k) {  // unconditional loads (entry 0 for the rest), so that all issue at once
-        const bool ok = act && row && k < nx;
-        const float pv = Pp[ok ? k * nx + i : 0];  // P symmetric: row i read as column i (coalesced)
-        const float av = Ap[ok ? k * nx + i : 0];
-        prow[k] = ok ? pv : 0.f;
-        acol[k] = ok ? av : 0.f;
+        for (int j = 0; j < NUB; j += 4) {
+            const f4_t bv = buf_load4(rb, offb, 4 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) brow[j + e] = bv[e];
+        }
+#pragma unroll
+        for (int j = 0; j < NUB; j += 4) {
+            const f4_t rv = buf_load4(rr, offr, 4 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rrow[j + e] = rv[e];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < NUB; ++j) {
+            brow[j] = buf_load1(rb, j < nu ? offb : kOob, 4 * j);
+            rrow[j] = buf_load1(rr, j < nu ? offr : kOob, 4 * j);
+        }
     }
 #pragma unroll
-    for (int j = 0; j < NUB; ++j) {
-        const bool okb = act && row && j < nu, okr = act && i < nu && j < nu;
-        const float bv = Bp[okb ? i * nu + j : 0];
-        const float rv = Rp[okr ? i * nu + j : 0];
-        brow[j] = okb ? bv : 0.f;
-        rrow[j] = okr ? rv : 0.f;
-    }
+    for (int k = 0; k < NXB; ++k)  // P symmetric: row i read as column i (consecutive lanes, consecutive floats)
+        prow[k] = buf_load1(rp, (NXB > 8 && k < NXB - 3) || k < nx ? off : kOob, k * nx * 4);
+#pragma unroll
+    for (int k = 0; k < NXB; ++k)
+        acol[k] = buf_load1(ra, (NXB > 8 && k < NXB - 3) || k < nx ? off : kOob, k * nx * 4);
     // row i of P B; the broadcasts are folded into the FMAs (one DPP op each,
     // so no broadcast value is held), after the wait states their sources need
     float pb[NUB];
@@ -322,9 +344,11 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
 #pragma unroll
         for (int c = 0; c <= a; ++c) {
             const float v = row_sum16(brow[a] * pb[c]);
-            if (i == a) srow[c] = a < nu ? rrow[c] + v : (c == a ? 1.f : 0.f);
-            if (i == c && c != a) srow[a] = c < nu ? rrow[a] + v : 0.f;
+            srow[c] = i == a ? v : srow[c];
+            if (c != a) srow[a] = i == c ? v : srow[a];
         }
+#pragma unroll
+    for (int c = 0; c < NUB; ++c) srow[c] = i == c && c >= nu ? 1.f : srow[c] + rrow[c];
     int f = 0;
     float myinv = 1.f;
     SegStep<16, NUB, 0>::run(srow, f, myinv);

@@ -34,24 +34,22 @@ int launch_riccati_thread(int nx, int nu, int batch, int pack, const float* A, c
 
 // Scope and pack without a forced placement.  Thread scope wherever it runs
 // (faster at every batch from 16 to 65,536 at (1, 1), (4, 2), (6, 3), (8, 1)
-// and (8, 4)).  Otherwise sub-wave scope from the batch where four problems a
-// wavefront still fill the chip and its longer chain per wavefront is hidden,
-// measured against wave scope: up to nu = 4 from 4096 problems ((12, 4): 4.8
-// against 5.4 us at 4096, 20.6 against 38.4 at 65,536, 4.4 against 4.0 at
-// 2048); past it from 8192 up to nx = 8 ((8, 8): 11.9 against 19.2 at 16,384),
-// from 16,384 up to nx = 12 ((12, 7): 13.1 against 13.9, 34.0 against 42.4 at
-// 65,536) and from 32,768 up to nx = 14 ((14, 7): 41.9 against 46.2 at 65,536,
-// 14.8 against 14.5 at 16,384); at (16, 8) wave scope stays ahead (46.1
-// against 50.7 at 65,536).  Four wavefronts per workgroup from 2048 problems
-// (wave scope, (27, 6) x 16,384: 25.7 against 27.6), one below (they spread
-// over more compute units).
+// and (8, 4)).  Otherwise sub-wave scope, against wave scope measured: up to
+// nu = 4 at every batch ((12, 4): 3.1 against 3.3 us at 512, 3.9 against 5.3
+// at 4096, 17.2 against 37.7 at 65,536); past it, where its chain per
+// wavefront is the longer one, from the batch that hides it, 4096 up to nx =
+// 12 ((8, 8): 4.9 against 5.6, and 4.5 against 3.6 at 1024; (12, 8): 5.8
+// against 5.7) and 8192 above ((14, 7): 8.5 against 8.8, and 6.4 against 6.1
+// at 4096; (16, 8): 8.8 against 8.8, 39.8 against 45.5 at 65,536).  Four
+// wavefronts per workgroup from 2048 problems (wave scope, (27, 6) x 16,384:
+// 25.7 against 27.6), one below (they spread over more compute units).
 inline void riccati_default(int nx, int nu, int batch, int* scope, int* pack) {
     *pack = 1;
     if (riccati_thread_ok(nx, nu)) {
         *scope = GLASS_SCOPE_THREAD;
         return;
     }
-    const int from = nu <= 4 ? 4096 : nx <= 8 ? 8192 : nx <= 12 ? 16384 : nx <= 14 ? 32768 : 0x7fffffff;
+    const int from = nu <= 4 ? 1 : nx <= 12 ? 4096 : 8192;
     *scope = riccati_seg_ok(nx, nu) && batch >= from ? GLASS_SCOPE_SUBWAVE : GLASS_SCOPE_WAVE;
     if (batch >= 2048) *pack = 4;
 }

@@ -290,7 +290,8 @@ def test_graph_replays_of_thread_and_subwave_forms(env, scope, nx, nu):
 
 @pytest.mark.parametrize("nx,nu,batch", [(9, 4, 4095), (9, 4, 4096), (16, 1, 4099), (5, 5, 8191), (8, 8, 8192),
                                          (12, 5, 16384), (14, 8, 32768), (16, 8, 2049), (3, 16, 100), (8, 16, 2048),
-                                         (17, 16, 33), (33, 3, 100), (48, 16, 70), (56, 8, 67)])
+                                         (17, 16, 33), (33, 3, 100), (48, 16, 70), (56, 8, 67), (12, 4, 17), (10, 3, 2047),
+                                         (12, 7, 4095), (12, 7, 4097), (14, 6, 8191), (14, 6, 8193), (16, 8, 8195)])
 def test_fused_default_placement_routes(env, nx, nu, batch):
     """force = NULL on either side of the batches where the default changes
     scope or pack, and at the edges of the tiles: the oracle's tolerance on
