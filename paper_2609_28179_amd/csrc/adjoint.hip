@@ -289,14 +289,15 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
     }
 }
 
-// Columns cb .. cb + 15 of a row-major [n][nr] matrix in T layout per block row
-// (lane (q, r): row 16 k + r, columns cb + 4 q ..; zero past n and nr).
+// Columns cb .. cb + 15 of a row-major [n][nr] matrix as operands of depth 4,
+// per block row (lane (q, r), element e: row 16 k + r, column cb + 4 e + q;
+// zero past n and nr).
 template <int NBLK, bool FULL>
 GLASS_DEV void cols_load_t(f4_t (&V)[NBLK], const float* Mg, int n, int nr, int cb, int q, int r) {
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(Mg, (uint32_t)(n * nr) * 4u);
     int off[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) off[e] = cb + 4 * q + e < nr ? (r * nr + cb + 4 * q + e) * 4 : kOob;
+    for (int e = 0; e < 4; ++e) off[e] = cb + 4 * e + q < nr ? (r * nr + cb + 4 * e + q) * 4 : kOob;
 #pragma unroll
     for (int k = 0; k < NBLK; ++k)
 #pragma unroll
@@ -308,15 +309,18 @@ GLASS_DEV void cols_load_t(f4_t (&V)[NBLK], const float* Mg, int n, int nr, int 
 // Several right-hand sides, 16 columns at a time: the matrix-core solve of the
 // blocked kernels (Y_k = L_kk^{-1} (G_k - sum L_kj Y_j), then its transpose),
 // then the lower blocks D_ij = dB_i X_j^T + X_i dB_j^T as products over the
-// columns.  With dB_i and X_i in T layout (dB through an LDS transpose), they
-// are M and, read as accumulator operands, the transposes.  D_ij comes out with lane
-// (q, r) holding rows 4 q .., column r: written to LDS by element it is block
-// (i, j), as 16-byte pieces block (j, i); the diagonal block's lower entries
+// columns, two of depth 4 for each four columns there are: dB (through LDS) and
+// X are held with column 4 e + q in lane row q, element e, so that groups of
+// columns past nr are skipped.  D_ij comes out with lane (q, r) holding rows
+// 4 q .., column r: written to LDS by element it is block (i, j), as 16-byte
+// pieces block (j, i); the diagonal block's lower entries
 // go to both places, so dA is bit-symmetric.  Past 16 columns D is formed
 // after the solves, from dB read back, so that L is no longer live.
-// Bound by the wavefront's chain of diagonal-block inverses and solves at
-// 3-5 wavefronts per SIMD.  Against the row-per-lane form, 16,384 problems:
-// n = 36, nr = 3 117.7 -> 58.3 us, n = 64, nr = 8 621.6 -> 112.1.
+// Bound by the matrix cores: each 16 x 16 x 4 product holds them 32 cycles.
+// With all 16 columns multiplied whatever nr, 16,384 problems of n = 36 and 3
+// columns took 46.6 us against 39.4 (96 and 60 products per problem), n = 28
+// and 4 columns at 65,536 107 against 101; row-per-lane 117.7, and n = 64 with
+// 8 columns 621.6 against 111.1.
 template <int NBLK, bool FULL>
 __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, const float* __restrict__ L,
                                                    const float* __restrict__ X, const float* G, float* dB,
@@ -367,21 +371,31 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
     for (int cb = 0; cb < nr; cb += 16) {
         f4_t Bt[NBLK];
         if (nr <= 16) {
-            f4_t v[4] = {zero4(), zero4(), zero4(), zero4()};
 #pragma unroll
-            for (int k = 0; k < NBLK; ++k) v[k] = Y[k];
-            transpose_blocks<NBLK>(v, xs, q, r);
+            for (int k = 0; k < NBLK; ++k) *reinterpret_cast<f4_t*>(xs + k * 16 * kXS + r * kXS + 4 * q) = Y[k];
+            wave_sync();
 #pragma unroll
-            for (int k = 0; k < NBLK; ++k) Bt[k] = v[k];
+            for (int k = 0; k < NBLK; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Bt[k][e] = xs[k * 16 * kXS + (4 * e + q) * kXS + r];
         } else {
             wave_sync();  // the dB this wavefront has stored
             cols_load_t<NBLK, FULL>(Bt, Bg, n, nr, cb, q, r);
             if (cb) cols_load_t<NBLK, FULL>(Xt, Xg, n, nr, cb, q, r);
         }
 #pragma unroll
-        for (int i = 0; i < NBLK; ++i)
+        for (int e = 0; e < 4; ++e) {
+            if (cb + 4 * e < nr) {  // wave-uniform
 #pragma unroll
-            for (int j = 0; j <= i; ++j) D[BI(i, j)] = mma(Xt[i], Bt[j], mma(Bt[i], Xt[j], D[BI(i, j)]));
+                for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+                    for (int j = 0; j <= i; ++j) {
+                        f4_t& d = D[BI(i, j)];
+                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(Bt[i][e], Xt[j][e], d, 0, 0, 0);
+                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(Xt[i][e], Bt[j][e], d, 0, 0, 0);
+                    }
+            }
+        }
     }
     wave_sync();
 #pragma unroll
