@@ -321,7 +321,7 @@ GLASS_DEV void cols_load_t(f4_t (&V)[NBLK], const float* Mg, int n, int nr, int 
 // columns took 46.6 us against 39.4 (96 and 60 products per problem), n = 28
 // and 4 columns at 65,536 107 against 101; row-per-lane 117.7, and n = 64 with
 // 8 columns 621.6 against 111.1.
-template <int NBLK, bool FULL>
+template <int NBLK, bool FULL, bool THIN>
 __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, const float* __restrict__ L,
                                                    const float* __restrict__ X, const float* G, float* dB,
                                                    float* __restrict__ dA) {
@@ -335,10 +335,11 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
     const float* Gg = G + p * n * nr;
     float* Bg = dB + p * n * nr;
     f4_t Y[NBLK], Xt[NBLK];
+    float b4[NBLK], x4[NBLK];  // dB and X with up to four columns, lane (q, r): row 16 k + r, column q
     {
         f4_t T[NT], linv[NBLK];
         blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
-        rhs_load<NBLK, FULL>(Y, Gg, n, nr, 0, q, r);
+        if (!THIN) rhs_load<NBLK, FULL>(Y, Gg, n, nr, 0, q, r);
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
             float m[16];
@@ -351,7 +352,20 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
         for (int k = 1; k < NBLK; ++k)
 #pragma unroll
             for (int j = 0; j < k; ++j) T[BI(k, j)] = neg4(T[BI(k, j)]);
-        for (int cb = 0; cb < nr; cb += 16) {
+        if (THIN) {
+            const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(Xg, (uint32_t)(n * nr) * 4u);
+            const int off = q < nr ? (r * nr + q) * 4 : kOob;
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) x4[k] = buf_load1(rx, off + 16 * k * nr * 4, 0);  // in flight behind the solves
+            float y[NBLK];
+            blk_solve4<NBLK>(T, linv, y, Gg, Bg, n, nr, xs, q, r);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) xs[64 * k + 16 * (r & 3) + 4 * (r >> 2) + q] = y[k];
+            wave_sync();
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) b4[k] = xs[64 * k + 16 * q + r];
+        }
+        for (int cb = THIN ? nr : 0; cb < nr; cb += 16) {
             if (cb) rhs_load<NBLK, FULL>(Y, Gg, n, nr, cb, q, r);
 #pragma unroll
             for (int k = 0; k < NBLK; ++k) {
@@ -368,7 +382,17 @@ __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, con
     f4_t D[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) D[t] = zero4();
-    for (int cb = 0; cb < nr; cb += 16) {
+    if (THIN) {
+#pragma unroll
+        for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) {
+                f4_t& d = D[BI(i, j)];
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(b4[i], x4[j], d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(x4[i], b4[j], d, 0, 0, 0);
+            }
+    }
+    for (int cb = THIN ? nr : 0; cb < nr; cb += 16) {
         f4_t Bt[NBLK];
         if (nr <= 16) {
 #pragma unroll
@@ -529,8 +553,10 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
     if (nblk == NBLK && full == FULL) {                                                                             \
         if (r == 1)                                                                                                 \
             hipLaunchKernelGGL((adjoint_blk1<NBLK, FULL>), grid, block, lds, st, n, batch, L, X, G, dB, dA);         \
+        else if (r <= 4)                                                                                            \
+            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL, true>), grid, block, lds, st, n, r, batch, L, X, G, dB, dA); \
         else                                                                                                        \
-            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL>), grid, block, lds, st, n, r, batch, L, X, G, dB, dA);       \
+            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL, false>), grid, block, lds, st, n, r, batch, L, X, G, dB, dA); \
         return (int)hipGetLastError();                                                                              \
     }
         CASE(2, false) CASE(2, true) CASE(3, false) CASE(3, true) CASE(4, false) CASE(4, true)

@@ -11,7 +11,7 @@ namespace {
 // op: 0 POTRF, 1 POSV, 2 POTRS, 3 TRSV (trans: 0 forward, 1 backward), 4 POSV
 // with one right-hand side.
 template <int NBLK, int OP, bool FULL>
-__global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int trans, int batch, const float* Ai, float* A,
+__global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int batch, const float* Ai, float* A,
                                                 const float* Bi, float* B, int32_t* __restrict__ info) {
     extern __shared__ float lds[];
     // POTRF on whole 16 x 16 tiles above order 32 (n = 48, 64) is write-bound
@@ -26,12 +26,12 @@ __global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int trans, int 
     const int w = wave_index(), lane = threadIdx.x & 63;
     const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
     if (p >= batch) return;
-    const int nr = OP >= 3 ? 1 : nrhs;
+    const int nr = OP == 4 ? 1 : nrhs;
     constexpr int region = OP == 4 ? blk_posv1_floats(NBLK) : kBlkRegionFloats;
     const int inf = blk_one<NBLK, OP, FULL>(Ai + p * n * n, A + p * n * n, OP == 0 ? nullptr : Bi + p * n * nr,
-                                            OP == 0 ? nullptr : B + p * n * nr, n, nrhs, trans,
+                                            OP == 0 ? nullptr : B + p * n * nr, n, nrhs,
                                             lds + (size_t)w * region, lane);
-    if ((OP <= 1 || OP == 4) && info && lane == 0) info[p] = inf;
+    if (OP != 2 && OP != 6 && info && lane == 0) info[p] = inf;
 }
 
 // One right-hand side (TRSV; POTRS with nrhs = 1) on VALU, no inverses:
@@ -61,12 +61,12 @@ int launch_chol_blk(const Shape& sh, const Geometry& g, int batch, const float* 
     const bool full =
         n == 16 * nblk && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Ai)) & 15) == 0;
     const int op = sh.op == GLASS_OP_POTRF ? 0
-                   : sh.op == GLASS_OP_POSV ? (sh.nrhs == 1 ? 4 : 1)
-                   : sh.op == GLASS_OP_POTRS ? 2
+                   : sh.op == GLASS_OP_POSV ? (sh.nrhs == 1 ? 4 : sh.nrhs <= 4 ? 5 : 1)
+                   : sh.op == GLASS_OP_POTRS ? (sh.nrhs == 1 ? 3 : sh.nrhs <= 4 ? 6 : 2)
                                              : 3;
     dim3 grid((unsigned)g.grid), block(g.threads);
-    if (op == 3 || (op == 2 && sh.nrhs == 1)) {
-        const int mode = op == 2 ? 3 : sh.trans == 0 ? 1 : 2;  // 1: L y = b, 2: L^T x = b, 3: both
+    if (op == 3) {
+        const int mode = sh.op == GLASS_OP_POTRS ? 3 : sh.trans == 0 ? 1 : 2;  // 1: L y = b, 2: L^T x = b, 3: both
 #define ONE(NBLK, FULL, MODE)                                                                                   \
     if (nblk == NBLK && full == FULL && mode == MODE) {                                                         \
         hipLaunchKernelGGL((chol_blk_solve1<NBLK, FULL, (MODE & 1) != 0, (MODE & 2) != 0>), grid, block,          \
@@ -82,12 +82,12 @@ int launch_chol_blk(const Shape& sh, const Geometry& g, int batch, const float* 
     }
 #define BLK(NBLK, OP, FULL)                                                                                    \
     if (nblk == NBLK && op == OP && full == FULL) {                                                            \
-        hipLaunchKernelGGL((chol_blk<NBLK, OP, FULL>), grid, block, g.lds_bytes, st, n, sh.nrhs, sh.trans, batch, \
-                           Ai, A, Bi, B, info);                                                                        \
+        hipLaunchKernelGGL((chol_blk<NBLK, OP, FULL>), grid, block, g.lds_bytes, st, n, sh.nrhs, batch, Ai, A, \
+                           Bi, B, info);                                                                       \
         return (int)hipGetLastError();                                                                         \
     }
 #define BLK_OPS(NBLK, FULL) \
-    BLK(NBLK, 0, FULL) BLK(NBLK, 1, FULL) BLK(NBLK, 2, FULL) BLK(NBLK, 3, FULL) BLK(NBLK, 4, FULL)
+    BLK(NBLK, 0, FULL) BLK(NBLK, 1, FULL) BLK(NBLK, 2, FULL) BLK(NBLK, 4, FULL) BLK(NBLK, 5, FULL) BLK(NBLK, 6, FULL)
     BLK_OPS(2, false) BLK_OPS(2, true) BLK_OPS(3, false) BLK_OPS(3, true) BLK_OPS(4, false) BLK_OPS(4, true)
 #undef BLK_OPS
 #undef BLK

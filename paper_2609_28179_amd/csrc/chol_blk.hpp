@@ -389,6 +389,16 @@ GLASS_DEV void transpose_blocks(f4_t (&v)[4], float* xs, int q, int r) {
     wave_sync();
 }
 
+// The first nb (a constant once unrolled) of up to NB blocks.
+template <int NB>
+GLASS_DEV void transpose_first(f4_t (&v)[4], int nb, float* xs, int q, int r) {
+    if (nb == NB) {
+        transpose_blocks<NB>(v, xs, q, r);
+    } else {
+        if constexpr (NB > 1) transpose_first<NB - 1>(v, nb, xs, q, r);
+    }
+}
+
 // Columns cb .. cb + 15 of the row-major [n][nr] right-hand sides, in
 // accumulator layout per block row (lane (q, r), element e: row 16 k + 4 q + e,
 // column cb + r): buffer accesses at a per-lane offset plus a scalar row
@@ -448,6 +458,90 @@ struct BwdBlk<NBLK, -1> {
     static GLASS_DEV void run(const f4_t (&)[NBLK * (NBLK + 1) / 2], const f4_t (&)[NBLK], f4_t (&)[NBLK], float*,
                               int, int) {}
 };
+
+// ------------------------------------------------- up to four columns at a time
+// A 16 x 16 x 16 product holds the matrix cores 128 cycles however few columns
+// X has.  With at most four, the sixteen 4 x 4 x 1 products of one
+// v_mfma_f32_4x4x1 do the work of a 16 x 16 x 4 in a quarter of the time: block
+// (q, i) multiplies rows 4 i .. 4 i + 3 and column 4 q + c of M by row 4 q + c
+// of X, so that M's T layout (register c of lane (q, 4 i + a) is
+// M[4 i + a][4 q + c]) is its operand as it stands, and what is left is a sum
+// over the four lane rows q.  Two forms of a 16 x 4 block of columns:
+//   piece form    lane (q, 4 i + j): V[4 i + q][j], one register (loads,
+//                 stores and what sum_pieces leaves)
+//   operand form  lane (q, 4 i + j), register c: V[4 q + c][j], for every i
+
+GLASS_DEV f4_t mma4(const f4_t& m, const f4_t& x, f4_t c) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_4x4x1f32(m[s], x[s], c, 0, 0, 0);
+    return c;
+}
+
+// Sum over the lane rows of products with register e, lane (q, 4 i + j)
+// holding row 4 i + e, column j: row e of the lanes receives register e's sum,
+// the piece form.  The leading wait covers the product's last write.
+GLASS_DEV float sum_pieces(f4_t d) {
+    float d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3];
+    asm volatile(
+        "s_nop 7\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\t"
+        "v_add_f32 %0, %0, %2\n\tv_add_f32 %1, %1, %3\n\ts_nop 1\n\t"
+        "v_permlane16_swap_b32 %0, %1\n\tv_add_f32 %0, %0, %1"
+        : "+v"(d0), "+v"(d1), "+v"(d2), "+v"(d3));
+    return d0;
+}
+
+// Piece form to operand form through 64 floats of LDS.
+GLASS_DEV f4_t piece_operand(float v, float* xs, int q, int r) {
+    xs[16 * (r & 3) + 4 * (r >> 2) + q] = v;
+    wave_sync();
+    const f4_t o = *reinterpret_cast<const f4_t*>(xs + 16 * (r & 3) + 4 * q);
+    wave_sync();
+    return o;
+}
+
+// The row-major [n][nr] right-hand sides, nr <= 4, in piece form (zero past n
+// and nr): byte offset of block row k.
+GLASS_DEV int piece_offset(int nr, int k, int q, int r) {
+    return (r & 3) < nr ? ((16 * k + 4 * (r >> 2) + q) * nr + (r & 3)) * 4 : kOob;
+}
+
+// L y = b, then L^T x = y, x stored and returned in piece form; nT: L in T layout with its off-diagonal blocks negated.
+template <int NBLK>
+GLASS_DEV void blk_solve4(const f4_t (&nT)[NBLK * (NBLK + 1) / 2], const f4_t (&linv)[NBLK], float (&y)[NBLK],
+                          const float* Bi, float* Bg, int n, int nr, float* xs, int q, int r) {
+    const __amdgpu_buffer_rsrc_t ri = buffer_rsrc(Bi, (uint32_t)(n * nr) * 4u);
+    const __amdgpu_buffer_rsrc_t ro = buffer_rsrc(Bg, (uint32_t)(n * nr) * 4u);
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) y[k] = buf_load1(ri, piece_offset(nr, k, q, r), 0);
+    f4_t o[NBLK];
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) {
+        f4_t acc = zero4();
+#pragma unroll
+        for (int j = 0; j < k; ++j) acc = mma4(nT[BI(k, j)], o[j], acc);
+        if (k) y[k] += sum_pieces(acc);
+        y[k] = sum_pieces(mma4(linv[k], piece_operand(y[k], xs, q, r), zero4()));
+        if (k + 1 < NBLK) o[k] = piece_operand(y[k], xs, q, r);
+    }
+#pragma unroll
+    for (int k = NBLK - 1; k >= 0; --k) {
+        const int ni = NBLK - 1 - k;
+        f4_t v[4] = {zero4(), zero4(), zero4(), zero4()};
+#pragma unroll
+        for (int i = 0; i < ni; ++i) v[i] = nT[BI(k + 1 + i, k)];
+        v[ni] = linv[k];
+        transpose_first<NBLK>(v, ni + 1, xs, q, r);
+        f4_t acc = zero4();
+#pragma unroll
+        for (int i = 0; i < ni; ++i) acc = mma4(v[i], o[k + 1 + i], acc);
+        if (ni) y[k] += sum_pieces(acc);
+        y[k] = sum_pieces(mma4(v[ni], piece_operand(y[k], xs, q, r), zero4()));
+        if (k) o[k] = piece_operand(y[k], xs, q, r);
+    }
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[k]), ro, piece_offset(nr, k, q, r), 0, 0);
+}
 
 // --------------------------------------------- one right-hand side, no inverses
 // A single right-hand side (TRSV; POTRS with nrhs = 1) gains nothing from the
@@ -737,26 +831,26 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
     blk_x_store<NBLK, FULL>(x, bg, n, q, r);
 }
 
-// One problem: factor (POTRF, POSV) or take L as given (POTRS, TRSV), then
-// solve.  op: 0 POTRF, 1 POSV, 2 POTRS, 3 TRSV (trans: 0 forward, 1 backward),
-// 4 POSV with one right-hand side (the factorization of op 1 with VALU
-// substitutions on the factor in registers: each forward step runs inside its
-// factorization step with the block inverse's coefficients, the backward pass
-// of blk_bwd1_posv after it on the inverses the panels used; no inverse of
-// the last diagonal block and no block transposes).  Every op forms the
-// diagonal blocks' inverses with tri_inverse_l on lane-local coefficients:
+// One problem: factor (POTRF, POSV) or take L as given (POTRS), then solve.
+// op: 0 POTRF, 1 POSV, 2 POTRS, 5 and 6 these two with 2..4 right-hand sides
+// (blk_solve4), 4 POSV with one right-hand side (the factorization of op 1
+// with VALU substitutions on the factor in registers: each forward step runs
+// inside its factorization step with the block inverse's coefficients, the
+// backward pass of blk_bwd1_posv after it on the inverses the panels used; no
+// inverse of the last diagonal block and no block transposes).  Every op forms
+// the diagonal blocks' inverses with tri_inverse_l on lane-local coefficients:
 // after a factorization from the rows of the staged block row with their
-// diagonal cleared, for the solves from rows read without it.  Ai is A (L for the solves), Bi the problem's [n][nr]
-// right-hand sides (nr = 1 for TRSV and op 4); L goes to Ag and the solution to
-// Bg, which are Ai and Bi themselves for a call in place.  xs: the wavefront's
-// LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).  Returns info (0 for
-// the solves); a failed factorization leaves B untouched (out of place: copies it).
+// diagonal cleared, for the solves from rows read without it.  Ai is A (L for
+// the solves), Bi the problem's [n][nrhs] right-hand sides; L goes to Ag and
+// the solution to Bg, which are Ai and Bi themselves for a call in place.  xs:
+// the wavefront's LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).
+// Returns info (0 for the solves); a failed factorization leaves B untouched
+// (out of place: copies it).
 template <int NBLK, int OP, bool FULL>
-GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, int n, int nrhs, int trans, float* xs,
-                      int lane) {
+GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, int n, int nrhs, float* xs, int lane) {
     constexpr int NT = NBLK * (NBLK + 1) / 2;
-    constexpr bool FACTOR = OP == 0 || OP == 1 || OP == 4;
-    constexpr bool MFMA_SOLVE = OP >= 1 && OP <= 3;
+    constexpr bool FACTOR = OP != 2 && OP != 6, THIN = OP >= 5;
+    constexpr bool MFMA_SOLVE = OP != 0 && OP != 4;
     const int q = lane >> 4, r = lane & 15;
     f4_t T[NT];
     blk_load<NBLK, FULL>(T, Ai, n, q, r);
@@ -850,22 +944,23 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
     for (int k = 1; k < NBLK; ++k)
 #pragma unroll
         for (int j = 0; j < k; ++j) T[BI(k, j)] = neg4(T[BI(k, j)]);
-    const int nr = OP == 3 ? 1 : nrhs;
-    const bool fwd = OP != 3 || trans == 0, bwd = OP != 3 || trans != 0;
-    for (int cb = 0; cb < nr; cb += 16) {
+    if (THIN) {
+        float y[NBLK];
+        blk_solve4<NBLK>(T, linv, y, Bi, Bg, n, nrhs, xs, q, r);
+        return 0;
+    }
+    for (int cb = 0; cb < nrhs; cb += 16) {
         f4_t Y[NBLK];
-        rhs_load<NBLK, FULL>(Y, Bi, n, nr, cb, q, r);
-        if (fwd) {
+        rhs_load<NBLK, FULL>(Y, Bi, n, nrhs, cb, q, r);
 #pragma unroll
-            for (int k = 0; k < NBLK; ++k) {
-                f4_t s = Y[k];
+        for (int k = 0; k < NBLK; ++k) {
+            f4_t s = Y[k];
 #pragma unroll
-                for (int j = 0; j < k; ++j) s = mma(T[BI(k, j)], Y[j], s);
-                Y[k] = mma(linv[k], s, zero4());
-            }
+            for (int j = 0; j < k; ++j) s = mma(T[BI(k, j)], Y[j], s);
+            Y[k] = mma(linv[k], s, zero4());
         }
-        if (bwd) BwdBlk<NBLK, NBLK - 1>::run(T, linv, Y, xs, q, r);
-        rhs_store<NBLK, FULL>(Y, Bg, n, nr, cb, q, r);
+        BwdBlk<NBLK, NBLK - 1>::run(T, linv, Y, xs, q, r);
+        rhs_store<NBLK, FULL>(Y, Bg, n, nrhs, cb, q, r);
     }
     return 0;
 }

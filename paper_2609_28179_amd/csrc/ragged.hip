@@ -468,9 +468,9 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
     float* Bg = B + uniform_i64(offB[e]);
     float* buf = chunk[w];
     if (big) {
-        const int inf = k <= 3   ? blk_one<2, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
-                        : k <= 5 ? blk_one<3, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane)
-                                 : blk_one<4, 1, false>(Ag, Ag, Bg, Bg, n, r, 0, buf, lane);
+        const int inf = k <= 3   ? blk_one<2, 1, false>(Ag, Ag, Bg, Bg, n, r, buf, lane)
+                        : k <= 5 ? blk_one<3, 1, false>(Ag, Ag, Bg, Bg, n, r, buf, lane)
+                                 : blk_one<4, 1, false>(Ag, Ag, Bg, Bg, n, r, buf, lane);
         if (lane == 0) info[e] = inf;
         return;
     }
