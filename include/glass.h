@@ -31,7 +31,9 @@
  *     for this exact call (e.g. nrhs or a rectangular GEMM exceeds what that
  *     scope supports) the call takes the first feasible of: the tabulated
  *     scope at pack 1, sub-wave, wavefront, workgroup scope, each at pack 1
- *     (wavefront / pack 1 is feasible for every supported shape).
+ *     (wavefront / pack 1 is feasible for every supported shape).  The table
+ *     is measured with one right-hand side: POSV and POTRS with several take
+ *     wavefront scope at pack 4 where it names sub-wave at orders from 17 on.
  *     `force != NULL` runs exactly that
  *     placement (only its `scope` and `pack` fields are read) or returns
  *     GLASS_ERR_INFEASIBLE_PLACEMENT without enqueuing anything.

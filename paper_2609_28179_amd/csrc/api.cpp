@@ -69,6 +69,14 @@ glass_status_t resolve(const Shape& s, long long batch, const glass_placement_t*
     }
     int scope, pack;
     table_lookup(s.op, order, batch, &scope, &pack);
+    // The table is measured with one right-hand side, where sub-wave and wave
+    // scope are within 3 % of each other at orders 17..24; with several the
+    // sub-wave kernel substitutes each column on its row lanes, and the blocked
+    // wave kernel is ahead (POSV x 65,536: n = 24, 2 columns 90 against 106 us,
+    // 8 columns 102 against 152; n = 17, 2 columns 87 against 105).
+    if ((s.op == GLASS_OP_POSV || s.op == GLASS_OP_POTRS) && s.nrhs > 1 && s.n >= kBlkMinN &&
+        scope == GLASS_SCOPE_SUBWAVE && make_geometry(s, GLASS_SCOPE_WAVE, 4, batch, g))
+        return GLASS_OK;
     if (make_geometry(s, scope, pack, batch, g)) return GLASS_OK;
     if (pack != 1 && make_geometry(s, scope, 1, batch, g)) return GLASS_OK;
     if (make_geometry(s, GLASS_SCOPE_SUBWAVE, 1, batch, g)) return GLASS_OK;

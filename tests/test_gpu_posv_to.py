@@ -4,6 +4,8 @@ autograd forward on top of it."""
 import numpy as np
 import pytest
 
+import oracle
+from helpers import TOL, normwise
 from paper_2609_28179_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +57,37 @@ def test_autograd_forward_keeps_inputs(env):
         glass.posv_(a.contiguous().clone(), want)
         assert torch.equal(X, want)
     assert torch.equal(A, A0) and torch.equal(B, B0)
+
+
+@pytest.mark.parametrize("r", [2, 3, 4, 5])
+def test_several_columns_every_blocked_order(env, r):
+    """POTRS with few right-hand sides at every order of the blocked kernels
+    (up to four columns take the 4 x 4 x 1 products): against the oracle."""
+    glass, torch = env
+    fails = []
+    for n in range(17, 65):
+        c = inputs.make_case("potrs", n, 9, cfg=11, nrhs=r)
+        L, B = (torch.from_numpy(c[k]).to("cuda:0") for k in ("L", "B"))
+        assert glass.glass_potrs_batched(n, r, 9, L, B, ("wave", 1)) == 0
+        torch.cuda.synchronize()
+        err = normwise(B.cpu().numpy(), oracle.potrs(c["L"], c["B"])).max()
+        if not err <= TOL:
+            fails.append((n, err))
+    assert not fails, fails
+
+
+@pytest.mark.parametrize("n,r,batch", [(17, 2, 40000), (20, 4, 65536), (24, 5, 65536), (24, 1, 65536), (16, 2, 40000)])
+def test_default_placement_several_columns(env, n, r, batch):
+    """force = NULL on either side of the rule for several columns: the
+    oracle's tolerance on a sample spread over the batch, info 0 throughout."""
+    glass, torch = env
+    c = inputs.make_case("posv", n, 512, cfg=12, nrhs=r)
+    reps = -(-batch // 512)
+    A, B = (torch.from_numpy(c[k]).to("cuda:0").repeat(reps, 1, 1)[:batch].contiguous() for k in ("A", "B"))
+    info = torch.full((batch,), -7, dtype=torch.int32, device="cuda:0")
+    assert glass.glass_posv_batched(n, r, batch, A, B, info) == 0
+    torch.cuda.synchronize()
+    pick = np.unique(np.r_[0:16, batch // 2:batch // 2 + 16, batch - 16:batch])
+    _, X_ref, _ = oracle.posv(c["A"][pick % 512], c["B"][pick % 512])
+    assert normwise(B.cpu().numpy()[pick], X_ref).max() <= TOL
+    assert (info.cpu().numpy() == 0).all()
