@@ -136,8 +136,12 @@ __global__ void __launch_bounds__(256) gemv_wg(int m, int n, int batch, int pack
 // each adding its partner's copy.  Afterwards lane c of a group holds the
 // whole dot product of row RPI k + g for k = c (N = 64) or k = c / 2 (N = 32;
 // lanes c and c ^ 1 agree).  At N = 16 a row is one instruction's four lanes
-// (K = 1) and two quad exchanges sum them.  VEC: n % 4 == 0 with A and x
-// 16-byte aligned; FULL: besides, n == N (no padding, no masks).
+// (K = 1) and two quad exchanges sum them.  KL: instructions that hold rows
+// (10 and 13 of N = 64's 16 for orders up to 40 and 52).  TAIL: n % 4 != 0; FULL: n == N (no
+// padding).  Bound by the read of A.  Orders that are no multiple of 4 used
+// one 4-byte load per element under lane conditions from 42 up and the
+// LDS-staged form below: at 65,536 problems n = 17 31.4 -> 15.1 us, 27 35.8 ->
+// 31.5, 33 52.4 -> 47.7, 45 168 -> 96, 63 260 -> 183; n = 33 x 4096 7.0 -> 5.3.
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, false));
@@ -156,12 +160,12 @@ __device__ __forceinline__ void bfly_step(float (&v)[16], bool hi) {
 
 constexpr int kDppRowMirror = 0x140, kDppHalfMirror = 0x141, kDppXor3 = 0x1B, kDppXor2 = 0x4E, kDppXor1 = 0xB1;
 
-template <int N, bool VEC, bool FULL>
+template <int N, int KL, bool TAIL, bool FULL>
 __global__ void __launch_bounds__(512) gemv_wave_dpp(int n, int batch, float alpha, const float* __restrict__ A,
                                                      const float* __restrict__ x, float beta,
                                                      float* __restrict__ y) {
     static_assert(N == 16 || N == 32 || N == 64, "padded orders 16, 32 and 64");
-    static_assert(VEC || !FULL, "the unpadded form loads 16-byte pieces");
+    static_assert(!TAIL || !FULL, "whole pieces");
     if (FULL) n = N;
     constexpr int LPR = N / 4, RPI = 64 / LPR, K = N / RPI;
     const int w = wave_index(), lane = threadIdx.x & 63;
@@ -170,38 +174,29 @@ __global__ void __launch_bounds__(512) gemv_wave_dpp(int n, int batch, float alp
     const int g = lane / LPR, c = lane % LPR;
     const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(A + p * n * n, (uint32_t)(n * n * 4));
     const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(x + p * n, (uint32_t)(n * 4));
-    f4_t a[K], xv = {0.f, 0.f, 0.f, 0.f};
-    if (VEC) {
-        const bool col = FULL || 4 * c < n;
-        if (col) xv = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(rx, 16 * c, 0, 0));
+    // Any alignment: buffer loads need 4 bytes.  The piece that holds column n - 1
+    // ends there and repeats columns of its neighbour, cleared in x and in A
+    // (an infinity times that zero would not vanish).
+    const int left = FULL ? 4 : n - 4 * c, skip = left < 4 ? 4 - left : 0;
+    const int col = left <= 0 ? kOob / 4 : 4 * c - skip;
+    f4_t xv = buf_load4(rx, 4 * col, 0);
+    f4_t a[KL];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int row = RPI * k + g;
-            a[k] = f4_t{0.f, 0.f, 0.f, 0.f};
-            if (FULL || (col && row < n))
-                a[k] = __builtin_bit_cast(f4_t,
-                                          __builtin_amdgcn_raw_buffer_load_b128(ra, (row * n + 4 * c) * 4, 0, 0));
-        }
-    } else {
+    for (int k = 0; k < KL; ++k) a[k] = buf_load4(ra, ((RPI * k + g) * n + col) * 4, 0);
+    if (TAIL) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * c + e < n)
-                xv[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, (4 * c + e) * 4, 0, 0));
+        for (int e = 0; e < 3; ++e) {
+            const bool dup = e < skip;
+            xv[e] = dup ? 0.f : xv[e];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int row = RPI * k + g;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[k][e] = 0.f;
-                if (row < n && 4 * c + e < n)
-                    a[k][e] = __builtin_bit_cast(
-                        float, __builtin_amdgcn_raw_buffer_load_b32(ra, (row * n + 4 * c + e) * 4, 0, 0));
-            }
+            for (int k = 0; k < KL; ++k) a[k][e] = dup ? 0.f : a[k][e];
         }
     }
     float v[16];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
+    for (int k = KL; k < K; ++k) v[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < KL; ++k) {
         float t = a[k][0] * xv[0];
         t = fmaf(a[k][1], xv[1], t);
         t = fmaf(a[k][2], xv[2], t);
@@ -343,14 +338,16 @@ int launch_gemv(const Shape& sh, const Geometry& g, int batch, float alpha, cons
         default: return (int)hipErrorInvalidValue;
         }
     } else if (g.scope == GLASS_SCOPE_WAVE && gemv_uses_dpp(sh)) {
-        const bool vec = sh.n % 4 == 0 && (uintptr_t)A % 16 == 0 && (uintptr_t)x % 16 == 0;
         const int pad = sh.n <= 16 ? 16 : sh.n <= 32 ? 32 : 64;
-        const bool full = vec && sh.n == pad;
-#define X(N, V, F)                                                                                            \
-    if (pad == N && vec == V && full == F)                                                                    \
-        hipLaunchKernelGGL((gemv_wave_dpp<N, V, F>), grid, block, 0, st, sh.n, batch, alpha, A, x, beta, y);
-        X(16, true, true) X(16, true, false) X(16, false, false) X(32, true, true) X(32, true, false)
-        X(32, false, false) X(64, true, true) X(64, true, false) X(64, false, false)
+        const bool full = sh.n == pad, tail = sh.n % 4 != 0;
+        const int kl = pad < 64 ? pad * pad / 256 : sh.n <= 40 ? 10 : sh.n <= 52 ? 13 : 16;
+#define X(N, KL, T, F)                                                                                            \
+    if (pad == N && kl == KL && tail == T && full == F)                                                           \
+        hipLaunchKernelGGL((gemv_wave_dpp<N, KL, T, F>), grid, block, 0, st, sh.n, batch, alpha, A, x, beta, y);
+        X(16, 1, false, true) X(16, 1, false, false)
+        X(32, 4, false, true) X(32, 4, false, false) X(32, 4, true, false)
+        X(64, 10, false, false) X(64, 10, true, false) X(64, 13, false, false) X(64, 13, true, false)
+        X(64, 16, false, true) X(64, 16, false, false) X(64, 16, true, false)
 #undef X
     } else if (g.scope == GLASS_SCOPE_WAVE) {
         const int mn = sh.m * sh.n;

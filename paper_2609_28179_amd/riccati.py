@@ -7,10 +7,9 @@ granularity one more measured placement.  Here:
 
   fused    one launch of glass_riccati_gain_batched, one problem per
            wavefront, every intermediate in VGPRs / LDS, pack P in
-           {1, 2, 4, 8}: for nx >= 9 every product runs on the matrix
-           cores in 16 x 16 tiles and S = R + B^T P B is factored as one
-           diagonal tile; below, P and B are staged in LDS and the
-           products read them as broadcasts;
+           {1, 2, 4, 8}: every product runs on the matrix cores in
+           16 x 16 tiles and S = R + B^T P B is factored as one diagonal
+           tile;
   fused_subwave  the same launch at sub-wave scope (nx <= 16, nu <= 8):
            four problems per wavefront, one per 16-lane row, every
            cross-lane move a DPP exchange inside the row;

@@ -278,3 +278,33 @@ def test_gemv_few_wide_rows(env, m, n, shift):
             mag = 1.5 * np.einsum("bij,bj->bi", np.abs(A.astype(np.float64)), np.abs(x)) + beta * np.abs(y0)
             assert (np.nan_to_num(np.abs(got - ref)) <= (n + 4) * 2.0 ** -24 * np.nan_to_num(mag, nan=np.inf)).all()
             assert all(guards_intact(b[0], pad) for b in bufs)
+
+
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_gemv_square_wave_orders(env, shift):
+    """Square GEMV at wave scope, every order of the register form (16-byte
+    pieces that end at the last column), operands 0..3 floats off 16-byte
+    alignment: the rounding bound (n + 4) u sum |a x| per element; an infinity
+    in the last column stays one where x is not zero."""
+    glass, torch = env
+    fails = []
+    for n in range(16, 65):
+        rng = np.random.default_rng(700 + n)
+        A, x = inputs.uniform(rng, (5, n, n)), inputs.uniform(rng, (5, n))
+        A[2, 1, n - 1] = np.inf
+        x[2, n - 1] = 0.5
+        buf = torch.zeros(A.size + x.size + 8, device="cuda:0")
+        Ad, xd = buf[shift:shift + A.size].view(A.shape), buf[A.size + 4:A.size + 4 + x.size].view(x.shape)
+        Ad.copy_(torch.from_numpy(A))
+        xd.copy_(torch.from_numpy(x))
+        y = torch.full((5, n), float("nan"), device="cuda:0")
+        assert glass.glass_gemv_batched(n, n, 5, 1.0, Ad, xd, 0.0, y, ("wave", 1)) == 0
+        torch.cuda.synchronize()
+        got = y.cpu().numpy().astype(np.float64)
+        A64, x64 = A.astype(np.float64), x.astype(np.float64)
+        ref = np.einsum("bij,bj->bi", A64, x64)
+        bound = (n + 4) * 2.0 ** -24 * np.einsum("bij,bj->bi", np.abs(A64), np.abs(x64))
+        fin = np.isfinite(ref)
+        if fin.sum() != 5 * n - 1 or got[2, 1] != np.inf or not (np.abs(got - ref)[fin] <= bound[fin]).all():
+            fails.append(n)
+    assert not fails, fails
