@@ -93,13 +93,14 @@ __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, c
     // the first block column of A, in flight behind the factorization of S
     f4_t Af[2][NXB];
     tile_col_elems<NXB>(Af[0], ra, nx, nx, r, q);
-    // S = R + B^T P B in accumulator layout, identity on the padded diagonal
+    // S = R + B^T P B in accumulator layout, its padded rows and columns set to
+    // the identity after the products (an infinity in P B times a padded zero of
+    // B is no zero)
     f4_t S = Rf[0];
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (4 * q + e == r && r >= nu) S[e] = 1.f;
-#pragma unroll
     for (int i = 0; i < NXB; ++i) S = mma(Bb[i], PB[i], S);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) S[e] = 4 * q + e < nu && r < nu ? S[e] : 4 * q + e == r ? 1.f : 0.f;
     // rows of S to the lanes: lane (q, r) holds row r of S after the exchange
 #pragma unroll
     for (int e = 0; e < 4; ++e) xs[(4 * q + e) * kXS + r] = S[e];
@@ -139,6 +140,8 @@ __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, c
         f4_t t = zero4();
 #pragma unroll
         for (int i = 0; i < NXB; ++i) t = mma(PB[i], Af[j & 1][i], t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = 4 * q + e < nu ? t[e] : 0.f;  // the padded rows, likewise
         const f4_t kj = mma(lt[0], mma(linv, t, zero4()), zero4());  // L^{-T} (L^{-1} T_j)
         const int col = 16 * j + r;
 #pragma unroll
@@ -348,7 +351,11 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
             if (c != a) srow[a] = i == c ? v : srow[a];
         }
 #pragma unroll
-    for (int c = 0; c < NUB; ++c) srow[c] = i == c && c >= nu ? 1.f : srow[c] + rrow[c];
+    for (int c = 0; c < NUB; ++c) srow[c] += rrow[c];
+    if (nu != NUB) {  // wave-uniform; set, as an infinity in P B times a padded zero of B is no zero
+#pragma unroll
+        for (int c = 0; c < NUB; ++c) srow[c] = i < nu && c < nu ? srow[c] : i == c ? 1.f : 0.f;
+    }
     int f = 0;
     float myinv = 1.f;
     SegStep<16, NUB, 0>::run(srow, f, myinv);
@@ -366,6 +373,10 @@ __global__ void __launch_bounds__(512) riccati_seg(int nx, int nu, int batch, co
 #pragma unroll
         for (int a = 0; a < NUB; ++a) fmac_bcast<k>(t[a], pb[a], acol[k]);
     });
+    if (nu != NUB) {
+#pragma unroll
+        for (int a = 0; a < NUB; ++a) t[a] = a < nu ? t[a] : 0.f;  // the padded rows of T, likewise
+    }
     // L's strictly lower entries and 1 / L_aa as broadcasts, then L L^T k = t
     float lo[NUB][NUB], inv[NUB];
     static_for<0, NUB>([&](auto ac) {

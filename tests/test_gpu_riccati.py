@@ -308,3 +308,38 @@ def test_fused_default_placement_routes(env, nx, nu, batch):
     ref, _ = oracle.riccati_gain(c["A"][pick], c["B"][pick], c["P"][pick], c["R"][pick])
     assert normwise(K.cpu().numpy()[pick], ref).max() <= TOL
     assert not np.isnan(K.cpu().numpy()).any() and (info.cpu().numpy() == 0).all()
+
+
+@pytest.mark.parametrize("nx,nu", [(6, 1), (7, 3), (8, 5), (8, 7), (12, 1), (9, 3), (15, 5), (16, 7), (20, 3), (33, 9), (40, 13)])
+def test_info_stays_within_the_inputs(env, nx, nu):
+    """An infinite P, and finite operands whose P B overflows FP32: info is the
+    oracle's (0 or a pivot of S, never one of the padding past nu), and the
+    other problems of the wavefront keep their K."""
+    glass, torch = env
+    batch = 11
+    c = inputs.make_riccati(batch, nx, nu, seed=31)
+    c["P"][2, 0, 0] = np.inf
+    c["P"][7] = np.inf
+    for p in (5, 8):
+        c["P"][p] = 2.0 * np.eye(nx)
+        c["B"][p] = 0.0
+        c["B"][p, :nu - 1, :nu - 1] = np.eye(nu - 1)
+        c["B"][p, nx - 1, nu - 1] = 3e38  # P B = 6e38: the one entry of its row and column
+    K_ref, info_ref = oracle.riccati_gain(*(c[k] for k in ("A", "B", "P", "R")))
+    good = [i for i in range(batch) if i not in (2, 5, 7, 8)]
+    d = {k: dev(torch, v) for k, v in c.items()}
+    ran = 0
+    for scope in ("thread", "wave", "subwave"):
+        if glass.glass_riccati_placement_feasible(nx, nu, glass.SCOPES[scope], 1) != 1:
+            continue
+        print(f"riccati info with infinities nx={nx} nu={nu} {scope}", flush=True)
+        K = torch.full((batch, nu, nx), float("nan"), device="cuda:0")
+        info = torch.full((batch,), -7, dtype=torch.int32, device="cuda:0")
+        assert glass.glass_riccati_gain_batched(nx, nu, batch, d["A"], d["B"], d["P"], d["R"], K, info, (scope, 1)) == 0
+        torch.cuda.synchronize()
+        h = info.cpu().numpy()
+        assert ((0 <= h) & (h <= nu)).all(), (scope, h)
+        assert np.array_equal(h, info_ref), (scope, h, info_ref)
+        assert normwise(K.cpu().numpy()[good], K_ref[good]).max() <= TOL
+        ran += 1
+    assert ran
