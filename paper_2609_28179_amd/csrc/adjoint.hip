@@ -261,10 +261,8 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
         float a[16];
-        const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
-        blk_fwd_step<NBLK>(T, k, a, myinv, b, pend, q, blk_live<NBLK, FULL>(n, k));
+        const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r));
+        blk_fwd_rows<NBLK, FULL>(T, k, a, myinv, b, pend, q, blk_live<NBLK, FULL>(n, k));
     }
     blk_bwd1<NBLK, FULL>(T, b, xs, n, q, r);
     blk_x_store<NBLK, FULL>(b, dB + p * n, n, q, r);

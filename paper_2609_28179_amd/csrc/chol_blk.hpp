@@ -607,6 +607,63 @@ GLASS_DEV void diag_bwd(float& s, const float (&m)[16], int live) {
     DiagSub<3, -1>::run(s, m);
 }
 
+// The substitutions on unscaled coefficients (row r of L forward, column r
+// backward, the diagonal entry cleared): in step K unknown K is s_K / L_KK,
+// kept in lane K of y, and its products leave s.  The lanes whose unknown is
+// already final meet zero coefficients, whose product with an infinity or a NaN
+// is no zero: it lands in their s, and y keeps every unknown that does not
+// depend on such an entry.  The select fills one of the two wait states
+// between the product and its DPP read.  Orders 17 .. 31 substitute so; from
+// 32 on the scaled coefficients stay, whose chain is an instruction a step
+// shorter (POTRS n = 64 x 256 4.2 us against 4.4).
+template <int NBLK, bool FULL>
+constexpr bool kSubstKeep = NBLK == 2 && !FULL;
+
+template <int K>
+GLASS_DEV void keep_and_fmac(float& s, float& y, float t, float a) {
+    asm volatile("v_cndmask_b32_e64 %1, %1, %2, %4\n\ts_nop 0\n\t"
+                 "v_fmac_f32_dpp %0, %2, -%3 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+                 : "+v"(s), "+v"(y)
+                 : "v"(t), "v"(a), "s"(seg_mask<16>() << K), "n"(K));
+}
+
+template <int K, int END>  // steps K, K + 1 .. END - 1, or K, K - 1 .. END + 1
+struct DiagKeep {
+    static GLASS_DEV void run(float& s, float& y, const float (&a)[16], float myinv) {
+        keep_and_fmac<K>(s, y, s * myinv, a[K]);
+        DiagKeep<K + (K < END ? 1 : -1), END>::run(s, y, a, myinv);
+    }
+};
+template <int END>
+struct DiagKeep<END, END> {
+    static GLASS_DEV void run(float&, float&, const float (&)[16], float) {}
+};
+
+GLASS_DEV float diag_keep_fwd(float s, const float (&a)[16], float myinv, int live) {
+    float y = 0.f;
+    DiagKeep<0, 4>::run(s, y, a, myinv);
+    if (live > 4) {
+        DiagKeep<4, 8>::run(s, y, a, myinv);
+        if (live > 8) {
+            DiagKeep<8, 12>::run(s, y, a, myinv);
+            if (live > 12) DiagKeep<12, 16>::run(s, y, a, myinv);
+        }
+    }
+    return y;
+}
+GLASS_DEV float diag_keep_bwd(float s, const float (&a)[16], float myinv, int live) {
+    float y = 0.f;
+    if (live > 4) {
+        if (live > 8) {
+            if (live > 12) DiagKeep<15, 11>::run(s, y, a, myinv);
+            DiagKeep<11, 7>::run(s, y, a, myinv);
+        }
+        DiagKeep<7, 3>::run(s, y, a, myinv);
+    }
+    DiagKeep<3, -1>::run(s, y, a, myinv);
+    return y;
+}
+
 // v summed over the four 16-lane rows (lanes r, r + 16, r + 32, r + 48), in
 // every lane: each v_permlane*_swap exchanges half of v with half of a copy,
 // and the VALU write of the copy gets its two wait states before the swap.
@@ -703,18 +760,22 @@ GLASS_DEV void blk_x_store(const float (&x)[NBLK], float* bg, int n, int q, int 
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[k]), rs, q == 0 ? (16 * k + r) * 4 : kOob, 0, 0);
 }
 
-// Forward step k: block k of y from its pending sum p[k], the diagonal
-// block's lane-local coefficients m_K = -L_rK / L_rr and 1 / L_rr (the
-// right-hand side is scaled by it first), then its contributions L_ik y_k to
-// the pending sums of the later blocks (right-looking, p[i] split over the
-// rows q).
-template <int NBLK>
+// Forward step k: block k of y from its pending sum p[k] by the diagonal
+// block's rows, then its contributions L_ik y_k to the pending sums of the
+// later blocks (right-looking, p[i] split over the rows q).  KEEP: m holds
+// L_rK; otherwise -L_rK / L_rr (op 4 of blk_one, whose block inverses use
+// them), and the right-hand side is scaled by 1 / L_rr first.
+template <int NBLK, bool KEEP>
 GLASS_DEV void blk_fwd_step(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&m)[16], float myinv,
                             float (&x)[NBLK], float (&p)[NBLK], int q, int live) {
     float s = k > 0 ? x[k] - sum_rows4(p[k]) : x[k];
-    s *= myinv;
-    diag_fwd(s, m, live);
-    x[k] = s;
+    if (KEEP) {
+        x[k] = diag_keep_fwd(s, m, myinv, live);
+    } else {
+        s *= myinv;
+        diag_fwd(s, m, live);
+        x[k] = s;
+    }
     if (k + 1 < NBLK) {
         float xc[4];
         r_to_c(x[k], xc, q);
@@ -723,6 +784,18 @@ GLASS_DEV void blk_fwd_step(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const
 #pragma unroll
             for (int c = 0; c < 4; ++c) p[i] = fmaf(T[BI(i, k)][c], xc[c], p[i]);
     }
+}
+
+// The same on the diagonal block's rows a as they are (diagonal entry cleared).
+template <int NBLK, bool FULL>
+GLASS_DEV void blk_fwd_rows(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, float (&a)[16], float myinv,
+                            float (&x)[NBLK], float (&p)[NBLK], int q, int live) {
+    if (!kSubstKeep<NBLK, FULL>) {
+        const float nmy = -myinv;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
+    }
+    blk_fwd_step<NBLK, kSubstKeep<NBLK, FULL>>(T, k, a, myinv, x, p, q, live);
 }
 
 // L^T x = y, bottom block first (left-looking over the columns: z[j] collects
@@ -743,11 +816,15 @@ GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK]
         }
         float col[16];
         const float myinv = recip(diag_cols(T[BI(k, k)], col, xs, q, r)), nmy = -myinv;
+        if (kSubstKeep<NBLK, FULL>) {
+            x[k] = diag_keep_bwd(s, col, myinv, blk_live<NBLK, FULL>(n, k));
+        } else {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) col[j] *= nmy;  // -L_jr / L_rr
-        s *= myinv;
-        diag_bwd(s, col, blk_live<NBLK, FULL>(n, k));
-        x[k] = s;
+            for (int j = 0; j < 16; ++j) col[j] *= nmy;  // -L_jr / L_rr
+            s *= myinv;
+            diag_bwd(s, col, blk_live<NBLK, FULL>(n, k));
+            x[k] = s;
+        }
 #pragma unroll
         for (int j = 0; j < k; ++j)
 #pragma unroll
@@ -821,10 +898,8 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
             float a[16];
-            const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
-            blk_fwd_step<NBLK>(T, k, a, myinv, x, p, q, blk_live<NBLK, FULL>(n, k));
+            const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r));
+            blk_fwd_rows<NBLK, FULL>(T, k, a, myinv, x, p, q, blk_live<NBLK, FULL>(n, k));
         }
     }
     if (BWD) blk_bwd1<NBLK, FULL>(T, x, xs, n, q, r);
@@ -925,7 +1000,7 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
             }
             // op 4: forward step k (needs this step's panel L_ik), on VALU
             // while the matrix cores run the trailing products
-            if (OP == 4) blk_fwd_step<NBLK>(T, k, m, myinv, x1, p1, q, live);
+            if (OP == 4) blk_fwd_step<NBLK, false>(T, k, m, myinv, x1, p1, q, live);
         }
     }
     if (FACTOR && OP != 0 && inf != 0 && Bi != Bg) {  // a failed factorization passes B through
