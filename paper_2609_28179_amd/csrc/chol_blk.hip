@@ -10,7 +10,7 @@ namespace {
 
 // op: 0 POTRF, 1 POSV, 2 POTRS, 3 TRSV (trans: 0 forward, 1 backward), 4 POSV
 // with one right-hand side.
-template <int NBLK, int OP, bool FULL>
+template <int NBLK, int OP, bool FULL, bool SUB>
 __global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int batch, const float* Ai, float* A,
                                                 const float* Bi, float* B, int32_t* __restrict__ info) {
     extern __shared__ float lds[];
@@ -28,7 +28,7 @@ __global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int batch, cons
     if (p >= batch) return;
     const int nr = OP == 4 ? 1 : nrhs;
     constexpr int region = OP == 4 ? blk_posv1_floats(NBLK) : kBlkRegionFloats;
-    const int inf = blk_one<NBLK, OP, FULL>(Ai + p * n * n, A + p * n * n, OP == 0 ? nullptr : Bi + p * n * nr,
+    const int inf = blk_one<NBLK, OP, FULL, SUB>(Ai + p * n * n, A + p * n * n, OP == 0 ? nullptr : Bi + p * n * nr,
                                             OP == 0 ? nullptr : B + p * n * nr, n, nrhs,
                                             lds + (size_t)w * region, lane);
     if (OP != 2 && OP != 6 && info && lane == 0) info[p] = inf;
@@ -80,15 +80,18 @@ int launch_chol_blk(const Shape& sh, const Geometry& g, int batch, const float* 
 #undef ONE
         return (int)hipErrorInvalidValue;
     }
-#define BLK(NBLK, OP, FULL)                                                                                    \
-    if (nblk == NBLK && op == OP && full == FULL) {                                                            \
-        hipLaunchKernelGGL((chol_blk<NBLK, OP, FULL>), grid, block, g.lds_bytes, st, n, sh.nrhs, batch, Ai, A, \
+#define BLK(NBLK, OP, FULL, SUB)                                                                               \
+    if (nblk == NBLK && op == OP && full == FULL && sub == SUB) {                                              \
+        hipLaunchKernelGGL((chol_blk<NBLK, OP, FULL, SUB>), grid, block, g.lds_bytes, st, n, sh.nrhs, batch, Ai, A, \
                            Bi, B, info);                                                                       \
         return (int)hipGetLastError();                                                                         \
     }
-#define BLK_OPS(NBLK, FULL) \
-    BLK(NBLK, 0, FULL) BLK(NBLK, 1, FULL) BLK(NBLK, 2, FULL) BLK(NBLK, 4, FULL) BLK(NBLK, 5, FULL) BLK(NBLK, 6, FULL)
-    BLK_OPS(2, false) BLK_OPS(2, true) BLK_OPS(3, false) BLK_OPS(3, true) BLK_OPS(4, false) BLK_OPS(4, true)
+#define BLK_OPS(NBLK, FULL, SUB)                                                                               \
+    BLK(NBLK, 0, FULL, SUB) BLK(NBLK, 1, FULL, SUB) BLK(NBLK, 2, FULL, SUB) BLK(NBLK, 4, FULL, SUB)            \
+    BLK(NBLK, 5, FULL, SUB) BLK(NBLK, 6, FULL, SUB)
+    const bool sub = n <= kBlkSubstMaxN;
+    BLK_OPS(2, false, true) BLK_OPS(2, false, false) BLK_OPS(2, true, false) BLK_OPS(3, false, false)
+    BLK_OPS(3, true, false) BLK_OPS(4, false, false) BLK_OPS(4, true, false)
 #undef BLK_OPS
 #undef BLK
     return (int)hipErrorInvalidValue;

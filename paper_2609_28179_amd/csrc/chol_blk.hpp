@@ -256,6 +256,97 @@ GLASS_DEV void diag_factor(f4_t& t, int& f, float& myinv, int q, int r, int live
     for (int c = 0; c < 4; ++c) t[c] = 4 * q + c <= r ? t[c] : 0.f;
 }
 
+// panel_cols with the same columns of the block u below the diagonal one (rows
+// in the same lanes, T layout): each is scaled by its pivot's 1 / sqrt and
+// taken off u's later columns against the diagonal block's rows.  Most of
+// u's instructions stand where panel_cols waits.
+template <int S>
+GLASS_DEV void panel_cols_rows(f4_t& t, f4_t& u, float inv, float& myinv) {
+    constexpr int J = 4 * S;
+    constexpr unsigned long long m = seg_mask<16>() << J;
+    float d;
+    asm volatile(
+        "s_nop 0\n\t"
+        "v_mul_f32_dpp %0, %0, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_mul_f32_dpp %4, %4, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %8, %8, %9, %11\n\t"
+        "v_fmac_f32_dpp %1, %0, -%0 row_newbcast:%16 row_mask:%15 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %0, -%4 row_newbcast:%16 row_mask:%15 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %0, -%0 row_newbcast:%17 row_mask:%15 bank_mask:0xf\n\t"
+        "v_readlane_b32 %10, %1, %19\n\t"
+        "v_fmac_f32_dpp %6, %0, -%4 row_newbcast:%17 row_mask:%15 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %0, -%0 row_newbcast:%18 row_mask:%15 bank_mask:0xf\n\t"
+        "v_rsq_f32_e32 %9, %10\n\t"
+        "v_fmac_f32_dpp %7, %0, -%4 row_newbcast:%18 row_mask:%15 bank_mask:0xf\n\t"
+        "v_mul_f32_dpp %1, %1, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_mul_f32_dpp %5, %5, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %8, %8, %9, %12\n\t"
+        "v_fmac_f32_dpp %2, %1, -%1 row_newbcast:%17 row_mask:%15 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %1, -%5 row_newbcast:%17 row_mask:%15 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %1, -%1 row_newbcast:%18 row_mask:%15 bank_mask:0xf\n\t"
+        "v_readlane_b32 %10, %2, %20\n\t"
+        "v_fmac_f32_dpp %7, %1, -%5 row_newbcast:%18 row_mask:%15 bank_mask:0xf\n\t"
+        "s_nop 0\n\tv_rsq_f32_e32 %9, %10\n\ts_nop 0\n\t"
+        "v_mul_f32_dpp %2, %2, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_mul_f32_dpp %6, %6, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %8, %8, %9, %13\n\t"
+        "v_fmac_f32_dpp %3, %2, -%2 row_newbcast:%18 row_mask:%15 bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %2, -%6 row_newbcast:%18 row_mask:%15 bank_mask:0xf\n\t"
+        "v_readlane_b32 %10, %3, %21\n\t"
+        "s_nop 1\n\tv_rsq_f32_e32 %9, %10\n\ts_nop 0\n\t"
+        "v_mul_f32_dpp %3, %3, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_mul_f32_dpp %7, %7, %9 quad_perm:[0,1,2,3] row_mask:%15 bank_mask:0xf\n\t"
+        "v_cndmask_b32_e64 %8, %8, %9, %14"
+        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]), "+v"(myinv),
+          "+v"(inv), "=&s"(d)
+        : "s"(m), "s"(m << 1), "s"(m << 2), "s"(m << 3), "n"(1 << S), "n"(J + 1), "n"(J + 2), "n"(J + 3),
+          "n"(16 * S + J + 1), "n"(16 * S + J + 2), "n"(16 * S + J + 3));
+}
+
+// panel_operand of t and of u.
+template <int S>
+GLASS_DEV void panel_operands(const f4_t& t, const f4_t& u, float& p, float& pu) {
+    float t0 = t[0], t1 = t[1], t2 = t[2], t3 = t[3], u0 = u[0], u1 = u[1], u2 = u[2], u3 = u[3];
+    asm volatile(
+        "s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3\n\t"
+        "v_permlane16_swap_b32 %4, %5\n\tv_permlane16_swap_b32 %6, %7\n\t"
+        ".if %8\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 0\n\tv_permlane32_swap_b32 %5, %7\n\t"
+        ".else\n\tv_permlane32_swap_b32 %0, %2\n\ts_nop 0\n\tv_permlane32_swap_b32 %4, %6\n\t.endif\n\ts_nop 1"
+        : "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3), "+v"(u0), "+v"(u1), "+v"(u2), "+v"(u3)
+        : "n"(S & 1));
+    p = S == 0 ? t0 : S == 1 ? t1 : t2;
+    pu = S == 0 ? u0 : S == 1 ? u1 : u2;
+}
+
+template <int S>
+GLASS_DEV void panel_steps_rows(f4_t& t, f4_t& u, float& myinv, int q) {
+    panel_cols_rows<S>(t, u, rsq(readlane(t[0], 20 * S)), myinv);
+    if constexpr (S < 3) {
+        float p, pu;
+        panel_operands<S>(t, u, p, pu);
+        const f4_t d = __builtin_amdgcn_mfma_f32_16x16x4f32(-p, p, t, 0, 0, 0);
+        const f4_t e = __builtin_amdgcn_mfma_f32_16x16x4f32(-p, pu, u, 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            t[c] = q > S ? d[c] : t[c];
+            u[c] = q > S ? e[c] : u[c];
+        }
+        panel_steps_rows<S + 1>(t, u, myinv, q);
+    }
+}
+
+// diag_factor of a whole diagonal block t and, column by column with it, the
+// block u below it: u <- u t^{-T}, by substitution and not by t's inverse.
+// With the inverse, POSV n = 22 took 4 % less (n = 22 x 16,384 27.3 us against
+// 28.4), and its factor was off by 1.3 to 1.6 times as much at condition 1e4,
+// 1.7 to 2.2 times at 1e6.
+GLASS_DEV void diag_factor_rows(f4_t& t, f4_t& u, int& f, float& myinv, int q, int r) {
+    panel_steps_rows<0>(t, u, myinv, q);
+    f = first_nonfinite<16>(myinv);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t[c] = 4 * q + c <= r ? t[c] : 0.f;
+}
+
 // X = L^{-1} of a 16 x 16 lower diagonal block, in T layout: lane (q, r)
 // returns row r, columns 4 q .. 4 q + 3.  Forward substitution against the
 // identity with the lane's own coefficients m_K = -L_rK / L_rr (zero in lane
@@ -843,8 +934,9 @@ GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK]
 //       block), so lane (q, r) reads its column r, rows 4 q .. 4 q + 3, and
 //       x_k = L_kk^{-T} s is four FMAs on s in C form (the form the sum of
 //       the pending products L_ik^T x_i already has) and one sum over the
-//       four rows q -- no substitution chain.
-template <int NBLK, bool FULL>
+//       four rows q -- no substitution chain.  SUB: block 0 by substitution on
+//       its columns, as the last block (there is no inverse of it).
+template <int NBLK, bool FULL, bool SUB>
 GLASS_DEV void blk_bwd1_posv(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float myinv_last,
                              const float* lt, float* xs, int n, int q, int r) {
     constexpr int K = NBLK - 1;
@@ -870,9 +962,18 @@ GLASS_DEV void blk_bwd1_posv(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[
     }
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
+        sum_row16(z[k]);
+        if (SUB) {
+            float col[16];
+            const float myinv = recip(diag_cols(T[BI(k, k)], col, xs, q, r)), nmy = -myinv;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) col[j] *= nmy;
+            x[k] = (x[k] - c_to_r(z[k], r)) * myinv;
+            diag_bwd(x[k], col, 16);
+            continue;  // block 0, the last to be solved
+        }
         float yc[4];
         r_to_c(x[k], yc, q);
-        sum_row16(z[k]);
         float part = 0.f;
 #pragma unroll
         for (int c = 0; c < 4; ++c) part = fmaf(lt[k * 16 * kXS + (4 * q + c) * kXS + r], yc[c] - z[k][c], part);
@@ -917,15 +1018,17 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int
 // after a factorization from the rows of the staged block row with their
 // diagonal cleared, for the solves from rows read without it.  Ai is A (L for
 // the solves), Bi the problem's [n][nrhs] right-hand sides; L goes to Ag and
-// the solution to Bg, which are Ai and Bi themselves for a call in place.  xs:
-// the wavefront's LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).
+// the solution to Bg, which are Ai and Bi themselves for a call in place.  SUB
+// (orders up to kBlkSubstMaxN): the panel under the first diagonal block is
+// factored with it (diag_factor_rows) instead of by its inverse.  xs: the wavefront's LDS, kBlkRegionFloats (op 4: blk_posv1_floats(NBLK)).
 // Returns info (0 for the solves); a failed factorization leaves B untouched
 // (out of place: copies it).
-template <int NBLK, int OP, bool FULL>
+template <int NBLK, int OP, bool FULL, bool SUB>
 GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, int n, int nrhs, float* xs, int lane) {
     constexpr int NT = NBLK * (NBLK + 1) / 2;
     constexpr bool FACTOR = OP != 2 && OP != 6, THIN = OP >= 5;
     constexpr bool MFMA_SOLVE = OP != 0 && OP != 4;
+    static_assert(!SUB || (NBLK == 2 && !FULL), "orders 17 .. 24");
     const int q = lane >> 4, r = lane & 15;
     f4_t T[NT];
     blk_load<NBLK, FULL>(T, Ai, n, q, r);
@@ -954,7 +1057,10 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
         float m[16], myinv = 1.f;
         if (FACTOR) {
             int f = 0;
-            diag_factor(T[BI(k, k)], f, myinv, q, r, live);
+            if (SUB && k == 0)
+                diag_factor_rows(T[0], T[BI(1, 0)], f, myinv, q, r);
+            else
+                diag_factor(T[BI(k, k)], f, myinv, q, r, live);
             if (inf == 0 && f != 0) inf = 16 * k + f;
             stage_block_row<NBLK>(T, k, xs, q, r);
             if (early) {
@@ -968,7 +1074,7 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
         // inverse; op 4's forward step): the rows with their diagonal entry
         // cleared, from the staged block row after a factorization, as they
         // come for the solves.
-        const bool need_inv = MFMA_SOLVE || k + 1 < NBLK;
+        const bool need_inv = MFMA_SOLVE || (!SUB && k + 1 < NBLK);
         if (need_inv || OP == 4) {
             if (FACTOR) {
                 if (early)
@@ -987,7 +1093,8 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
         if (OP == 4 && k + 1 == NBLK) myinv_last = myinv;
         if (FACTOR) {
 #pragma unroll
-            for (int i = k + 1; i < NBLK; ++i) T[BI(i, k)] = mma(linv[k], T[BI(i, k)], zero4());
+            for (int i = k + 1; i < NBLK; ++i)
+                if (!SUB) T[BI(i, k)] = mma(linv[k], T[BI(i, k)], zero4());
             if (!early) {
                 block_row_store<NBLK, FULL>(Ag, k, n, xs, lane);
                 wave_sync();
@@ -1008,7 +1115,7 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
     }
     if (OP == 4) {
         if (inf == 0) {
-            blk_bwd1_posv<NBLK, FULL>(T, x1, myinv_last, lt, xs, n, q, r);
+            blk_bwd1_posv<NBLK, FULL, SUB>(T, x1, myinv_last, lt, xs, n, q, r);
             blk_x_store<NBLK, FULL>(x1, Bg, n, q, r);
         }
         return inf;

@@ -111,6 +111,11 @@ constexpr int kGemmStageStride = 68;  // LDS row stride of the staged 16-row out
 // tiles of matrix).  The blocked MFMA kernel's LDS per wavefront holds one
 // staged 16-row block row of L or four 16 x 16 exchange blocks.
 constexpr int kBlkMinN = 17;
+// Up to this order the blocked kernels substitute with the first diagonal
+// block, as the row-per-lane kernels do below them; from 25 on they
+// multiply by its explicit inverse, which is less accurate where the block is
+// ill-conditioned (n = 24: L off by 1.6 times as much at condition 1e4, 2.2 at 1e6).
+constexpr int kBlkSubstMaxN = 24;
 constexpr int kBlkRegionFloats = 1280;
 constexpr int kBlkXS = 20;  // LDS row stride of a 16 x 16 exchange block
 // LDS row stride of a staged block row of L: 16 nblk floats and four of padding.

@@ -468,9 +468,11 @@ __global__ void __launch_bounds__(256, 3) ragged_solve(const int32_t* __restrict
     float* Bg = B + uniform_i64(offB[e]);
     float* buf = chunk[w];
     if (big) {
-        const int inf = k <= 3   ? blk_one<2, 1, false>(Ag, Ag, Bg, Bg, n, r, buf, lane)
-                        : k <= 5 ? blk_one<3, 1, false>(Ag, Ag, Bg, Bg, n, r, buf, lane)
-                                 : blk_one<4, 1, false>(Ag, Ag, Bg, Bg, n, r, buf, lane);
+        static_assert(kBlkSubstMaxN == 8 * (kBigClass + 1), "class 2 substitutes");
+        const int inf = k == 2   ? blk_one<2, 1, false, true>(Ag, Ag, Bg, Bg, n, r, buf, lane)
+                        : k == 3 ? blk_one<2, 1, false, false>(Ag, Ag, Bg, Bg, n, r, buf, lane)
+                        : k <= 5 ? blk_one<3, 1, false, false>(Ag, Ag, Bg, Bg, n, r, buf, lane)
+                                 : blk_one<4, 1, false, false>(Ag, Ag, Bg, Bg, n, r, buf, lane);
         if (lane == 0) info[e] = inf;
         return;
     }
