@@ -337,9 +337,9 @@ GLASS_DEV void panel_steps_rows(f4_t& t, f4_t& u, float& myinv, int q) {
 
 // diag_factor of a whole diagonal block t and, column by column with it, the
 // block u below it: u <- u t^{-T}, by substitution and not by t's inverse.
-// With the inverse, POSV n = 22 took 4 % less (n = 22 x 16,384 27.3 us against
-// 28.4), and its factor was off by 1.3 to 1.6 times as much at condition 1e4,
-// 1.7 to 2.2 times at 1e6.
+// With the inverse, POSV n = 22 took 10.0 us against 10.5 at 4096 problems (27.8
+// and 28.0 at 16,384, POTRF alike throughout), and its factor was off by 1.3 to
+// 1.6 times as much at condition 1e4, 1.7 to 2.2 times at 1e6.
 GLASS_DEV void diag_factor_rows(f4_t& t, f4_t& u, int& f, float& myinv, int q, int r) {
     panel_steps_rows<0>(t, u, myinv, q);
     f = first_nonfinite<16>(myinv);
