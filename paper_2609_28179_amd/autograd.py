@@ -16,7 +16,8 @@ from . import glass
 class CholeskySolve(torch.autograd.Function):
     @staticmethod
     def forward(ctx, A, B, force=None):
-        L, X, info = glass.posv_to(A.contiguous(), B.contiguous(), force)
+        # a negated view (the imaginary part of a conjugate) can be contiguous on the values it negates
+        L, X, info = glass.posv_to(A.resolve_neg().contiguous(), B.resolve_neg().contiguous(), force)
         ctx.save_for_backward(L, X)
         ctx.force = force
         ctx.info = info

@@ -91,3 +91,20 @@ def test_default_placement_several_columns(env, n, r, batch):
     _, X_ref, _ = oracle.posv(c["A"][pick % 512], c["B"][pick % 512])
     assert normwise(B.cpu().numpy()[pick], X_ref).max() <= TOL
     assert (info.cpu().numpy() == 0).all()
+
+
+def test_autograd_forward_takes_negated_views(env):
+    """A negated view shares the storage of the values it negates: the solve
+    uses the values, for A, for B and in the gradients."""
+    glass, torch = env
+    from paper_2609_28179_amd.autograd import cholesky_solve
+    c = inputs.make_case("posv", 6, 10, cfg=9, nrhs=2)
+    A, B = (torch.from_numpy(c[k]).to("cuda:0") for k in ("A", "B"))
+    want = cholesky_solve(A, B)
+    nA, nB = torch._neg_view(-A), torch._neg_view(-B)
+    assert nA.is_neg() and nB.is_neg() and nA.is_contiguous()
+    assert torch.equal(cholesky_solve(nA, nB), want)
+    a, b = A.clone().requires_grad_(), B.clone().requires_grad_()
+    g = torch.autograd.grad(cholesky_solve(a, b).sum(), (a, b))
+    n = torch.autograd.grad(cholesky_solve(torch._neg_view(-a), torch._neg_view(-b)).sum(), (a, b))
+    assert torch.equal(g[0], n[0]) and torch.equal(g[1], n[1])
