@@ -253,8 +253,8 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
     float* xs = lds + (size_t)w * adjoint_blk_floats(NBLK, true);
     f4_t T[NBLK * (NBLK + 1) / 2];
     float b[NBLK], x[NBLK], pend[NBLK];
-    blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
     blk_x_load<NBLK, FULL>(b, G + p * n, n, r);
+    blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
     blk_x_load<NBLK, FULL>(x, X + p * n, n, r);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) pend[k] = 0.f;

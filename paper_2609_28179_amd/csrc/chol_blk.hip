@@ -45,8 +45,10 @@ __global__ void __launch_bounds__(512) chol_blk_solve1(int n, int batch, const f
     if (p >= batch) return;
     const int q = lane >> 4, r = lane & 15;
     f4_t T[NBLK * (NBLK + 1) / 2];
+    float x[NBLK];  // loaded first: needed with the first diagonal block, ahead of the rest of L
+    blk_x_load<NBLK, FULL>(x, B + p * n, n, r);
     blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
-    blk_solve1<NBLK, FULL, FWD, BWD>(T, B + p * n, n, lds + (size_t)w * kBlkSolve1Floats, q, r);
+    blk_solve1<NBLK, FULL, FWD, BWD>(T, x, B + p * n, n, lds + (size_t)w * kBlkSolve1Floats, q, r);
 }
 
 }  // namespace

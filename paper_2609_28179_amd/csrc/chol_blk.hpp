@@ -985,13 +985,12 @@ GLASS_DEV void blk_bwd1_posv(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[
     }
 }
 
-// L x = b (FWD) and / or L^T x = b (BWD) for one right-hand side bg[0..n)
-// (unit stride), in place; T: L in T layout (diagonal blocks with a zero
+// L x = b (FWD) and / or L^T x = b (BWD) for one right-hand side, loaded into x,
+// to bg[0..n) (unit stride); T: L in T layout (diagonal blocks with a zero
 // strict upper part, identity rows past n).
 template <int NBLK, bool FULL, bool FWD, bool BWD>
-GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float* bg, int n, float* xs, int q, int r) {
-    float x[NBLK];
-    blk_x_load<NBLK, FULL>(x, bg, n, r);
+GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float* bg, int n, float* xs, int q,
+                          int r) {
     if (FWD) {
         float p[NBLK];  // pending sum_j L_kj x_j of block row k, split over the rows q
 #pragma unroll
@@ -1031,7 +1030,6 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
     static_assert(!SUB || (NBLK == 2 && !FULL), "orders 17 .. 24");
     const int q = lane >> 4, r = lane & 15;
     f4_t T[NT];
-    blk_load<NBLK, FULL>(T, Ai, n, q, r);
     // op 4: the right-hand side, loaded with A, and the forward substitution's
     // pending sums; step k of the substitution runs inside factorization step k
     float x1[NBLK], p1[NBLK], myinv_last = 1.f;
@@ -1041,6 +1039,7 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) p1[k] = 0.f;
     }
+    blk_load<NBLK, FULL>(T, Ai, n, q, r);
     f4_t linv[NBLK];
     int inf = 0;
 #pragma unroll
