@@ -290,9 +290,15 @@ __global__ void __launch_bounds__(256) mlp_adam_k(int P, float* __restrict__ p, 
 
 size_t mlp_num_params(int d) { return (size_t)offsets(d).total; }
 
+// Backward workgroups, one partial vector each: the launch and the workspace
+// size both come from here.
+static int mlp_backward_blocks(int N) {
+    const long long tiles = ((long long)N + kBwdSamples - 1) / kBwdSamples;
+    return (int)(tiles < kBwdBlocks ? tiles : kBwdBlocks);
+}
+
 size_t mlp_backward_workspace_bytes(int N, int d) {
-    const int nb = (N + kBwdSamples - 1) / kBwdSamples;
-    return sizeof(float) * (size_t)nb * offsets(d).total;
+    return sizeof(float) * (size_t)mlp_backward_blocks(N) * offsets(d).total;
 }
 
 int launch_mlp_forward(int N, int d, const float* X, const float* P, float* H1, float* H2, float* Y, void* stream) {
@@ -305,8 +311,7 @@ int launch_mlp_forward(int N, int d, const float* X, const float* P, float* H1, 
 int launch_mlp_backward(int N, int d, const float* X, const float* P, const float* H1, const float* H2,
                         const float* Y, const float* T, float* grad, void* workspace, void* stream) {
     (void)hipGetLastError();  // a stale error of an earlier runtime call is not ours
-    const long long tiles = ((long long)N + kBwdSamples - 1) / kBwdSamples;
-    const int nb = (int)(tiles < kBwdBlocks ? tiles : kBwdBlocks);  // partial vectors: never more than the workspace holds
+    const int nb = mlp_backward_blocks(N);
     const int np = offsets(d).total;
     float* part = reinterpret_cast<float*>(workspace);
     hipLaunchKernelGGL(mlp_backward_k, dim3(nb), dim3(256), 0, (hipStream_t)stream, N, d, X, P, H1, H2, Y, T, part);

@@ -118,6 +118,25 @@ def test_backward_rejects_small_workspace(env):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("N", [1, 33, 8191, 8192, 8193, 20001])
+def test_backward_workspace_is_what_it_uses(env, N):
+    """The reported size, on either side of the sample count from which a
+    workgroup takes several tiles: one partial vector per workgroup, at most
+    256, every byte of it written and nothing behind it."""
+    glass, torch = env
+    d = 15
+    X, t, p = case(N, d, 7)
+    Xd, pd, H1, H2, y = run_forward(glass, torch, X, p)
+    P, wsb = glass.glass_mlp_num_params(d), glass.glass_mlp_backward_workspace_size(N, d)
+    assert wsb == 4 * P * min(-(-N // 32), 256)
+    ws = torch.full((wsb // 4 + 64,), float("nan"), dtype=torch.float32, device="cuda:0")
+    g = torch.full((P,), float("nan"), dtype=torch.float32, device="cuda:0")
+    assert glass.glass_mlp_backward(N, d, Xd, pd, H1, H2, y, dev(torch, t), g, ws, wsb) == 0
+    torch.cuda.synchronize()
+    assert torch.isnan(ws[wsb // 4:]).all() and not torch.isnan(ws[:wsb // 4]).any()
+    assert rel(g.cpu().numpy(), mlp.grad(p.astype(np.float64), X.astype(np.float64), t.astype(np.float64))) <= TOL
+
+
 @pytest.mark.parametrize("P,step", [(1, 1), (5185, 3), (70000, 1000)])
 def test_adam_parity(env, P, step):
     glass, torch = env
