@@ -34,6 +34,8 @@
  *     (wavefront / pack 1 is feasible for every supported shape).  The table
  *     is measured with one right-hand side: POSV and POTRS with several take
  *     wavefront scope at pack 4 where it names sub-wave at orders from 17 on.
+ *     A GEMV with m <= 16 < n (few wide rows) bypasses the table from the batch
+ *     where its own kernel, four problems per wavefront, is measured faster.
  *     `force != NULL` runs exactly that
  *     placement (only its `scope` and `pack` fields are read) or returns
  *     GLASS_ERR_INFEASIBLE_PLACEMENT without enqueuing anything.
@@ -128,7 +130,10 @@ glass_status_t glass_gemm_batched_ex(int transa, int transb, int m, int n, int k
 /* y = alpha * A x + beta * y  (Sec. III-B, BLAS L2).
  * A [batch][m][n], x [batch][n], y [batch][m]; beta == 0: y is not read.
  * y must not overlap A or x.  Thread scope requires m == n <= 16, sub-wave
- * scope m, n <= 16. */
+ * scope m, n <= 16.  With m <= 16 < n and force NULL, batches from 1 (m <= 4), 4 or
+ * 3000 (m <= 8), 4, 4096 or 6144 (by the row length) run four problems per
+ * wavefront; no forced placement does: a forced wavefront one runs a problem
+ * per wavefront. */
 glass_status_t glass_gemv_batched(int m, int n, int batch, float alpha,
                                   const float* A, const float* x, float beta,
                                   float* y, const glass_placement_t* force,

@@ -85,6 +85,21 @@ glass_status_t resolve(const Shape& s, long long batch, const glass_placement_t*
     return GLASS_ERR_INFEASIBLE_PLACEMENT;
 }
 
+// Batch from which a GEMV with few wide rows (gemv_thin) runs four problems per
+// wavefront without a forced placement; below it, the tabulated one.  Up to 4
+// rows always (1 x 64: 0.77 of the tabulated placement's time at batch 1, 0.66 at 4,
+// 0.36 at 16,384).  With more, a wavefront's loads and its reduction run longer
+// than the four one-problem wavefronts they replace until those fill the chip: 5..8
+// rows from batch 4 (8 x 28: 1.14 at 1, 0.91 at 4), or 3000 where rows are short (8 x
+// 18: 1.19 at 2, 1.02 at 1024, 0.88 at 3000); 9..16 rows, twice the loads, from 4
+// with nearly full pieces (16 x 60: 1.26 at 1, 0.85 at 4), else 4096 (12 x 28: 1.13 at
+// 256, 0.89 at 4096) or 6144 (9 x 18: 1.38 at 256, 1.12 at 4096, 0.94 at 6000).
+int gemv_thin_from(int m, int n) {
+    if (m <= 4) return 1;
+    if (m <= 8) return n > 20 ? 4 : 3000;
+    return n >= 58 ? 4 : n >= 28 ? 4096 : 6144;
+}
+
 thread_local int t_last_launch_error = 0;
 
 inline glass_status_t launched(int err) {
@@ -128,7 +143,8 @@ glass_status_t glass_gemv_batched(int m, int n, int batch, float alpha, const fl
     if (batch < 0) return GLASS_ERR_INVALID_VALUE;
     if (batch == 0) return GLASS_OK;
     if (!A || !x || !y) return GLASS_ERR_INVALID_VALUE;
-    if (!force && gemv_thin(m, n)) return launched(launch_gemv_thin(m, n, batch, alpha, A, x, beta, y, stream));
+    if (!force && gemv_thin(m, n) && batch >= gemv_thin_from(m, n))
+        return launched(launch_gemv_thin(m, n, batch, alpha, A, x, beta, y, stream));
     Shape s{GLASS_OP_GEMV, m, n, n, 1, 0};
     Geometry g;
     glass_status_t st = resolve(s, batch, force, &g);

@@ -280,6 +280,25 @@ def test_gemv_few_wide_rows(env, m, n, shift):
             assert all(guards_intact(b[0], pad) for b in bufs)
 
 
+@pytest.mark.parametrize("m,n,at", [(5, 17, 3000), (8, 20, 3000), (5, 21, 4), (8, 64, 4), (9, 17, 6144), (16, 27, 6144),
+                                    (9, 28, 4096), (16, 57, 4096), (9, 58, 4), (16, 64, 4)])
+def test_gemv_few_wide_rows_either_side(env, m, n, at):
+    """The batches on either side of where the call changes kernel: the rounding
+    bound of an FP32 dot product in any order, as above."""
+    glass, torch = env
+    for batch in (at - 1, at):
+        _say(f"gemv few wide rows m={m} n={n} batch={batch}")
+        rng = _rng(10, m, n, batch)
+        A, x, y0 = (inputs.uniform(rng, s) for s in ((batch, m, n), (batch, n), (batch, m)))
+        bufs = [guarded(torch, a, "cuda:0") for a in (A, x, y0)]
+        assert glass.glass_gemv_batched(m, n, batch, 1.5, bufs[0][1], bufs[1][1], 0.5, bufs[2][1]) == 0
+        torch.cuda.synchronize()
+        got, ref = bufs[2][1].cpu().numpy(), oracle.gemv(A, x, y0, alpha=1.5, beta=0.5)
+        mag = 1.5 * np.matmul(np.abs(A.astype(np.float64)), np.abs(x)[:, :, None])[:, :, 0] + 0.5 * np.abs(y0)
+        assert (np.abs(got - ref) <= (n + 4) * 2.0 ** -24 * mag).all()
+        assert all(guards_intact(b[0]) for b in bufs)
+
+
 @pytest.mark.parametrize("shift", [0, 1, 2, 3])
 def test_gemv_square_wave_orders(env, shift):
     """Square GEMV at wave scope, every order of the register form (16-byte
