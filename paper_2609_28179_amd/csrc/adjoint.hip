@@ -225,11 +225,6 @@ __global__ void __launch_bounds__(512) adjoint_wave(int n, int nrhs, int batch, 
 }
 
 // ------------------------------------------------ blocked form, orders 17..64
-// LDS floats of one wavefront: the staged block row of dA and, with several
-// right-hand sides, one exchange block per tile of the transposes.
-constexpr int adjoint_blk_floats(int nblk, bool one) {
-    return one ? 16 * blk_row_stride(nblk) : nblk * 16 * kXS;
-}
 static_assert(adjoint_blk_floats(2, false) >= 16 * blk_row_stride(2) && adjoint_blk_floats(3, false) >= 16 * blk_row_stride(3) &&
                   adjoint_blk_floats(4, false) >= 16 * blk_row_stride(4),
               "the staged block row fits the exchange blocks");
@@ -546,15 +541,14 @@ int launch_posv_adjoint(const Shape& sh, const Geometry& g, int batch, const flo
         // from the row-per-lane ones
         const int nblk = blk_nblk(n);
         const bool full = n == 16 * nblk && al16(L) && al16(dA);
-        const size_t lds = sizeof(float) * (size_t)adjoint_blk_floats(nblk, r == 1) * g.pack;
 #define CASE(NBLK, FULL)                                                                                            \
     if (nblk == NBLK && full == FULL) {                                                                             \
         if (r == 1)                                                                                                 \
-            hipLaunchKernelGGL((adjoint_blk1<NBLK, FULL>), grid, block, lds, st, n, batch, L, X, G, dB, dA);         \
+            hipLaunchKernelGGL((adjoint_blk1<NBLK, FULL>), grid, block, g.lds_bytes, st, n, batch, L, X, G, dB, dA); \
         else if (r <= 4)                                                                                            \
-            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL, true>), grid, block, lds, st, n, r, batch, L, X, G, dB, dA); \
+            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL, true>), grid, block, g.lds_bytes, st, n, r, batch, L, X, G, dB, dA); \
         else                                                                                                        \
-            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL, false>), grid, block, lds, st, n, r, batch, L, X, G, dB, dA); \
+            hipLaunchKernelGGL((adjoint_blk<NBLK, FULL, false>), grid, block, g.lds_bytes, st, n, r, batch, L, X, G, dB, dA); \
         return (int)hipGetLastError();                                                                              \
     }
         CASE(2, false) CASE(2, true) CASE(3, false) CASE(3, true) CASE(4, false) CASE(4, true)

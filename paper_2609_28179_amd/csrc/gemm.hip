@@ -523,16 +523,15 @@ int launch_gemm_t(const Shape& sh, const Geometry& g, int batch, float alpha, co
                 hipLaunchKernelGGL(gemm_tvec<16>, grid, block, 0, st, m, k, batch, alpha, A, B, beta, C);
             return (int)hipGetLastError();
         }
-        const size_t lds = sizeof(float) * 16 * kGemmStageStride * (size_t)g.pack;
         // one array as both operands of A^T B with m = n: its fragments serve twice
         const bool syrk = TA && !TBT && m == n && A == B;
 #define X(NTB, KTB)                                                                                                   \
     if (nt == NTB && kt == KTB) {                                                                                     \
         if (syrk)                                                                                                     \
-            hipLaunchKernelGGL((gemm_mfma_wave<NTB, KTB, TA, TBT, TA && !TBT>), grid, block, lds, st, m, n, k, batch, \
+            hipLaunchKernelGGL((gemm_mfma_wave<NTB, KTB, TA, TBT, TA && !TBT>), grid, block, g.lds_bytes, st, m, n, k, batch, \
                                alpha, A, B, beta, C);                                                                 \
         else                                                                                                          \
-            hipLaunchKernelGGL((gemm_mfma_wave<NTB, KTB, TA, TBT, false>), grid, block, lds, st, m, n, k, batch,      \
+            hipLaunchKernelGGL((gemm_mfma_wave<NTB, KTB, TA, TBT, false>), grid, block, g.lds_bytes, st, m, n, k, batch, \
                                alpha, A, B, beta, C);                                                                 \
         return (int)hipGetLastError();                                                                                \
     }

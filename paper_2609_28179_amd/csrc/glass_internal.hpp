@@ -72,7 +72,7 @@ inline bool gemm_uses_mfma(const Shape& s) {
 }
 
 // LDS floats of one problem region of the workgroup scope (and of the wave
-// scope for GEMV and small-n GEMM): the staged, row-padded problem.
+// scope for GEMV outside the register form): the staged, row-padded problem.
 inline size_t region_floats(const Shape& s) {
     const int n = s.n;
     switch (s.op) {
@@ -142,13 +142,20 @@ inline bool gemv_uses_dpp(const Shape& s) {
     return s.n > 16 || s.n % 4 == 0;
 }
 
+// The blocked adjoint: the staged block row of dA and, with several right-hand
+// sides, one exchange block per tile of the transposes.
+constexpr int adjoint_blk_floats(int nblk, bool one) {
+    return one ? 16 * blk_row_stride(nblk) : nblk * 16 * kBlkXS;
+}
+
+// What a wave-scope launch reserves per wavefront, and what its feasibility is
+// judged by.
 inline size_t wave_region_floats(const Shape& s) {
     switch (s.op) {
     case GLASS_OP_GEMV:
         return gemv_uses_dpp(s) ? 0 : region_floats(s);
     case GLASS_OP_GEMM:
-        // MFMA path: one 16-row block of C staged for full-row stores
-        return gemm_uses_mfma(s) ? (size_t)16 * kGemmStageStride : region_floats(s);
+        return (size_t)16 * kGemmStageStride;  // one 16-row block of C staged for full-row stores
     case GLASS_OP_POTRF:
     case GLASS_OP_POTRS:
     case GLASS_OP_POSV:
@@ -157,11 +164,15 @@ inline size_t wave_region_floats(const Shape& s) {
         if (blk_posv1_shape(s)) return (size_t)blk_posv1_floats(blk_nblk(s.n));
         return s.n >= kBlkMinN ? (size_t)kBlkRegionFloats : (size_t)8 * bucket8_host(s.n);
     case GLASS_OP_POSV_ADJOINT:
-        return (size_t)8 * bucket8_host(s.n);
+        return s.n >= kBlkMinN ? (size_t)adjoint_blk_floats(blk_nblk(s.n), s.nrhs == 1) : (size_t)8 * bucket8_host(s.n);
     default:
         return region_floats(s);
     }
 }
+static_assert(8 * 16 * kGemmStageStride * sizeof(float) <= kLdsBudgetBytes &&
+                  8 * adjoint_blk_floats(4, false) * sizeof(float) <= kLdsBudgetBytes &&
+                  8 * blk_posv1_floats(4) * sizeof(float) <= kLdsBudgetBytes,
+              "eight wavefronts of every matrix-core kernel fit: wave scope is feasible at every pack");
 
 // Sub-wave scope of the batched Cholesky family (orders <= 32): 64 / SEG
 // problems per wavefront, one per SEG-lane segment, SEG = 16 up to order 16
