@@ -309,11 +309,15 @@ GLASS_DEV void cols_load_t(f4_t (&V)[NBLK], const float* Mg, int n, int nr, int 
 // pieces block (j, i); the diagonal block's lower entries
 // go to both places, so dA is bit-symmetric.  Past 16 columns D is formed
 // after the solves, from dB read back, so that L is no longer live.
-// Bound by the matrix cores: each 16 x 16 x 4 product holds them 32 cycles.
-// With all 16 columns multiplied whatever nr, 16,384 problems of n = 36 and 3
-// columns took 46.6 us against 39.4 (96 and 60 products per problem), n = 28
-// and 4 columns at 65,536 107 against 101; row-per-lane 117.7, and n = 64 with
-// 8 columns 621.6 against 111.1.
+// Bound by the matrix cores: each 16 x 16 x 4 product holds them 32 cycles.  With
+// all 16 columns multiplied whatever nr, n = 28 and 4 columns at 65,536 took 107 us
+// against 101, n = 36 and 3 columns at 16,384 46.6 against 39.4; up to four columns
+// (THIN) the solve then runs on 4 x 4 x 1 products (39.4 -> 35.6 there, and 32
+// registers fewer).  Row-per-lane: n = 36 with 3 columns 117.7, n = 64 with 8 621.6
+// against 111.1.  On ill-conditioned factors the inverses of the diagonal blocks
+// leave a larger residual than that form's substitutions (n = 28, 2 columns: 1.6
+// times at condition 1e4, 2.2 at 1e6; n = 64 alike), dB's error is 0.6, 0.99 and 1.1
+// times as large at conditions of a few, 1e4 and 1e6.
 template <int NBLK, bool FULL, bool THIN>
 __global__ void __launch_bounds__(512) adjoint_blk(int n, int nr, int batch, const float* __restrict__ L,
                                                    const float* __restrict__ X, const float* G, float* dB,

@@ -8,8 +8,9 @@
 namespace glass {
 namespace {
 
-// op: 0 POTRF, 1 POSV, 2 POTRS, 3 TRSV (trans: 0 forward, 1 backward), 4 POSV
-// with one right-hand side.
+// op: 0 POTRF, 1 POSV, 2 POTRS (five right-hand sides or more), 4 POSV with one, 5
+// POSV and 6 POTRS with two to four (POTRS with one and TRSV: chol_blk_solve1).
+// SUB: orders up to kBlkSubstMaxN.
 template <int NBLK, int OP, bool FULL, bool SUB>
 __global__ void __launch_bounds__(512) chol_blk(int n, int nrhs, int batch, const float* Ai, float* A,
                                                 const float* Bi, float* B, int32_t* __restrict__ info) {

@@ -4,7 +4,12 @@
 //
 // POTRF / POSV / POTRS / TRSV of one problem of order 17..64 per wavefront,
 // blocked in 16 x 16 tiles, with every block product on the matrix cores
-// (v_mfma_f32_16x16x4_f32).
+// (v_mfma_f32_16x16x4_f32).  From order 25 on, and in every solve with several
+// right-hand sides, a diagonal block enters the products as its explicit
+// inverse.  Against substitution that leaves the error of X as it is up to
+// condition 1e4 (0.6 to 0.9 times as large at conditions of a few, 1.15 at 1e6) but a
+// residual 1.2 to 2.5 times as large at 1e4, 0.02 of n u |A| |X|; the factor's own error
+// grows too (kBlkSubstMaxN), so that orders up to 24 factor by substitution.
 //
 // Right-looking block Cholesky (the factorization of Sec. III-B, in blocks):
 // for each block column k, factor the diagonal block A_kk = L_kk L_kk^T, form

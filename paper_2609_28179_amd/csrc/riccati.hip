@@ -57,8 +57,11 @@ namespace {
 // S.  With guarded element-wise loads at the point of use, 16,384 problems took
 // (20, 3) 28.4 us against 22.3 now, (27, 6) 35.6 against 27.6, (41, 9) 104
 // against 62.5, (48, 16) 97.6 against 84.7, and (32, 8) at 65,536 144.5 against
-// 131.9.  What is left is matrix and vector issue: 20 + 8 ceil(nx / 16) products
-// of 16 x 16 x 16 blocks at two tiles of states, a third of them padding.
+// 131.9.  With T = ceil(nx / 16) tiles of states the products are T^2 (P B), T (S) and
+// T (T + 2) (T_j and its two solves) blocks of 16 x 16 x 16, four matrix
+// instructions each: 14 blocks at two tiles, a third of them padding, about 12 us of
+// matrix-core time at (27, 6) x 16,384.  The rest is the serial part between: S
+// through LDS into row form, its factorization and its inverse.
 template <int NXB, int NUB>
 __global__ void __launch_bounds__(512) riccati_mfma(int nx, int nu, int batch, const float* __restrict__ A,
                                                     const float* __restrict__ B, const float* __restrict__ P,

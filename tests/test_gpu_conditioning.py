@@ -200,3 +200,53 @@ def test_conditioned_multi_rhs(env, op, scope):
             f, _ = _run(glass, torch, op, n, 1e4, 0, scope, nrhs=nrhs)
             fails += f
     assert not fails, "\n".join(fails)
+
+
+@pytest.mark.parametrize("kappa", KAPPAS)
+@pytest.mark.parametrize("scope", ["thread", "wave", "subwave"])
+def test_conditioned_adjoint(env, scope, kappa):
+    """The adjoint of the solve: dB by the bars of POTRS (it is that solve on
+    G), dA against the float64 product of the FP32 dB and X, within the
+    rounding bound (2 r + 3) u (|dB| |X|^T + |X| |dB|^T) / 2 of its sum in any order."""
+    glass, torch = env
+    fails, worst = [], {}
+    for n in NS + (17, 20, 36):
+        for r in (1, 3, 8, 17):
+            if glass.glass_placement_feasible(glass.OP_POSV_ADJOINT, n, r, glass.SCOPES[scope], 1) != 1:
+                continue
+            _say(f"adjoint n={n} nrhs={r} kappa={kappa:.0e} {scope}/P=1")
+            case = inputs.make_case("potrs", n, BATCH, cfg=301, nrhs=r, extra=int(np.log10(kappa)), kappa=kappa)
+            L, X = case["L"], case["B"]
+            G = inputs.uniform(inputs.rng_for(302, "adjoint", n, BATCH, r), X.shape)
+            Ld, Xd, Gd = (torch.from_numpy(a).to("cuda:0") for a in (L, X, G))
+            dB, dA = torch.empty_like(Xd), torch.empty_like(Ld)
+            assert glass.glass_posv_adjoint_batched(n, r, BATCH, Ld, Xd, Gd, dB, dA, (scope, 1)) == 0
+            torch.cuda.synchronize()
+            dB, dA = dB.cpu().numpy(), dA.cpu().numpy()
+            L64, dB64, X64 = L.astype(np.float64), dB.astype(np.float64), X.astype(np.float64)
+            A64 = np.matmul(L64, np.swapaxes(L64, 1, 2))
+            fwd, rho = normwise(dB, oracle.potrs(L, G)).max(), _rho_s(A64, dB, G).max()
+            P = np.matmul(dB64, np.swapaxes(X64, 1, 2))
+            Q = np.matmul(np.abs(dB64), np.swapaxes(np.abs(X64), 1, 2))
+            off = np.abs(dA + 0.5 * (P + np.swapaxes(P, 1, 2)))
+            share = (off / ((2 * r + 3) * U * 0.5 * (Q + np.swapaxes(Q, 1, 2)))).max()
+            worst[n] = max(worst.get(n, 0.0), float(rho))
+            if not fwd <= _x_bar(kappa, n) or not rho <= RHO_MAX or not share <= 1.0:
+                fails.append((n, r, float(fwd), float(rho), float(share)))
+    for n, v in sorted(worst.items()):
+        _say(f"  worst rho_s n={n} kappa={kappa:.0e}: {v:.3e}")
+    assert not fails, fails
+
+
+@pytest.mark.parametrize("op", ["posv", "potrs"])
+def test_conditioned_multi_rhs_blocked_orders(env, op):
+    """Several right-hand sides at the smallest orders of the blocked kernels, whose
+    solves multiply by explicit inverses of the diagonal blocks."""
+    glass, torch = env
+    fails = []
+    for n in (17, 20, 23):
+        for nrhs in (2, 4, 5, 17):
+            _say(f"{op} n={n} nrhs={nrhs} kappa=1e4 wave/P=1")
+            f, _ = _run(glass, torch, op, n, 1e4, 0, "wave", nrhs=nrhs)
+            fails += f
+    assert not fails, "\n".join(fails)
