@@ -9,9 +9,9 @@ samples kept, a 5 % dispatch margin).
   python -m paper_2609_28179_amd.autotune ragged [--out FILE]   (per-class ragged placement)
   python -m paper_2609_28179_amd.autotune emit-ragged [--sweep FILE] [--out INC]
 
-The sweep covers the 300 cells {GEMM, GEMV, POTRF, POTRS, POSV, TRSV} x
-n in {3,4,6,7,12,16,32,64} x batch in {1,16,256,1024,4096,65536} plus SE(3)
-compose / inverse x batch, each at every feasible (scope, pack).  It appends
+The sweep covers the 444 cells {GEMM, GEMV, POTRF, POTRS, POSV, TRSV} x
+n in {3,4,6,7,8,10,12,16,24,32,40,64} x batch in {1,16,256,1024,4096,65536} plus
+SE(3) compose / inverse x batch, each at every feasible (scope, pack).  It appends
 one JSON record per (cell, placement) and resumes by skipping cells already
 complete, and only on the kernel sources it started on (the meta line
 records their hash; emit stamps that hash and the sweep file's own into the
@@ -372,7 +372,7 @@ def main(argv=None):
     s.add_argument("--ns", default="", help="comma-separated orders to sweep (default: all)")
     s.add_argument("--max-batch", type=int, default=0)
     s.add_argument("--cells", choices=("table", "heldout"), default="table",
-                   help="table: the 408 cells of the dispatch table; heldout: n in {5,9,20,48} x "
+                   help="table: the 444 cells of the dispatch table; heldout: n in {5,9,20,48} x "
                         "batch in {256,65536}, the cost model's evaluation set")
     e = sub.add_parser("emit")
     e.add_argument("--sweep", default=DEFAULT_SWEEP)

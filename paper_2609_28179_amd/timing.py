@@ -31,10 +31,11 @@ SE3_OPS = ("se3_compose", "se3_inverse")
 SWEEP_N = (3, 4, 6, 7, 12, 16, 32, 64)
 SWEEP_B = (1, 16, 256, 4096, 65536)          # the benchmark grid's batches
 # The dispatch table's keys.  Orders: the benchmark's, 10 (orders 8..10 took the
-# placement of 12), 24 (17..24 are faster on sub-wave segments than on the wave
+# placement of 12) and 8 (POTRF n = 8 x 16 takes 3.5 us at thread scope, order 10's
+# placement, and 2.9 at sub-wave scope), 24 (17..24 are faster on sub-wave segments than on the wave
 # placement of 32 at large batches: POTRF n = 20 x 65,536 59 against 65 us) and
 # 40 (33..40 took the pack of 64).  Batches: the benchmark's and the 1024-system POSV.
-TABLE_N = (3, 4, 6, 7, 10, 12, 16, 24, 32, 40, 64)
+TABLE_N = (3, 4, 6, 7, 8, 10, 12, 16, 24, 32, 40, 64)
 TABLE_B = (1, 16, 256, 1024, 4096, 65536)
 PACKS = (1, 2, 4, 8)
 HELDOUT_N = (5, 9, 20, 48)          # orders the table does not hold (cost-model evaluation)
@@ -71,7 +72,7 @@ def flops(op: str, n: int, nrhs: int = 1) -> float:
 
 def sweep_cells(batches=SWEEP_B, orders=SWEEP_N):
     """The benchmark grid (250 cells); with TABLE_B and TABLE_N the dispatch
-    table's grid (408 cells)."""
+    table's grid (444 cells)."""
     cells = [(op, n, b) for op in SWEEP_OPS for n in orders for b in batches]
     cells += [(op, 4, b) for op in SE3_OPS for b in batches]
     return cells
