@@ -248,18 +248,21 @@ __global__ void __launch_bounds__(512) adjoint_blk1(int n, int batch, const floa
     float* xs = lds + (size_t)w * adjoint_blk_floats(NBLK, true);
     f4_t T[NBLK * (NBLK + 1) / 2];
     float b[NBLK], x[NBLK], pend[NBLK];
-    blk_x_load<NBLK, FULL>(b, G + p * n, n, r);
+    if (FULL) blk_x_load<NBLK, FULL>(b, G + p * n, n, r);  // ahead of L as in chol_blk_solve1
     blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
+    if (!FULL) blk_x_load<NBLK, FULL>(b, G + p * n, n, r);
     blk_x_load<NBLK, FULL>(x, X + p * n, n, r);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) pend[k] = 0.f;
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
         float a[16];
-        const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r));
-        blk_fwd_rows<NBLK, FULL>(T, k, a, myinv, b, pend, q, blk_live<NBLK, FULL>(n, k));
+        const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
+        blk_fwd_step<NBLK, false>(T, k, a, myinv, b, pend, q, blk_live<NBLK, FULL>(n, k));
     }
-    blk_bwd1<NBLK, FULL>(T, b, xs, n, q, r);
+    blk_bwd1<NBLK, FULL, false>(T, b, xs, n, q, r);
     blk_x_store<NBLK, FULL>(b, dB + p * n, n, q, r);
     float bc[NBLK][4], xc[NBLK][4];
 #pragma unroll

@@ -45,11 +45,31 @@ __global__ void __launch_bounds__(512) chol_blk_solve1(int n, int batch, const f
     const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
     if (p >= batch) return;
     const int q = lane >> 4, r = lane & 15;
+    float* xs = lds + (size_t)w * kBlkSolve1Floats;
+    float* bg = B + p * n;
     f4_t T[NBLK * (NBLK + 1) / 2];
-    float x[NBLK];  // loaded first: needed with the first diagonal block, ahead of the rest of L
-    blk_x_load<NBLK, FULL>(x, B + p * n, n, r);
+    float x[NBLK];
+    // On whole tiles b is loaded ahead of L (the first diagonal step waits for
+    // it: TRSV transposed n = 64 x 256 3.22 us against 3.42), on cut tiles behind
+    // it (n = 33 x 16 2.52 us against 2.70).
+    if (FULL) blk_x_load<NBLK, FULL>(x, bg, n, r);
     blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
-    blk_solve1<NBLK, FULL, FWD, BWD>(T, x, B + p * n, n, lds + (size_t)w * kBlkSolve1Floats, q, r);
+    if (!FULL) blk_x_load<NBLK, FULL>(x, bg, n, r);
+    blk_solve1<NBLK, FULL, FWD, BWD, false>(T, x, n, xs, q, r);
+    // One direction leaves the unknowns before a non-finite entry of b finite: such
+    // a problem is solved again, from its operands, by the form that keeps them
+    // (in every problem it took TRSV n = 22 x 65,536 from 27 us to 31).
+    if (FWD != BWD) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) s += fabsf(x[k]);
+        if (__builtin_expect(__ballot(!(s < INFINITY)) != 0, 0)) {
+            blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
+            blk_x_load<NBLK, FULL>(x, bg, n, r);
+            blk_solve1<NBLK, FULL, FWD, BWD, true>(T, x, n, xs, q, r);
+        }
+    }
+    blk_x_store<NBLK, FULL>(x, bg, n, q, r);
 }
 
 }  // namespace

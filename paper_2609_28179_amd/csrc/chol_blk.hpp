@@ -703,18 +703,13 @@ GLASS_DEV void diag_bwd(float& s, const float (&m)[16], int live) {
     DiagSub<3, -1>::run(s, m);
 }
 
-// The substitutions on unscaled coefficients (row r of L forward, column r
-// backward, the diagonal entry cleared): in step K unknown K is s_K / L_KK,
-// kept in lane K of y, and its products leave s.  The lanes whose unknown is
-// already final meet zero coefficients, whose product with an infinity or a NaN
-// is no zero: it lands in their s, and y keeps every unknown that does not
-// depend on such an entry.  The select fills one of the two wait states
-// between the product and its DPP read.  Orders 17 .. 31 substitute so; from
-// 32 on the scaled coefficients stay, whose chain is an instruction a step
-// shorter (POTRS n = 64 x 256 4.2 us against 4.4).
-template <int NBLK, bool FULL>
-constexpr bool kSubstKeep = NBLK == 2 && !FULL;
-
+// The same on unscaled coefficients (row r of L forward, column r backward, the
+// diagonal entry cleared), for a right-hand side with an infinity or a NaN: in
+// step K unknown K is s_K / L_KK, kept in lane K of y, and its products leave
+// s.  The lanes whose unknown is already final meet zero coefficients, whose
+// product with such an entry is no zero: it lands in their s, and y keeps
+// every unknown that does not depend on it.  The select fills one of the two
+// wait states between the product and its DPP read.
 template <int K>
 GLASS_DEV void keep_and_fmac(float& s, float& y, float t, float a) {
     asm volatile("v_cndmask_b32_e64 %1, %1, %2, %4\n\ts_nop 0\n\t"
@@ -857,10 +852,10 @@ GLASS_DEV void blk_x_store(const float (&x)[NBLK], float* bg, int n, int q, int 
 }
 
 // Forward step k: block k of y from its pending sum p[k] by the diagonal
-// block's rows, then its contributions L_ik y_k to the pending sums of the
-// later blocks (right-looking, p[i] split over the rows q).  KEEP: m holds
-// L_rK; otherwise -L_rK / L_rr (op 4 of blk_one, whose block inverses use
-// them), and the right-hand side is scaled by 1 / L_rr first.
+// block's lane-local coefficients m_K = -L_rK / L_rr and 1 / L_rr (the
+// right-hand side is scaled by it first; KEEP: m_K = L_rK, diag_keep_fwd), then
+// its contributions L_ik y_k to the pending sums of the later blocks
+// (right-looking, p[i] split over the rows q).
 template <int NBLK, bool KEEP>
 GLASS_DEV void blk_fwd_step(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const float (&m)[16], float myinv,
                             float (&x)[NBLK], float (&p)[NBLK], int q, int live) {
@@ -882,21 +877,9 @@ GLASS_DEV void blk_fwd_step(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, const
     }
 }
 
-// The same on the diagonal block's rows a as they are (diagonal entry cleared).
-template <int NBLK, bool FULL>
-GLASS_DEV void blk_fwd_rows(const f4_t (&T)[NBLK * (NBLK + 1) / 2], int k, float (&a)[16], float myinv,
-                            float (&x)[NBLK], float (&p)[NBLK], int q, int live) {
-    if (!kSubstKeep<NBLK, FULL>) {
-        const float nmy = -myinv;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
-    }
-    blk_fwd_step<NBLK, kSubstKeep<NBLK, FULL>>(T, k, a, myinv, x, p, q, live);
-}
-
 // L^T x = y, bottom block first (left-looking over the columns: z[j] collects
 // sum_i L_ij^T x_i split over the lanes of a row).
-template <int NBLK, bool FULL>
+template <int NBLK, bool FULL, bool KEEP>
 GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float* xs, int n, int q, int r) {
     float z[NBLK][4];
 #pragma unroll
@@ -912,7 +895,7 @@ GLASS_DEV void blk_bwd1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK]
         }
         float col[16];
         const float myinv = recip(diag_cols(T[BI(k, k)], col, xs, q, r)), nmy = -myinv;
-        if (kSubstKeep<NBLK, FULL>) {
+        if (KEEP) {
             x[k] = diag_keep_bwd(s, col, myinv, blk_live<NBLK, FULL>(n, k));
         } else {
 #pragma unroll
@@ -990,12 +973,11 @@ GLASS_DEV void blk_bwd1_posv(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[
     }
 }
 
-// L x = b (FWD) and / or L^T x = b (BWD) for one right-hand side, loaded into x,
-// to bg[0..n) (unit stride); T: L in T layout (diagonal blocks with a zero
-// strict upper part, identity rows past n).
-template <int NBLK, bool FULL, bool FWD, bool BWD>
-GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], float* bg, int n, float* xs, int q,
-                          int r) {
+// L x = b (FWD) and / or L^T x = b (BWD) for one right-hand side in x; T: L in T
+// layout (diagonal blocks with a zero strict upper part, identity rows past n).
+// KEEP: see diag_keep_fwd.
+template <int NBLK, bool FULL, bool FWD, bool BWD, bool KEEP>
+GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBLK], int n, float* xs, int q, int r) {
     if (FWD) {
         float p[NBLK];  // pending sum_j L_kj x_j of block row k, split over the rows q
 #pragma unroll
@@ -1003,12 +985,15 @@ GLASS_DEV void blk_solve1(const f4_t (&T)[NBLK * (NBLK + 1) / 2], float (&x)[NBL
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
             float a[16];
-            const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r));
-            blk_fwd_rows<NBLK, FULL>(T, k, a, myinv, x, p, q, blk_live<NBLK, FULL>(n, k));
+            const float myinv = recip(diag_rows(T[BI(k, k)], a, xs, q, r)), nmy = -myinv;
+            if (!KEEP) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) a[j] *= nmy;  // -L_rj / L_rr
+            }
+            blk_fwd_step<NBLK, KEEP>(T, k, a, myinv, x, p, q, blk_live<NBLK, FULL>(n, k));
         }
     }
-    if (BWD) blk_bwd1<NBLK, FULL>(T, x, xs, n, q, r);
-    blk_x_store<NBLK, FULL>(x, bg, n, q, r);
+    if (BWD) blk_bwd1<NBLK, FULL, KEEP>(T, x, xs, n, q, r);
 }
 
 // One problem: factor (POTRF, POSV) or take L as given (POTRS), then solve.
@@ -1039,12 +1024,13 @@ GLASS_DEV int blk_one(const float* Ai, float* Ag, const float* Bi, float* Bg, in
     // pending sums; step k of the substitution runs inside factorization step k
     float x1[NBLK], p1[NBLK], myinv_last = 1.f;
     float* lt = xs + 16 * blk_row_stride(NBLK);  // op 4: L_kk^{-1} of the blocks k < NBLK - 1
+    if (OP == 4 && FULL) blk_x_load<NBLK, FULL>(x1, Bi, n, r);
+    blk_load<NBLK, FULL>(T, Ai, n, q, r);
     if (OP == 4) {
-        blk_x_load<NBLK, FULL>(x1, Bi, n, r);
+        if (!FULL) blk_x_load<NBLK, FULL>(x1, Bi, n, r);
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) p1[k] = 0.f;
     }
-    blk_load<NBLK, FULL>(T, Ai, n, q, r);
     f4_t linv[NBLK];
     int inf = 0;
 #pragma unroll
