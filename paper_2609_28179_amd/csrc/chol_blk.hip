@@ -45,15 +45,18 @@ __global__ void __launch_bounds__(512) chol_blk_solve1(int n, int batch, const f
     const long long p = (long long)blockIdx.x * (blockDim.x >> 6) + w;
     if (p >= batch) return;
     const int q = lane >> 4, r = lane & 15;
-    float* xs = lds + (size_t)w * kBlkSolve1Floats;
-    float* bg = B + p * n;
     f4_t T[NBLK * (NBLK + 1) / 2];
     float x[NBLK];
     // On whole tiles b is loaded ahead of L (the first diagonal step waits for
     // it: TRSV transposed n = 64 x 256 3.22 us against 3.42), on cut tiles behind
-    // it (n = 33 x 16 2.52 us against 2.70).
-    if (FULL) blk_x_load<NBLK, FULL>(x, bg, n, r);
+    // it (n = 33 x 16 2.52 us against 2.70).  Computing the two addresses here makes
+    // the schedule mask the last diagonal block behind the first substitution step
+    // instead of waiting for every tile ahead of it (POTRS n = 53 x 1024 6.46 us
+    // against 6.82).
+    if (FULL) blk_x_load<NBLK, FULL>(x, B + p * n, n, r);
     blk_load<NBLK, FULL>(T, L + p * n * n, n, q, r);
+    float* bg = B + p * n;
+    float* xs = lds + (size_t)w * kBlkSolve1Floats;
     if (!FULL) blk_x_load<NBLK, FULL>(x, bg, n, r);
     blk_solve1<NBLK, FULL, FWD, BWD, false>(T, x, n, xs, q, r);
     // One direction leaves the unknowns before a non-finite entry of b finite: such
