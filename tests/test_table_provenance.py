@@ -120,3 +120,17 @@ def test_source_hash_ignores_comments_not_code():
     assert autotune._code_only(a) == autotune._code_only(b)
     assert autotune._code_only(a) != autotune._code_only(c)
     assert autotune._code_only(a) != autotune._code_only(d)
+
+
+def test_tie_between_scopes_goes_to_the_wave_scope():
+    """Placements within 1 % of a cell's fastest are ordered by chance, and the
+    orders between the table's keys pay for the wrong scope; past 1 % the
+    fastest wins."""
+    def winner(**us):
+        recs = [{"op": "gemv", "n": 64, "batch": 65536, "scope": s, "pack": p, "median_us": us[k]}
+                for k, s, p in (("wave1", 1, 1), ("wave8", 1, 8), ("block1", 2, 1), ("sub4", 3, 4))]
+        return autotune.choose(recs)[("gemv", 64, 65536)]["winner"]
+    assert winner(wave1=192.7, wave8=190.56, block1=189.99, sub4=300.) == (1, 8)
+    assert winner(wave1=100.9, wave8=100.9, block1=100., sub4=100.2) == (1, 1)
+    assert winner(wave1=101.1, wave8=101.2, block1=100.1, sub4=100.) == (3, 4)
+    assert winner(wave1=100., wave8=99.9, block1=100., sub4=100.) == (1, 8)
